@@ -5,16 +5,17 @@
 // Sec. IV-A: the canonical operand layout maps directly to a GEMM).  Both
 // operands are K-contiguous, so the product is A * B^T per batch entry.
 //
-// 4M form on FP32 MFMA.  A complex row of A, read as 2k floats
-// (ar0, ai0, ar1, ai1, ...), times the real 2k-vector
+// Here are the 3M form of complex64 and both forms of split precision; the
+// 4M form of complex64 has a file of its own (kern_cgemm_c64.hip).
+//
+// 4M form.  A complex row of A, read as 2k floats (ar0, ai0, ar1, ai1, ...),
+// times the real 2k-vector
 //   (br0, -bi0, br1, -bi1, ...)  gives Re C,
 //   (bi0,  br0, bi1,  br1, ...)  gives Im C,
 // so C, viewed as an m x 2n float matrix, is a single real GEMM of
-// m x 2n x 2k whose B operand is built in registers from B's interleaved
-// values (a lane-dependent select and sign flip).  The MFMA output columns
-// then alternate re/im: exactly the interleaved complex64 layout, with no
-// de-interleaving anywhere.  8 real FLOPs per complex MAC (the paper's
-// counting convention, Sec. II-B).
+// m x 2n x 2k.  The MFMA output columns then alternate re/im: exactly the
+// interleaved complex64 layout, with no de-interleaving anywhere.  8 real
+// FLOPs per complex MAC (the paper's counting convention, Sec. II-B).
 //
 // 3M form: T1 = Ar Br, T2 = Ai Bi, T3 = (Ar+Ai)(Br+Bi), Re = T1 - T2,
 // Im = T3 - T1 - T2: three real GEMMs, 6 executed FLOPs per complex MAC.
@@ -52,78 +53,26 @@
 
 #include "bf16_split.hpp"
 #include "gemm_common.hpp"
+#include "gemm_tile.hpp"
 
 namespace tnc {
 
 namespace {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef short s8v __attribute__((ext_vector_type(8)));
 
 constexpr int BKC = 16;     // complex k per LDS stage
-constexpr int PITCH = 36;   // floats per LDS row (32 data + 4 pad)
 constexpr int SPITCH = 40;  // uint16 per LDS row of a bf16 plane (32 data + 8 pad)
-constexpr int GROUP_M = 8;
 
 template <int WM, int WN, int PW = 1>
 struct Shape {
   static constexpr int BM = 64 * WM;        // rows of C per workgroup
   static constexpr int BNC = 32 * WN * PW;  // complex columns of C per workgroup (PW per wave)
   static constexpr int NT = 64 * WM * WN;
-  static constexpr size_t lds_f32 = 2 * (BM + BNC) * PITCH * sizeof(float);
   // bf16 stage: A hi/lo planes of BM rows, B' hi/lo planes of 2*BNC real
   // columns (the 4M real operand, built at staging), two buffers
   static constexpr int BF16_STAGE = (2 * BM + 4 * BNC) * SPITCH;  // uint16 per buffer
   static constexpr size_t lds_bf16 = 2 * BF16_STAGE * sizeof(uint16_t);
 };
-
-struct TileCoord {
-  int64_t b, row0, col0;
-};
-
-// Tile of workgroup index `wg` (already in XCD order) within one GEMM:
-// batch entry, then groups of GROUP_M M-tiles swept along N.
-template <int BM, int BNC>
-__device__ __forceinline__ TileCoord tile_of(int64_t wg, int64_t tiles_m, int64_t tiles_n) {
-  const int64_t tpb = tiles_m * tiles_n;
-  const int64_t b = wg / tpb;
-  const int64_t r = wg - b * tpb;
-  const int64_t gw = static_cast<int64_t>(GROUP_M) * tiles_n;
-  const int64_t grp = r / gw;
-  const int64_t first_m = grp * GROUP_M;
-  const int64_t rem_m = tiles_m - first_m;
-  const int64_t gsz = rem_m < GROUP_M ? rem_m : GROUP_M;
-  const int64_t rr = r - grp * gw;
-  TileCoord tc;
-  tc.b = b;
-  tc.row0 = (first_m + rr % gsz) * BM;
-  tc.col0 = (rr / gsz) * BNC;
-  return tc;
-}
-
-template <int BM, int BNC>
-__device__ __forceinline__ TileCoord map_tile(int64_t tiles_m, int64_t tiles_n, int64_t total) {
-  int64_t wg = blockIdx.x;
-  const int64_t per = total >> 3;
-  if (wg < (per << 3)) wg = (wg & 7) * per + (wg >> 3);
-  return tile_of<BM, BNC>(wg, tiles_m, tiles_n);
-}
-
-// The same 8 x 4 blocks of tiles per XCD, but the eight XCDs work on the
-// same eight M-tiles at once (XCD x takes N-tiles x, x + 8, ...): the A
-// panels every XCD reads from its own L2 are then shared in the memory-side
-// cache, so HBM serves each once instead of once per XCD.  Needs whole
-// groups of 64 tiles (tiles_n a multiple of 8, GROUP_M M-tiles per group);
-// other shapes keep map_tile's order.
-template <int BM, int BNC>
-__device__ __forceinline__ TileCoord map_tile_shared(int64_t tiles_m, int64_t tiles_n, int64_t total) {
-  const int64_t wg = blockIdx.x;
-  if (tiles_n % 8 != 0 || tiles_m % GROUP_M != 0) return map_tile<BM, BNC>(tiles_m, tiles_n, total);
-  const int64_t g = wg >> 3, x = wg & 7;
-  return tile_of<BM, BNC>(64 * (g >> 3) + 8 * x + (g & 7), tiles_m, tiles_n);
-}
 
 // Global -> register staging of one K stage (VW complex per load).  With
 // SWZ the rows are dealt to the 8-lane groups in a permuted order within
@@ -190,23 +139,6 @@ struct Stage {
     }
   }
 
-  __device__ __forceinline__ static void put_f32(float* base, int row, int idx, const f4& v) {
-    float* p = base + row * PITCH + 2 * (idx % PER_ROW) * VW;
-    if constexpr (VW == 2) {
-      *reinterpret_cast<f4*>(p) = v;
-    } else {
-      p[0] = v.x;
-      p[1] = v.y;
-    }
-  }
-
-  __device__ __forceinline__ void store_f32(float* As, float* Bs, int tid) const {
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) put_f32(As, row_a(tid + S::NT * i), tid + S::NT * i, a[i]);
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i) put_f32(Bs, row_b(tid + S::NT * i), tid + S::NT * i, b[i]);
-  }
-
   // bf16 planes: the hi and lo halves of every float go to separate planes
   // (hardware round-to-nearest-even conversion of two floats at a time,
   // packed [first | second << 16]; lo = rne(x - hi), x - hi exact in
@@ -264,203 +196,6 @@ struct Stage {
     for (int i = 0; i < A_LOADS; ++i) put_split(Ah, Al, tid + S::NT * i, a[i]);
 #pragma unroll
     for (int i = 0; i < B_LOADS; ++i) put_split_b(Bh, Bl, tid + S::NT * i, b[i]);
-  }
-};
-
-// Output offsets within one batch entry of C, in complex elements: a row's
-// (offM[row], or row * n) plus a column's (offN[col], or col); -1 marks a
-// row or column outside C.  Permuted-store epilogues read them into
-// registers before issuing any store: C and the store tables are different
-// arrays, but the compiler cannot know it, so a table read between two
-// stores would wait for each read in turn.  (Row-major stores compute their
-// addresses inline: that keeps the main loop's register allocation, and so
-// its schedule, as it is without tables.)
-__device__ __forceinline__ int64_t col_offset(const GemmDesc& d, bool perm, int64_t col) {
-  return col < d.n ? (perm ? d.offN[col] : col) : -1;
-}
-
-// Rows 8*(v>>2) + 4*h + (v&3) of a 32-row MFMA block starting at row0, for
-// v = v0 .. v0+7 (the accumulator layout of a 32x32 MFMA).
-__device__ __forceinline__ void row_offsets8(const GemmDesc& d, bool perm, int64_t row0, int h, int v0,
-                                             int64_t (&o)[8]) {
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int v = v0 + u;
-    const int64_t row = row0 + 8 * (v >> 2) + 4 * h + (v & 3);
-    o[u] = row < d.m ? (perm ? d.offM[row] : row * d.n) : -1;
-  }
-}
-
-// Permuted store of a wave's 64 x 32 complex block held in the 4M layout
-// (MFMA 32x32 accumulators over real columns: even lanes hold the real and
-// odd lanes the imaginary part of one complex column, for rows v and v+1 of
-// each register pair).  One lane swap lets the even lane store row v's
-// complex value and the odd lane row v+1's, as 8-byte stores (half the
-// store instructions of a 4-byte store per part); each lane reads only the
-// row offsets of the rows it stores.  The swap runs in both lanes of a pair
-// whatever their row bounds (the column bound is shared by the pair).
-// val(i, j, v) is the lane's accumulated value of MFMA block (i, j), entry v.
-template <int PW = 1, class Val>
-__device__ __forceinline__ void store_perm_pairs(const GemmDesc& d, const TileCoord& tc, int wm, int wn, int lane,
-                                                 Val val) {
-  constexpr int NJ = 2 * PW;  // 32-real-column blocks per wave
-  const int h = lane >> 5, l32 = lane & 31;
-  const bool odd = l32 & 1;
-  float2* Cz = d.C + tc.b * d.m * d.n;
-  int64_t co[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) co[j] = col_offset(d, true, (tc.col0 * 2 + wn * 64 * PW + j * 32 + l32) >> 1);
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int v0 = 0; v0 < 16; v0 += 8) {
-      // this lane stores rows v = v0 + 2t + odd of the 32-row block
-      int64_t ro[4];
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int v = v0 + 2 * t + (odd ? 1 : 0);
-        const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-        ro[t] = row < d.m ? d.offM[row] : -1;
-      }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        if (co[j] < 0) continue;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const float a0 = val(i, j, v0 + 2 * t), a1 = val(i, j, v0 + 2 * t + 1);
-          const int sent = __builtin_bit_cast(int, odd ? a0 : a1);
-          // quad_perm [1,0,3,2]: exchange with the neighbouring lane
-          const float got = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, false));
-          if (ro[t] >= 0) Cz[ro[t] + co[j]] = odd ? make_float2(got, a1) : make_float2(a0, got);
-        }
-      }
-    }
-}
-
-// Store of a wave's 64 x 32 complex block from the 3M products (one 32x32
-// accumulator block per 32 rows: T1 = Ar Br, T2 = Ai Bi, T3 = (Ar+Ai)(Br+Bi);
-// Re = T1 - T2, Im = T3 - T1 - T2), row-major or through the offset tables.
-__device__ __forceinline__ void store_3m(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn, int lane,
-                                         const f16v (&t1)[2], const f16v (&t2)[2], const f16v (&t3)[2]) {
-  const int h = lane >> 5, l32 = lane & 31;
-  if (!perm) {  // row-major [M|N]: addresses from the indices alone
-    const int64_t col = tc.col0 + wn * 32 + l32;
-    if (col >= d.n) return;
-    float2* C = d.C + tc.b * d.m * d.n + col;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (row < d.m) {
-          float2 o;
-          o.x = t1[i][v] - t2[i][v];
-          o.y = t3[i][v] - t1[i][v] - t2[i][v];
-          C[row * d.n] = o;
-        }
-      }
-    return;
-  }
-  const int64_t co = col_offset(d, perm, tc.col0 + wn * 32 + l32);
-  if (co < 0) return;
-  float2* C = d.C + tc.b * d.m * d.n + co;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int v0 = 0; v0 < 16; v0 += 8) {
-      int64_t ro[8];
-      row_offsets8(d, perm, tc.row0 + wm * 64 + i * 32, h, v0, ro);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int v = v0 + u;
-        if (ro[u] >= 0) {
-          float2 o;
-          o.x = t1[i][v] - t2[i][v];
-          o.y = t3[i][v] - t1[i][v] - t2[i][v];
-          C[ro[u]] = o;
-        }
-      }
-    }
-}
-
-// ------------------------------------------------------------------ 4M, FP32 MFMA
-template <int WM, int WN, int VW>
-struct Ops4M {
-  using S = Shape<WM, WN>;
-  static constexpr bool kSwizzle = false;
-  static constexpr int kPW = 1;
-  static constexpr size_t kLds = S::lds_f32;
-  f16v acc[2][2];
-
-  __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  }
-
-  template <class St>
-  __device__ __forceinline__ void stage(const St& st, char* lds, int buf, int tid) const {
-    float* As = reinterpret_cast<float*>(lds) + buf * (S::BM + S::BNC) * PITCH;
-    st.store_f32(As, As + S::BM * PITCH, tid);
-  }
-
-  __device__ __forceinline__ void compute(const char* lds, int buf, int wm, int wn, int lane) {
-    const float* as = reinterpret_cast<const float*>(lds) + buf * (S::BM + S::BNC) * PITCH;
-    const float* bs = as + S::BM * PITCH;
-    const int h = lane >> 5, l32 = lane & 31, p = lane & 1;
-#pragma unroll
-    for (int g = 0; g < BKC / 4; ++g) {
-      const int koff = (4 * g + 2 * h) * 2;
-      f4 a[2], bt[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[i] = *reinterpret_cast<const f4*>(as + (wm * 64 + i * 32 + l32) * PITCH + koff);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const f4 r = *reinterpret_cast<const f4*>(bs + (wn * 32 + j * 16 + (l32 >> 1)) * PITCH + koff);
-        f4 t;
-        t.x = p ? r.y : r.x;
-        t.y = p ? r.x : -r.y;
-        t.z = p ? r.w : r.z;
-        t.w = p ? r.z : -r.w;
-        bt[j] = t;
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].x, bt[j].x, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].y, bt[j].y, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].z, bt[j].z, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].w, bt[j].w, acc[i][j], 0, 0, 0);
-        }
-    }
-  }
-
-  __device__ __forceinline__ void store(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn,
-                                        int lane) const {
-    const int h = lane >> 5, l32 = lane & 31;
-    // real column tc.col0*2 + wn*64 + j*32 + l32: complex column >> 1, re/im by parity
-    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
-    if (!perm) {  // row-major [M|N]: addresses from the indices alone
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int64_t col = (tc.col0 * 2 + wn * 64 + j * 32 + l32) >> 1;
-          if (col >= d.n) continue;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-            if (row < d.m) C[2 * (row * d.n + col)] = acc[i][j][v];
-          }
-        }
-      return;
-    }
-    store_perm_pairs(d, tc, wm, wn, lane, [&](int i, int j, int v) { return acc[i][j][v]; });
   }
 };
 
@@ -1385,7 +1120,7 @@ hipError_t launch_variant(const GemmDesc& d, int variant, bool bf16, hipStream_t
 }  // namespace
 
 void prepare_gemm_kernels() {
-  prepare_ops<Ops4M>(false);
+  prepare_gemm_c64();
   prepare_ops<Ops3M>(false);
   prepare_ops<OpsBF16x3>(true);
   prepare_ops<Ops3MBF16>(true);
@@ -1419,7 +1154,8 @@ int64_t grouped_layout(GroupedEntry* e, int n, int variant) {
 bool grouped_variant_ok(Form form, Prec prec, int variant) {
   if (prec == Prec::BF16X3)
     return form == Form::M3 ? grouped_ok<Ops3MBF16>(variant) : grouped_ok<OpsBF16x3>(variant);
-  return form == Form::M3 ? grouped_ok<Ops3M>(variant) : grouped_ok<Ops4M>(variant);
+  if (form == Form::M3) return grouped_ok<Ops3M>(variant);
+  return variant >= 0 && variant < kGemmVariants;
 }
 
 hipError_t launch_gemm_grouped(const GroupedEntry* dev, int n, int64_t total, int variant, Form form, Prec prec,
@@ -1429,7 +1165,7 @@ hipError_t launch_gemm_grouped(const GroupedEntry* dev, int n, int64_t total, in
     return form == Form::M3 ? launch_grouped_variant<Ops3MBF16>(dev, n, total, variant, true, s)
                             : launch_grouped_variant<OpsBF16x3>(dev, n, total, variant, true, s);
   if (form == Form::M3) return launch_grouped_variant<Ops3M>(dev, n, total, variant, false, s);
-  return launch_grouped_variant<Ops4M>(dev, n, total, variant, false, s);
+  return launch_gemm_c64_4m_grouped(dev, n, total, variant, s);
 }
 
 hipError_t launch_gemm_presplit(const GemmDesc& d, void* planes, bool have_a, bool have_b, hipStream_t s) {
@@ -1518,7 +1254,7 @@ hipError_t launch_gemm(const GemmDesc& d, GemmKernel kind, int variant, Form for
     return form == Form::M3 ? launch_variant<Ops3MBF16>(d, variant, true, s)
                             : launch_variant<OpsBF16x3>(d, variant, true, s);
   if (form == Form::M3) return launch_variant<Ops3M>(d, variant, false, s);
-  return launch_variant<Ops4M>(d, variant, false, s);
+  return launch_gemm_c64_4m(d, variant, s);
 }
 
 }  // namespace tnc

@@ -1,0 +1,522 @@
+// complex64 GEMM in the 4M form on the bf16 matrix pipe, at float32
+// precision:  C[b,i,j] = sum_l A[b,i,l] B[b,j,l].
+//
+// A float32 has 24 significant bits, a bf16 eight, so x = hi + mid + lo with
+// hi = rne(x), mid = rne(x - hi), lo = x - hi - mid, every difference and lo
+// itself exact: the operands keep all their bits.  Of the nine products of
+// two such sums six are formed (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi;
+// the others are below 2^-24 of the product, about 2^-26 rms), each exact in
+// float32, and added up by the bf16 MFMA in float32.  A bf16 MFMA adds 16
+// products per rounding of the accumulator where the FP32 MFMA adds them one
+// by one (it is a chain of FMAs), so with six products per term there are 6
+// roundings per 16 terms instead of 16, and the result is nearer to the exact
+// one than the FP32 pipe's.
+//
+// Where the split is not exact the tile is computed again on the FP32 pipe
+// (fp32_tile below), so every input that a float32 can hold means what it
+// meant there: a remainder that is a subnormal float32 (|x| below about
+// 2^-102: bf16 has no bits there) is noticed while the operands are staged,
+// infinities, NaNs and values that round to a bf16 infinity make the tile's
+// own sums non-finite, which is looked at once at the end.
+//
+// 4M form as one real GEMM of m x 2n x 2k: a complex row of A read as 2k
+// floats, times (br, -bi, ...) for Re C and (bi, br, ...) for Im C; both real
+// rows of B' are laid out at staging (a sign flip and a swap of packed
+// halves).
+#include <atomic>
+#include <type_traits>
+
+#include "gemm_tile.hpp"
+
+namespace tnc {
+
+namespace {
+
+constexpr int XK = 8;  // complex k per LDS stage: 16 real, one bf16 MFMA step
+
+// The next part of x and y, packed [x | y << 16], which it is taken off.
+__device__ __forceinline__ uint32_t take_part(float& x, float& y) {
+  typedef float fv2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bv2 __attribute__((ext_vector_type(2)));
+  const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((fv2){x, y}, bv2));
+  x -= __uint_as_float(w << 16);
+  y -= __uint_as_float(w & 0xFFFF0000u);
+  return w;
+}
+
+// The last part.  It is what is left of x and y, exactly, unless that is a
+// subnormal float32: `tiny` keeps the smallest (bits << 1) - 1 seen, where
+// zero wraps to the top and a subnormal value ends up below 0x00ffffff.
+__device__ __forceinline__ uint32_t last_part(float x, float y, uint32_t& tiny) {
+  typedef float fv2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bv2 __attribute__((ext_vector_type(2)));
+  const uint32_t tx = (__float_as_uint(x) << 1) - 1, ty = (__float_as_uint(y) << 1) - 1;
+  const uint32_t t = tx < ty ? tx : ty;
+  tiny = tiny < t ? tiny : t;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((fv2){x, y}, bv2));
+}
+
+// f(integral_constant 0), ..., f(N - 1): loops whose counters index registers
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void each(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    each<N, I + 1>(f);
+  }
+}
+
+// A tile's coordinates in scalar registers (every lane has the same).
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x >> 32));
+  return static_cast<int64_t>((uint64_t{hi} << 32) | lo);
+}
+__device__ __forceinline__ TileCoord uniform(const TileCoord& t) {
+  return {uniform(t.b), uniform(t.row0), uniform(t.col0)};
+}
+
+typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));  // rows of odd length start on 8 bytes
+
+template <int WM, int WN, int PW>
+struct XTile {
+  static constexpr int BM = 64 * WM, BNC = 32 * WN * PW, NT = 64 * WM * WN;
+  static constexpr int NJ = 2 * PW;                      // 32-column blocks of the real view per wave
+  static constexpr int PA = BM * 32, PB = 2 * BNC * 32;  // bytes of one part's plane: 16 bf16 per row
+  static constexpr int STAGE = 3 * (PA + PB);
+  static constexpr size_t kLds = 2 * STAGE;
+  static constexpr int AL = BM * 4 / NT, BL = BNC * 4 / NT;  // 16-byte loads per thread and stage
+  static_assert(AL >= 1 && AL * NT == BM * 4 && BL >= 1 && BL * NT == BNC * 4, "staging must tile evenly");
+
+  f16v acc[2][NJ];
+  f16v t[2];  // sums of one stage: of the block at hand and of the one before
+  f4 ra[AL], rb[BL];
+  const float2 *pa[AL], *pb[BL];
+  uint32_t tiny;
+
+  // rows past the edge repeat the last one: their products are not stored
+  __device__ __forceinline__ void init(const float2* A, const float2* B, const GemmDesc& d, const TileCoord& tc,
+                                       int tid) {
+    const int64_t ld = row_stride(d);
+#pragma unroll
+    for (int i = 0; i < AL; ++i) {
+      int64_t r = tc.row0 + ((tid + NT * i) >> 2);
+      r = r < d.m ? r : d.m - 1;
+      pa[i] = A + r * ld + 2 * (tid & 3);
+    }
+#pragma unroll
+    for (int i = 0; i < BL; ++i) {
+      int64_t r = tc.col0 + ((tid + NT * i) >> 2);
+      r = r < d.n ? r : d.n - 1;
+      pb[i] = B + r * ld + 2 * (tid & 3);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    t[0] = t[1] = f16v{};
+    tiny = 0xFFFFFFFFu;
+  }
+
+  // The stage at the pointers, which move on.  CHECK: the row ends `left`
+  // complex k (1 .. XK) into it; what would lie behind reads as zero (its
+  // last element is loaded instead, so no lane branches).
+  template <bool CHECK>
+  __device__ __forceinline__ static f4 fetch(const float2*& p, int left, int tid) {
+    f4 v;
+    if constexpr (CHECK) {
+      const int c = 2 * (tid & 3), last = left - 1 - c;
+      const float2 x = p[last < 0 ? last : 0], y = p[last < 1 ? last : 1];
+      v.x = last >= 0 ? x.x : 0.f;
+      v.y = last >= 0 ? x.y : 0.f;
+      v.z = last >= 1 ? y.x : 0.f;
+      v.w = last >= 1 ? y.y : 0.f;
+    } else {
+      v = *reinterpret_cast<const f4u*>(p);
+    }
+    p += XK;
+    return v;
+  }
+  // LDS rows are 32 bytes, their two 16-byte halves swapped every 8 rows
+  // (half ^ ((row >> 3) & 1)): the fragment reads of 16 lanes (16 rows, one
+  // half) and the 8-byte stores of 32 lanes (8 rows) touch every bank once.
+  // Within 16 rows of B' the even rows come first (row r at ((r & 1) << 3) |
+  // (r >> 1 & 7)), so that the rows that one store instruction writes are
+  // neighbours.
+  // Staging of a stage, in units of one 16-byte load (the first AL of A,
+  // the others of B) and eight pieces each, so that it can be dealt out
+  // between the MFMAs of the stage before.
+  static constexpr int U = AL + BL, PIECES = 8;
+  uint32_t w[2][3];  // the unit's parts: of its first and second complex value
+
+  template <int u>
+  __device__ __forceinline__ f4& staged() {
+    if constexpr (u < AL)
+      return ra[u];
+    else
+      return rb[u - AL];
+  }
+  template <int u, int q>
+  __device__ __forceinline__ void piece(char* lds, int tid) {
+    const int r = tid >> 2, c = tid & 3;
+    f4& v = staged<u>();
+    if constexpr (q < 6) {
+      constexpr int e = q / 3, part = q % 3;
+      float x = v[2 * e], y = v[2 * e + 1];
+      if constexpr (part < 2) {
+        w[e][part] = take_part(x, y);
+        v[2 * e] = x;
+        v[2 * e + 1] = y;
+      } else {
+        w[e][2] = last_part(x, y, tiny);
+      }
+      return;
+    }
+    if constexpr (u < AL) {
+      if (q == 7) return;
+      char* p = lds + r * 32 + ((8 * c) ^ (((r >> 3) & 1) << 4)) + u * (NT / 4) * 32;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) *reinterpret_cast<uint2*>(p + t * PA) = make_uint2(w[0][t], w[1][t]);
+      return;
+    }
+    char* p = lds + 3 * PA + (((2 * r) & ~15) | (r & 7)) * 32 + (u - AL) * (NT / 4) * 64;
+    if (q == 6) {
+      constexpr uint32_t NEG_IM = 0x80000000u;
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        *reinterpret_cast<uint2*>(p + t * PB + 8 * c) = make_uint2(w[0][t] ^ NEG_IM, w[1][t] ^ NEG_IM);
+    } else {
+      auto swap = [](uint32_t x) { return (x >> 16) | (x << 16); };
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        *reinterpret_cast<uint2*>(p + t * PB + 256 + ((8 * c) ^ 16)) = make_uint2(swap(w[0][t]), swap(w[1][t]));
+    }
+  }
+  template <bool CHECK, int u>
+  __device__ __forceinline__ void load_unit(int left, int tid) {
+    if constexpr (u < AL)
+      ra[u] = fetch<CHECK>(pa[u], left, tid);
+    else
+      rb[u - AL] = fetch<CHECK>(pb[u - AL], left, tid);
+  }
+  // `left` complex k are left of the rows
+  __device__ __forceinline__ void load(int64_t left, int tid) {
+    if (left >= XK)
+      each<U>([&](auto u) { load_unit<false, u>(0, tid); });
+    else
+      each<U>([&](auto u) { load_unit<true, u>(static_cast<int>(left), tid); });
+  }
+  __device__ __forceinline__ void stage(char* lds, int tid) {
+    each<U * PIECES>([&](auto q) { piece<q / PIECES, q % PIECES>(lds, tid); });
+  }
+
+  __device__ __forceinline__ static f16v mm(const s8v& a, const s8v& b, const f16v& c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+  }
+
+  // One stage: the products of `cur`; with NEXT the staged registers are
+  // split into `nxt` and loaded again (whole stages).  Each 32 x 32 block's
+  // six products of the stage are summed from zero and then added to its
+  // accumulator by the VALU.
+  template <bool NEXT>
+  __device__ __forceinline__ void step(const char* cur, char* nxt, int tid, int wm, int wn, int lane) {
+    const int h = lane >> 5, r = lane & 31;
+    const char* a = cur + (wm * 64 + r) * 32 + ((h ^ ((r >> 3) & 1)) << 4);
+    const char* b = cur + 3 * PA + (wn * 64 * PW + ((r & 16) | ((r & 1) << 3) | ((r >> 1) & 7))) * 32 +
+                    ((h ^ (r & 1)) << 4);
+    constexpr int SLOTS = 12 * NJ, Q = U * PIECES;
+    s8v fa[2][3], fb[2][3];
+    auto read_a = [&](int i, int q) { fa[i][q] = *reinterpret_cast<const s8v*>(a + q * PA + i * 1024); };
+    auto read_b = [&](int j, int q) { fb[j & 1][q] = *reinterpret_cast<const s8v*>(b + q * PB + j * 1024); };
+    read_a(0, 0);
+    read_b(0, 2);
+    read_b(0, 1);
+    read_a(0, 1);
+    read_b(0, 0);
+    read_a(0, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    each<SLOTS>([&](auto slot) {
+      constexpr int s = slot, c = s / 6, k6 = s % 6, i = c & 1, j = c >> 1;
+      // hi hi last; each product shares a fragment with the one before
+      constexpr int xa[6] = {0, 0, 1, 1, 2, 0}, xb[6] = {2, 1, 1, 0, 0, 0};
+      if constexpr (k6 == 0) t[i] = f16v{};
+      t[i] = mm(fa[i][xa[k6]], fb[j & 1][xb[k6]], t[i]);
+      if constexpr (c == 0 && k6 < 3) read_a(1, k6);
+      if constexpr (i == 1 && j + 1 < NJ) {  // the next block's, once this one's part is done with
+        if constexpr (k6 == 0) read_b(j + 1, 0);
+        if constexpr (k6 == 1) read_b(j + 1, 2);
+        if constexpr (k6 == 3) read_b(j + 1, 1);
+      }
+      if constexpr (k6 >= 2) {  // four of the sums of the block before
+        f16v& d = acc[i ^ 1][c == 0 ? NJ - 1 : (c - 1) >> 1];
+        each<4>([&](auto v) { d[4 * (k6 - 2) + v] += t[i ^ 1][4 * (k6 - 2) + v]; });
+      }
+      if constexpr (NEXT)
+        each<(s + 1) * Q / SLOTS - s * Q / SLOTS>([&](auto n) {
+          constexpr int q = s * Q / SLOTS + n;
+          piece<q / PIECES, q % PIECES>(nxt, tid);
+          if constexpr (q % PIECES == 7) load_unit<false, q / PIECES>(0, tid);
+        });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+
+  // The tile again, on the FP32 pipe, straight from global memory and back:
+  // right for every float32, and only as fast as such tiles are rare.
+  __device__ __forceinline__ static void fp32_tile(const GemmDesc& d, const TileCoord& tc, int wm, int wn, int lane) {
+    int64_t oa, ob;
+    batch_offsets(d, tc.b, oa, ob);
+    const int64_t ld = row_stride(d);
+    const int h = lane >> 5, l32 = lane & 31;
+    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
+#pragma unroll 1
+    for (int ij = 0; ij < 2 * NJ; ++ij) {
+      const int64_t row0 = tc.row0 + wm * 64 + (ij & 1) * 32;
+      const int64_t col = tc.col0 + wn * 32 * PW + (ij >> 1) * 16 + (l32 >> 1);
+      const float2* x = d.A + oa + (row0 + l32 < d.m ? row0 + l32 : d.m - 1) * ld + h;
+      const float2* y = d.B + ob + (col < d.n ? col : d.n - 1) * ld + h;
+      f16v c = {};
+#pragma unroll 1
+      for (int64_t l = 0; l < d.k; l += 2) {
+        float2 u = make_float2(0.f, 0.f), w = u;
+        if (l + h < d.k) {
+          u = x[l];
+          w = y[l];
+        }
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.x, lane & 1 ? w.y : w.x, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.y, lane & 1 ? w.x : -w.y, c, 0, 0, 0);
+      }
+      if (col >= d.n) continue;
+      const int64_t co = d.offM ? d.offN[col] : col;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int64_t row = row0 + 8 * (v >> 2) + 4 * h + (v & 3);
+        if (row < d.m) C[2 * ((d.offM ? d.offM[row] : row * d.n) + co)] = c[v];
+      }
+    }
+  }
+
+  // The tile's sums; false if they have to come from the FP32 pipe.
+  __device__ __forceinline__ bool run(const GemmDesc& d, const TileCoord& tc, char* lds, int tid, int wm, int wn,
+                                      int lane) {
+    int64_t oa, ob;
+    batch_offsets(d, tc.b, oa, ob);
+    const float2* A = d.A + uniform(oa);
+    const float2* B = d.B + uniform(ob);
+    init(A, B, d, tc, tid);
+    const int64_t k = d.k, nk = (k + XK - 1) / XK, full = k / XK;
+    load(k, tid);
+    stage(lds, tid);
+    if (nk > 1) load(k - XK, tid);
+    __syncthreads();
+    int64_t kt = 0;
+    for (; kt + 2 < full; ++kt) {
+      char* cur = lds + (kt & 1) * STAGE;
+      char* nxt = lds + ((kt & 1) ^ 1) * STAGE;
+      step<true>(cur, nxt, tid, wm, wn, lane);
+      __syncthreads();
+    }
+    for (; kt < nk; ++kt) {
+      char* cur = lds + (kt & 1) * STAGE;
+      char* nxt = lds + ((kt & 1) ^ 1) * STAGE;
+      if (kt + 1 < nk) stage(nxt, tid);
+      if (kt + 2 < nk) load(k - (kt + 2) * XK, tid);
+      step<false>(cur, nxt, tid, wm, wn, lane);
+      __syncthreads();
+    }
+    acc[1][NJ - 1] += t[1];
+    float s = 0.f;  // NaN if any sum is not finite
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s = fmaf(acc[i][j][v], 0.f, s);
+    return !__syncthreads_or(tiny < 0x00FFFFFFu || !(s == 0.f));
+  }
+
+  __device__ __forceinline__ void store(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn,
+                                        int lane) const {
+    if (perm) {
+      store_perm_pairs<PW>(d, tc, wm, wn, lane, [&](int i, int j, int v) { return acc[i][j][v]; });
+      return;
+    }
+    const int h = lane >> 5, l32 = lane & 31;
+    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int64_t col = (tc.col0 * 2 + wn * 64 * PW + j * 32 + l32) >> 1;
+        if (col >= d.n) continue;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+          if (row < d.m) C[2 * (row * d.n + col)] = acc[i][j][v];
+        }
+      }
+  }
+};
+
+template <int WM, int WN, int PW, bool PERM>
+__global__ __launch_bounds__(64 * WM * WN, 2) void cgemm_c64(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
+                                                            int64_t total) {
+  using T = XTile<WM, WN, PW>;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const TileCoord tc = uniform(map_tile_shared<T::BM, T::BNC>(tiles_m, tiles_n, total));
+  T t;
+  if (t.run(d, tc, lds, tid, wm, wn, lane))
+    t.store(d, PERM, tc, wm, wn, lane);
+  else
+    T::fp32_tile(d, tc, wm, wn, lane);
+}
+
+// Persistent grouped form: see GroupedEntry.  Tiles are dealt to the 8 XCDs
+// in contiguous ranges (tiles of one entry stay on few XCDs, whose L2 they
+// share) and each workgroup of an XCD takes every nb-th tile of its range.
+template <int WM, int WN, int PW>
+__global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void cgemm_c64_grouped(
+    const GroupedEntry* __restrict__ tab, int n, int64_t total) {
+  using T = XTile<WM, WN, PW>;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int64_t per = (total + 7) >> 3;  // tiles per XCD
+  const int64_t xcd = blockIdx.x & 7, nb = gridDim.x >> 3;
+  for (int64_t q = blockIdx.x >> 3; q < per; q += nb) {
+    const int64_t x = xcd * per + q;
+    if (x >= total) break;
+    int e = 0;
+    while (e + 1 < n && tab[e + 1].tile0 <= x) ++e;
+    const GemmDesc& d = tab[e].d;
+    const TileCoord tc = uniform(tile_of<T::BM, T::BNC>(x - tab[e].tile0, tab[e].tiles_m, tab[e].tiles_n));
+    // opaque, so that what depends on the lane is worked out again for each
+    // tile instead of kept in registers across the main loop
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    T t;
+    if (t.run(d, tc, lds, tid, wm, wn, lane))
+      t.store(d, d.offM != nullptr, tc, wm, wn, lane);
+    else
+      T::fp32_tile(d, tc, wm, wn, lane);
+  }
+}
+
+// LDS above 64 KiB must be allowed per kernel, once per device.
+template <class F>
+hipError_t allow_lds(F* kernel, size_t lds, std::atomic<uint64_t>& done) {
+  if (lds <= 65536) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = uint64_t{1} << (dev & 63);
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          static_cast<int>(lds));
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_acq_rel);
+  return e;
+}
+
+template <int WM, int WN, int PW, bool PERM>
+hipError_t ready_one() {
+  static std::atomic<uint64_t> done{0};
+  return allow_lds(cgemm_c64<WM, WN, PW, PERM>, XTile<WM, WN, PW>::kLds, done);
+}
+template <int WM, int WN, int PW>
+hipError_t ready_grouped() {
+  static std::atomic<uint64_t> done{0};
+  return allow_lds(cgemm_c64_grouped<WM, WN, PW>, XTile<WM, WN, PW>::kLds, done);
+}
+
+template <int WM, int WN, int PW, bool PERM>
+hipError_t launch_one(const GemmDesc& d, hipStream_t s) {
+  using T = XTile<WM, WN, PW>;
+  const int64_t tiles_m = (d.m + T::BM - 1) / T::BM;
+  const int64_t tiles_n = (d.n + T::BNC - 1) / T::BNC;
+  const int64_t total = tiles_m * tiles_n * d.h;
+  // one workgroup per tile; the grid's work-items must fit 32 bits
+  if (total * T::NT > 0xFFFFFFFFLL) return hipErrorInvalidValue;
+  const hipError_t e = ready_one<WM, WN, PW, PERM>();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((cgemm_c64<WM, WN, PW, PERM>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s, d,
+                     tiles_m, tiles_n, total);
+  return hipGetLastError();
+}
+template <int WM, int WN, int PW>
+hipError_t launch_shape(const GemmDesc& d, hipStream_t s) {
+  return d.offM ? launch_one<WM, WN, PW, true>(d, s) : launch_one<WM, WN, PW, false>(d, s);
+}
+
+// Persistent grid: a multiple of 8 (one range of tiles per XCD), never more
+// than the tiles; at most 512 workgroups (two per compute unit), or 2048
+// waves for the shapes of fewer than four waves.
+template <int WM, int WN, int PW>
+hipError_t launch_grouped_shape(const GroupedEntry* tab, int n, int64_t total, hipStream_t s) {
+  using T = XTile<WM, WN, PW>;
+  const hipError_t e = ready_grouped<WM, WN, PW>();
+  if (e != hipSuccess) return e;
+  constexpr int64_t cap = WM * WN < 4 ? 2048 / (WM * WN) : 512;
+  int64_t grid = (total + 7) / 8 * 8;
+  if (grid > cap) grid = cap;
+  hipLaunchKernelGGL((cgemm_c64_grouped<WM, WN, PW>), dim3(static_cast<unsigned>(grid)), dim3(T::NT), T::kLds, s, tab, n,
+                     total);
+  return hipGetLastError();
+}
+
+template <int WM, int WN, int PW>
+void prepare_shape() {
+  (void)ready_one<WM, WN, PW, false>();
+  (void)ready_one<WM, WN, PW, true>();
+  (void)ready_grouped<WM, WN, PW>();
+}
+
+}  // namespace
+
+void prepare_gemm_c64() {
+  prepare_shape<4, 1, 2>();
+  prepare_shape<2, 2, 2>();
+  prepare_shape<4, 2, 2>();
+  prepare_shape<2, 4, 1>();
+}
+
+// The 128 x 128 tile runs as four wide waves (each A fragment feeds four
+// column blocks: fewer LDS reads), or as eight narrow ones where a launch
+// has no more tiles than compute units: a CU then has two waves per SIMD
+// from its one workgroup instead of one (6 x 1000 x 500 x 777, 192 tiles:
+// 0.141 -> 0.125 ms; 8192 x 8192 x 4096, 4096 tiles: 10.3 -> 9.8 ms the
+// other way).  An element's sums do not depend on which of them ran.
+hipError_t launch_gemm_c64_4m(const GemmDesc& d, int variant, hipStream_t s) {
+  switch (variant) {
+    case 0: return launch_shape<2, 2, 1>(d, s);
+    case 1: return launch_shape<4, 1, 2>(d, s);
+    case 2:
+      if (d.h * ((d.m + 127) / 128) * ((d.n + 127) / 128) <= 256) return launch_shape<2, 4, 1>(d, s);
+      return launch_shape<2, 2, 2>(d, s);
+    case 3: return launch_shape<4, 2, 2>(d, s);
+    case 4: return launch_shape<1, 2, 1>(d, s);
+    case 5: return launch_shape<2, 1, 1>(d, s);
+    case 6: return launch_shape<1, 1, 1>(d, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_gemm_c64_4m_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, hipStream_t s) {
+  switch (variant) {
+    case 0: return launch_grouped_shape<2, 2, 1>(tab, n, total, s);
+    case 1: return launch_grouped_shape<4, 1, 2>(tab, n, total, s);
+    case 2:
+      if (total <= 256) return launch_grouped_shape<2, 4, 1>(tab, n, total, s);
+      return launch_grouped_shape<2, 2, 2>(tab, n, total, s);
+    case 3: return launch_grouped_shape<4, 2, 2>(tab, n, total, s);
+    case 4: return launch_grouped_shape<1, 2, 1>(tab, n, total, s);
+    case 5: return launch_grouped_shape<2, 1, 1>(tab, n, total, s);
+    case 6: return launch_grouped_shape<1, 1, 1>(tab, n, total, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace tnc

@@ -148,6 +148,10 @@ int64_t grouped_layout(GroupedEntry* e, int n, int variant);
 bool grouped_variant_ok(Form form, Prec prec, int variant);
 hipError_t launch_gemm_grouped(const GroupedEntry* dev, int n, int64_t total, int variant, Form form, Prec prec,
                                hipStream_t s);
+// The complex64 4M form (called by launch_gemm and its siblings).
+hipError_t launch_gemm_c64_4m(const GemmDesc& d, int variant, hipStream_t s);
+hipError_t launch_gemm_c64_4m_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, hipStream_t s);
+void prepare_gemm_c64();
 hipError_t launch_gemm_valu(const GemmDesc& d, GemmKernel kind, Prec prec, hipStream_t s);
 // Split-bf16x3 on operands split once into bf16 planes (large steps of one
 // batch entry, h == 1, no operand tables): the launch splits A and B into
