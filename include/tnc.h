@@ -59,8 +59,12 @@ typedef enum {
   TNC_E_UNSUPPORTED = 6   /* request needs something not built here    */
 } tnc_status;
 
-/* Arithmetic of the GEMMs.  C64: complex64 operands, FP32 MFMA, FP32
- * accumulate (the paper's setting, Sec. V).  BF16X3: each float32 operand
+/* Arithmetic of the GEMMs.  C64: complex64 operands, float32 products and
+ * accumulation (the paper's setting, Sec. V).  Its 4M form runs on the bf16
+ * matrix pipe with every operand split exactly into three bf16 parts; its
+ * error against exact arithmetic is below that of a chain of float32 FMAs,
+ * and values that such a split cannot hold (infinities, NaNs, the far ends
+ * of the exponent range) are computed on the FP32 pipe.  BF16X3: each float32 operand
  * plane is split into bf16 hi + lo (round to nearest even) and every real
  * product is a_hi*b_hi + a_hi*b_lo + a_lo*b_hi on bf16 MFMA with FP32
  * accumulate (an extension, not in the paper). */
