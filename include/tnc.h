@@ -333,12 +333,11 @@ tnc_status tnc_permute(tnc_ctx ctx, const void* in, void* out, int32_t rank,
  * until the process ends, instead of memory the library allocates.
  * TNC_E_NOMEM if the tables need more than 1 MiB (decided on the host
  * before any device work; the tables of a 2^30-element permutation take
- * about 130 KiB).  Every call on one GPU shares that area and leaves its
- * own tables in it: a call first waits for the context's stream (earlier
- * calls on it have finished reading the area), copies its tables and waits
- * for the copy, then launches.  Calls that overlap on one GPU from
- * different streams or threads race on the area.  Small permutations that
- * run as a plain gather use no tables and do not wait. */
+ * about 130 KiB).  Every call on one GPU shares that area: its launches are
+ * ordered behind those of the call before it, whatever their streams and
+ * threads.  Neither form waits on the host, and neither can be captured in a
+ * graph (TNC_E_DEVICE), except small permutations that run as a plain
+ * gather: they use no tables. */
 tnc_status tnc_permute_noalloc(tnc_ctx ctx, const void* in, void* out, int32_t rank,
                                const int64_t* extents, const int32_t* perm);
 /* Batched complex GEMM with both operands K-contiguous:

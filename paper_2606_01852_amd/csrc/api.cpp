@@ -146,7 +146,7 @@ tnc_status tnc_ctx_create(int device, void* arena, size_t arena_bytes, void* str
     // per-device address of the allocation-free permute tables, looked up
     // once here with the device current; if the lookup fails, the error is
     // cleared and tnc_permute_noalloc looks again and reports it
-    void* tables = nullptr;
+    StaticTables* tables = nullptr;
     if (static_table_area(device, &tables) != hipSuccess) (void)hipGetLastError();
     load_tune_cache(c);
     prepare_gemm_kernels();
@@ -653,13 +653,10 @@ tnc_status tnc_plan_result_norm2(tnc_plan plan, double* out) {
 
 namespace {
 
-// A checked permutation of a complex64 tensor: its gather-permute and, when
-// tiled, the index tables packed into one host blob (parts 256-byte
-// aligned, offsets in off[]).
+// A checked permutation of a complex64 tensor.
 struct PermuteJob {
-  PermuteHost ph;
-  std::vector<uint8_t> blob;
-  size_t off[6] = {0, 0, 0, 0, 0, 0};
+  PermuteShape shape;
+  GatherDesc plain;
 };
 
 PermuteJob plan_permute(int32_t rank, const int64_t* extents, const int32_t* perm) {
@@ -681,48 +678,44 @@ PermuteJob plan_permute(int32_t rank, const int64_t* extents, const int32_t* per
     st[q] = ist[p];
   }
   PermuteJob j;
-  j.ph = build_permute(ext, st);
-  if (j.ph.tiled) {
-    auto put = [&](const void* src, size_t bytes) {
-      const size_t off = (j.blob.size() + 255) / 256 * 256;
-      j.blob.resize(off + bytes);
-      std::memcpy(j.blob.data() + off, src, bytes);
-      return off;
-    };
-    const PermuteHost& ph = j.ph;
-    j.off[0] = put(ph.tile_in.data(), ph.tile_in.size() * 4);
-    j.off[1] = put(ph.tile_slot_r.data(), ph.tile_slot_r.size() * 4);
-    j.off[2] = put(ph.tile_out.data(), ph.tile_out.size() * 4);
-    j.off[3] = put(ph.tile_slot_w.data(), ph.tile_slot_w.size() * 4);
-    j.off[4] = put(ph.lo_tab.data(), ph.lo_tab.size() * 8);
-    j.off[5] = put(ph.hi_tab.data(), ph.hi_tab.size() * 8);
-  }
+  j.shape = permute_shape(ext, st, j.plain);
   return j;
 }
 
-// Launch a planned permutation; `tables` is the device copy of j.blob.
-hipError_t launch_permute_job(const PermuteJob& j, const void* in, void* out, const char* tables, hipStream_t s) {
-  if (!j.ph.tiled) {
-    GatherDesc g = j.ph.plain;
+// Enqueue a planned permutation: its tables into `tables` (shape.bytes() of
+// device memory), then the permutation that reads them.
+void enqueue_permute(const PermuteJob& j, const void* in, void* out, char* tables, hipStream_t s) {
+  if (!j.shape.tiled) {
+    GatherDesc g = j.plain;
     g.in = static_cast<const float2*>(in);
     g.out = static_cast<float2*>(out);
-    return launch_gather(g, s);
+    check_hip(launch_gather(g, s), "permute launch");
+    return;
   }
+  check_hip(launch_permute_tables(j.shape, tables, s), "permute tables");
   PermuteDesc d{};
   d.in = static_cast<const float2*>(in);
   d.out = static_cast<float2*>(out);
-  d.tile_in = reinterpret_cast<const int32_t*>(tables + j.off[0]);
-  d.tile_slot_r = reinterpret_cast<const int32_t*>(tables + j.off[1]);
-  d.tile_out = reinterpret_cast<const int32_t*>(tables + j.off[2]);
-  d.tile_slot_w = reinterpret_cast<const int32_t*>(tables + j.off[3]);
-  d.lo_tab = reinterpret_cast<const int64_t*>(tables + j.off[4]);
-  d.hi_tab = reinterpret_cast<const int64_t*>(tables + j.off[5]);
-  d.n_tiles = j.ph.n_tiles;
-  d.L = j.ph.L;
-  d.T = j.ph.T;
-  d.slots = j.ph.slots;
-  d.pairs = j.ph.pairs ? 1 : 0;
-  return launch_permute(d, s);
+  d.tile_in = reinterpret_cast<const int32_t*>(tables + j.shape.offset(0));
+  d.tile_slot_r = reinterpret_cast<const int32_t*>(tables + j.shape.offset(1));
+  d.tile_out = reinterpret_cast<const int32_t*>(tables + j.shape.offset(2));
+  d.tile_slot_w = reinterpret_cast<const int32_t*>(tables + j.shape.offset(3));
+  d.lo_tab = reinterpret_cast<const int64_t*>(tables + j.shape.offset(4));
+  d.hi_tab = reinterpret_cast<const int64_t*>(tables + j.shape.offset(5));
+  d.n_tiles = j.shape.n_tiles;
+  d.L = static_cast<int32_t>(j.shape.L);
+  d.T = j.shape.T;
+  d.slots = j.shape.slots;
+  d.pairs = j.shape.pairs;
+  check_hip(launch_permute(d, s), "permute launch");
+}
+
+// The table areas are shared by calls, in stream order: a graph that had
+// captured one would share it with calls made outside its stream's order.
+void refuse_capture(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  check_hip(hipStreamIsCapturing(s, &st), "capture status");
+  if (st != hipStreamCaptureStatusNone) fail(TNC_E_DEVICE, "a tiled permutation cannot be captured");
 }
 
 }  // namespace
@@ -736,12 +729,18 @@ tnc_status tnc_permute(tnc_ctx ctx, const void* in, void* out, int32_t rank, con
   const PermuteJob j = plan_permute(rank, extents, perm);
   Ctx& c = *ctx->c;
   set_device(c);
-  if (j.ph.tiled) {
-    check_hip(hipStreamSynchronize(c.stream), "stream synchronize");
-    if (c.scratch.bytes < j.blob.size()) c.scratch.alloc(j.blob.size());
-    check_hip(hipMemcpy(c.scratch.ptr, j.blob.data(), j.blob.size(), hipMemcpyHostToDevice), "table upload");
+  if (j.shape.tiled) {
+    refuse_capture(c.stream);
+    // every call on the context's stream writes its tables here before the
+    // launch that reads them, so calls need not wait for each other; only a
+    // larger area does (the first: 1 MiB, a 2^30-element permutation's tables
+    // take about 130 KiB)
+    if (c.scratch.bytes < j.shape.bytes()) {
+      check_hip(hipStreamSynchronize(c.stream), "stream synchronize");
+      c.scratch.alloc(std::max(j.shape.bytes(), kStaticPermuteTableBytes));
+    }
   }
-  check_hip(launch_permute_job(j, in, out, static_cast<const char*>(c.scratch.ptr), c.stream), "permute launch");
+  enqueue_permute(j, in, out, static_cast<char*>(c.scratch.ptr), c.stream);
   TNC_CATCH
 }
 
@@ -750,22 +749,22 @@ tnc_status tnc_permute_noalloc(tnc_ctx ctx, const void* in, void* out, int32_t r
   TNC_TRY
   if (!ctx || !in || !out || rank < 0 || (rank && (!extents || !perm))) fail(TNC_E_ARG, "bad arguments");
   const PermuteJob j = plan_permute(rank, extents, perm);
-  if (j.blob.size() > kStaticPermuteTableBytes)
-    fail(TNC_E_NOMEM, "the permutation's index tables need " + std::to_string(j.blob.size()) +
+  if (j.shape.bytes() > kStaticPermuteTableBytes)
+    fail(TNC_E_NOMEM, "the permutation's index tables need " + std::to_string(j.shape.bytes()) +
                           " bytes, above the fixed table area of " + std::to_string(kStaticPermuteTableBytes));
   Ctx& c = *ctx->c;
   set_device(c);
-  void* tables = nullptr;
-  if (j.ph.tiled) {
-    check_hip(static_table_area(c.device, &tables), "table area address");
-    // earlier launches on this stream may still read the shared tables: wait
-    // for them, copy the new tables, and wait for the copy (the host blob
-    // is pageable and goes away when this call returns)
-    check_hip(hipStreamSynchronize(c.stream), "stream synchronize");
-    check_hip(hipMemcpyAsync(tables, j.blob.data(), j.blob.size(), hipMemcpyHostToDevice, c.stream), "table upload");
-    check_hip(hipStreamSynchronize(c.stream), "table upload");
+  if (!j.shape.tiled) {
+    enqueue_permute(j, in, out, nullptr, c.stream);
+    return TNC_OK;
   }
-  check_hip(launch_permute_job(j, in, out, static_cast<const char*>(tables), c.stream), "permute launch");
+  refuse_capture(c.stream);
+  StaticTables* t = nullptr;
+  check_hip(static_table_area(c.device, &t), "table area address");
+  std::lock_guard<std::mutex> g(t->mu);
+  check_hip(hipStreamWaitEvent(c.stream, t->last_use, 0), "table area");
+  enqueue_permute(j, in, out, t->ptr, c.stream);
+  check_hip(hipEventRecord(t->last_use, c.stream), "table area");
   TNC_CATCH
 }
 

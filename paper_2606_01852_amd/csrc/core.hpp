@@ -134,6 +134,8 @@ struct PermuteHost {
 // Build the gather-permute out[w] = in[base + sum_d digit_d(w) * in_stride[d]]
 // for row-major output dims ext[].
 PermuteHost build_permute(const std::vector<int64_t>& ext, const std::vector<int64_t>& in_stride);
+// The same without its tables: the tile's digits, and the plain gather.
+PermuteShape permute_shape(const std::vector<int64_t>& ext, const std::vector<int64_t>& in_stride, GatherDesc& plain);
 
 struct LeafPrep {
   int leaf = -1;

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include <mutex>
 
 namespace tnc {
 
@@ -103,6 +104,67 @@ struct PermuteDesc {
   int64_t pk;
   int64_t pplane;
 };
+
+// A tiled permutation as mixed-radix digits, from which its tables follow:
+// the planner fills them on the host, once per plan; a stand-alone permute
+// has launch_permute_tables fill them on the device, so that the call
+// neither uploads nor waits.
+struct PermuteShape {
+  static constexpr int kTileDims = 12;  // T <= 4096, extents >= 2
+  int32_t tiled = 0;                    // 0: no useful tile, plain gather only
+  int32_t pairs = 0;                    // PermuteDesc::pairs
+  int32_t T = 0, slots = 0;
+  int32_t n_tile = 0, n_outer = 0, split = 0;  // outer dims [split, n_outer) make the lo table
+  int64_t n_tiles = 0, L = 1, n_hi = 1;
+  // tile dims, fastest first, in read order (input strides) and in write
+  // order (output strides and the element's place in the read order)
+  uint32_t rext[kTileDims], wext[kTileDims];
+  int32_t rin[kTileDims], wout[kTileDims], wpos[kTileDims];
+  uint32_t oext[64];            // outer dims in output order
+  int64_t oin[64], oout[64];
+  static __host__ __device__ int32_t pad(int64_t x) { return static_cast<int32_t>(x + (x >> 5)); }
+  __host__ __device__ void read_entry(uint32_t x, int32_t& in, int32_t& slot) const {
+    slot = pad(x);
+    int32_t o = 0;
+    for (int d = 0; d < n_tile; ++d) {
+      const uint32_t q = x / rext[d];
+      o += static_cast<int32_t>(x - q * rext[d]) * rin[d];
+      x = q;
+    }
+    in = o;
+  }
+  __host__ __device__ void write_entry(uint32_t x, int32_t& out, int32_t& slot) const {
+    int32_t o = 0, p = 0;
+    for (int d = 0; d < n_tile; ++d) {
+      const uint32_t q = x / wext[d];
+      const int32_t dig = static_cast<int32_t>(x - q * wext[d]);
+      o += dig * wout[d];
+      p += dig * wpos[d];
+      x = q;
+    }
+    out = o;
+    slot = pad(p);
+  }
+  // entry x of the lo (hi = false) or hi table
+  __host__ __device__ void outer_entry(bool hi, uint32_t x, int64_t& in, int64_t& out) const {
+    in = out = 0;
+    for (int d = (hi ? split : n_outer) - 1; d >= (hi ? 0 : split); --d) {
+      const uint32_t q = x / oext[d];
+      const int64_t dig = x - q * oext[d];
+      in += dig * oin[d];
+      out += dig * oout[d];
+      x = q;
+    }
+  }
+  // Byte offsets of the tables (read and write offsets and slots, lo, hi:
+  // each 256-byte aligned) and their total size.
+  __host__ __device__ size_t offset(int table) const {
+    const size_t al = 255, t = (size_t(T) * 4 + al) & ~al, l = (size_t(L) * 16 + al) & ~al;
+    return table <= 4 ? t * table : table == 5 ? 4 * t + l : 4 * t + l + size_t(n_hi) * 16;
+  }
+  size_t bytes() const { return tiled ? offset(6) : 0; }
+};
+hipError_t launch_permute_tables(const PermuteShape& p, char* tables, hipStream_t s);
 
 // Plain gather: out[w] = in[base + sum_d digit_d(w) * in_stride[d]] over
 // row-major output dims (any shape; used for small tensors).
@@ -246,10 +308,18 @@ hipError_t launch_group_gather_runs(const GroupRun* runs, int n_runs, int64_t to
 hipError_t launch_permute(const PermuteDesc& d, hipStream_t s);
 // Fixed device-resident table area for permutes of callers that cannot
 // allocate (tnc_permute_noalloc): kStaticPermuteTableBytes per GPU, shared
-// by every such call on that GPU.  static_table_area looks its address up
-// once per device (the device must be current) and returns it.
+// by every such call on that GPU.  A call holds `mu` while it makes its
+// stream wait for `last_use`, enqueues its launches and records `last_use`
+// behind them, so calls from several streams take the area in turn.
+// static_table_area looks the address up and makes the event once per
+// device (the device must be current).
 constexpr size_t kStaticPermuteTableBytes = size_t{1} << 20;
-hipError_t static_table_area(int device, void** out);
+struct StaticTables {
+  std::mutex mu;
+  char* ptr = nullptr;
+  hipEvent_t last_use = nullptr;
+};
+hipError_t static_table_area(int device, StaticTables** out);
 hipError_t launch_gather(const GatherDesc& d, hipStream_t s);
 // acc[i] += sum_s root[s * R + i] (complex64 in, complex128 out), pairwise
 // over s in a fixed tree; hs = number of s.  overwrite: acc[i] = the sum

@@ -105,8 +105,8 @@ void validate_path(const Net& net, const std::vector<std::array<int, 2>>& pairs)
 }
 
 // ------------------------------------------------------------------ permutation tables
-PermuteHost build_permute(const std::vector<int64_t>& ext0, const std::vector<int64_t>& st0) {
-  PermuteHost P;
+PermuteShape permute_shape(const std::vector<int64_t>& ext0, const std::vector<int64_t>& st0, GatherDesc& g) {
+  PermuteShape P;
   // drop unit dims, fuse output-adjacent dims that are also input-adjacent
   std::vector<int64_t> ext, st;
   for (size_t j = 0; j < ext0.size(); ++j) {
@@ -122,7 +122,6 @@ PermuteHost build_permute(const std::vector<int64_t>& ext0, const std::vector<in
   int64_t total = 1;
   for (int64_t e : ext) total *= e;
   if (static_cast<int>(ext.size()) > kMaxRank) fail(TNC_E_UNSUPPORTED, "permute rank above limit");
-  GatherDesc& g = P.plain;
   std::memset(&g, 0, sizeof(g));
   g.total = total;
   g.rank = static_cast<int32_t>(ext.size());
@@ -130,11 +129,6 @@ PermuteHost build_permute(const std::vector<int64_t>& ext0, const std::vector<in
     g.ext[j] = ext[j];
     g.in_stride[j] = st[j];
   }
-  auto plain_only = [&]() {
-    PermuteHost Q;
-    Q.plain = g;
-    return Q;
-  };
   if (total < 4096 || ext.size() <= 1) return P;
 
   // split a large dim at a divisor <= 64 so that tiles stay small
@@ -223,75 +217,76 @@ PermuteHost build_permute(const std::vector<int64_t>& ext0, const std::vector<in
       s *= ext[d];
     }
   }
-  auto pad = [](int64_t x) { return static_cast<int32_t>(x + (x >> 5)); };
   P.T = static_cast<int32_t>(T);
-  P.slots = pad(T - 1) + 1;
-  P.tile_in.resize(T);
-  P.tile_slot_r.resize(T);
-  P.tile_out.resize(T);
-  P.tile_slot_w.resize(T);
-  for (int64_t x = 0; x < T; ++x) {
-    int64_t rest = x, in_off = 0;
-    for (int d : rfast) {
-      const int64_t dig = rest % ext[d];
-      rest /= ext[d];
-      in_off += dig * st[d];
-    }
-    if (in_off > INT32_MAX) return plain_only();
-    P.tile_in[x] = static_cast<int32_t>(in_off);
-    P.tile_slot_r[x] = pad(x);
-    rest = x;
-    int64_t out_off = 0, rpos = 0;
-    for (int d : wfast) {
-      const int64_t dig = rest % ext[d];
-      rest /= ext[d];
-      out_off += dig * ost[d];
-      rpos += dig * rstride[d];
-    }
-    if (out_off > INT32_MAX) return plain_only();
-    P.tile_out[x] = static_cast<int32_t>(out_off);
-    P.tile_slot_w[x] = pad(rpos);
+  P.slots = PermuteShape::pad(T - 1) + 1;
+  // offsets inside a tile are kept in 32 bits
+  int64_t max_in = 0, max_out = 0;
+  for (int d : rfast) {
+    max_in += (ext[d] - 1) * st[d];
+    max_out += (ext[d] - 1) * ost[d];
+  }
+  if (max_in > INT32_MAX || max_out > INT32_MAX) return PermuteShape{};
+  P.n_tile = static_cast<int32_t>(rfast.size());
+  for (int q = 0; q < P.n_tile; ++q) {
+    const int d = rfast[q], e = wfast[q];
+    P.rext[q] = static_cast<uint32_t>(ext[d]);
+    P.rin[q] = static_cast<int32_t>(st[d]);
+    P.wext[q] = static_cast<uint32_t>(ext[e]);
+    P.wout[q] = static_cast<int32_t>(ost[e]);
+    P.wpos[q] = static_cast<int32_t>(rstride[e]);
   }
   // outer dims (not in the tile), output order; split into lo (inner) and hi
   std::vector<int> outer;
   for (int d = 0; d < r; ++d)
     if (!inU[d]) outer.push_back(d);
-  const int64_t n_tiles = total / T;
-  int64_t L = 1;
-  int split = static_cast<int>(outer.size());
-  while (split > 0 && (L * ext[outer[split - 1]] <= 4096 || L * L < n_tiles)) {
-    L *= ext[outer[split - 1]];
-    --split;
+  P.n_tiles = total / T;
+  P.n_outer = static_cast<int32_t>(outer.size());
+  P.split = P.n_outer;
+  while (P.split > 0 && (P.L * ext[outer[P.split - 1]] <= 4096 || P.L * P.L < P.n_tiles)) {
+    P.L *= ext[outer[P.split - 1]];
+    --P.split;
   }
-  auto make_tab = [&](int from, int to, std::vector<int64_t>& tab) {
-    int64_t cnt = 1;
-    for (int q = from; q < to; ++q) cnt *= ext[outer[q]];
-    tab.assign(2 * cnt, 0);
-    for (int64_t x = 0; x < cnt; ++x) {
-      int64_t rest = x, io = 0, oo = 0;
-      for (int q = to - 1; q >= from; --q) {
-        const int d = outer[q];
-        const int64_t dig = rest % ext[d];
-        rest /= ext[d];
-        io += dig * st[d];
-        oo += dig * ost[d];
-      }
-      tab[2 * x] = io;
-      tab[2 * x + 1] = oo;
-    }
-  };
-  make_tab(split, static_cast<int>(outer.size()), P.lo_tab);
-  make_tab(0, split, P.hi_tab);
-  P.pairs = T % 2 == 0;
-  for (int64_t x = 0; P.pairs && x < T; x += 2)
-    P.pairs = P.tile_in[x] % 2 == 0 && P.tile_in[x + 1] == P.tile_in[x] + 1 && P.tile_out[x] % 2 == 0 &&
-              P.tile_out[x + 1] == P.tile_out[x] + 1;
-  for (size_t q = 0; P.pairs && q < P.lo_tab.size(); ++q) P.pairs = P.lo_tab[q] % 2 == 0;
-  for (size_t q = 0; P.pairs && q < P.hi_tab.size(); ++q) P.pairs = P.hi_tab[q] % 2 == 0;
-  P.L = static_cast<int32_t>(L);
-  P.n_tiles = n_tiles;
-  P.tiled = true;
+  P.n_hi = P.n_tiles / P.L;
+  if (P.L > INT32_MAX || P.n_hi > INT32_MAX) return PermuteShape{};
+  // pairs: the same innermost mode, of even extent, in both orders, and every
+  // other stride even
+  bool pairs = rfast[0] == wfast[0] && st[rfast[0]] == 1 && ost[rfast[0]] == 1 && ext[rfast[0]] % 2 == 0;
+  for (int d = 0; d < r; ++d)
+    if (d != rfast[0]) pairs = pairs && st[d] % 2 == 0 && ost[d] % 2 == 0;
+  P.pairs = pairs ? 1 : 0;
+  for (int q = 0; q < P.n_outer; ++q) {
+    P.oext[q] = static_cast<uint32_t>(ext[outer[q]]);
+    P.oin[q] = st[outer[q]];
+    P.oout[q] = ost[outer[q]];
+  }
+  P.tiled = 1;
   return P;
+}
+
+PermuteHost build_permute(const std::vector<int64_t>& ext, const std::vector<int64_t>& st) {
+  PermuteHost H;
+  const PermuteShape P = permute_shape(ext, st, H.plain);
+  if (!P.tiled) return H;
+  H.tiled = true;
+  H.pairs = P.pairs != 0;
+  H.T = P.T;
+  H.slots = P.slots;
+  H.L = static_cast<int32_t>(P.L);
+  H.n_tiles = P.n_tiles;
+  H.tile_in.resize(P.T);
+  H.tile_slot_r.resize(P.T);
+  H.tile_out.resize(P.T);
+  H.tile_slot_w.resize(P.T);
+  for (int32_t x = 0; x < P.T; ++x) {
+    P.read_entry(x, H.tile_in[x], H.tile_slot_r[x]);
+    P.write_entry(x, H.tile_out[x], H.tile_slot_w[x]);
+  }
+  H.lo_tab.resize(2 * P.L);
+  H.hi_tab.resize(2 * P.n_hi);
+  for (int64_t x = 0; x < P.L; ++x) P.outer_entry(false, static_cast<uint32_t>(x), H.lo_tab[2 * x], H.lo_tab[2 * x + 1]);
+  for (int64_t x = 0; x < P.n_hi; ++x)
+    P.outer_entry(true, static_cast<uint32_t>(x), H.hi_tab[2 * x], H.hi_tab[2 * x + 1]);
+  return H;
 }
 
 // ------------------------------------------------------------------ chunk plan
