@@ -200,7 +200,13 @@ struct StepPlan {
 struct LevelPlan {
   std::vector<int> group_leaves, single_leaves;
   std::vector<int> group_steps, single_steps;
-  int64_t off_gemm = -1, off_gemm_prefix = -1, gemm_total = 0;
+  int64_t off_gemm = -1, off_gemm_blocks = -1, gemm_blocks = 0;
+  int32_t gemm_per = 256;
+  // a chain starts here: this many levels run as one launch (the others of
+  // them have chained set); 0: none
+  int chain = 0;
+  bool chained = false;
+  int64_t off_chain = -1, off_chain_bounds = -1;
   int64_t off_gather = -1, off_gather_prefix = -1, gather_total = 0;
 };
 

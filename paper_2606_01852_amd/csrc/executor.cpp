@@ -62,10 +62,23 @@ void materialize(const Net& net, ChunkPlan& cp, hipStream_t stream) {
   }
   // grouped-launch tables reserve their space now and are filled once the
   // blob's device address (for the offset tables they point to) is known
-  for (LevelPlan& L : cp.levels) {
-    if (!L.group_steps.empty()) {
+  auto outs_of = [&](int s) { return cp.steps[s].desc.h * cp.steps[s].desc.m * cp.steps[s].desc.n; };
+  for (size_t li = 0; li < cp.levels.size(); ++li) {
+    LevelPlan& L = cp.levels[li];
+    if (L.chain) {
+      int64_t items = 0;
+      for (int q = 0; q < L.chain; ++q)
+        for (int s : cp.levels[li + q].group_steps) items += outs_of(s);
+      L.off_chain = put(blob, std::vector<ChainItem>(items));
+      L.off_chain_bounds = put(blob, std::vector<int32_t>(L.chain + 1));
+    } else if (!L.chained && !L.group_steps.empty()) {
+      int64_t total = 0;
+      for (int s : L.group_steps) total += outs_of(s);
+      L.gemm_per = group_per(total);
+      L.gemm_blocks = 0;
+      for (int s : L.group_steps) L.gemm_blocks += (outs_of(s) + L.gemm_per - 1) / L.gemm_per;
       L.off_gemm = put(blob, std::vector<GroupGemm>(L.group_steps.size()));
-      L.off_gemm_prefix = put(blob, std::vector<int64_t>(L.group_steps.size()));
+      L.off_gemm_blocks = put(blob, std::vector<GroupBlock>(L.gemm_blocks));
     }
     if (!L.group_leaves.empty()) {
       L.off_gather = put(blob, std::vector<GroupGather>(L.group_leaves.size()));
@@ -88,38 +101,75 @@ void materialize(const Net& net, ChunkPlan& cp, hipStream_t stream) {
     }
   }
   const int n = net.n_tensors;
-  for (LevelPlan& L : cp.levels) {
-    if (!L.group_steps.empty()) {
-      GroupGemm* tab = reinterpret_cast<GroupGemm*>(blob.data() + L.off_gemm);
-      int64_t* pre = reinterpret_cast<int64_t*>(blob.data() + L.off_gemm_prefix);
-      int64_t acc = 0;
-      for (size_t q = 0; q < L.group_steps.size(); ++q) {
-        const StepPlan& sp = cp.steps[L.group_steps[q]];
-        GroupGemm g;
-        std::memset(&g, 0, sizeof(g));
-        g.d = sp.desc;
-        auto operand = [&](int id, int32_t& rel) -> void* {
-          if (id < n && (cp.leaf[id].direct || cp.leaf[id].inplace)) {
-            rel = 0;
-            return net.leaf[id].ptr;
+  // an operand's device address, or its offset in the arena (rel = 1)
+  auto operand = [&](int id, int32_t& rel) -> void* {
+    rel = 0;
+    if (id < n && (cp.leaf[id].direct || cp.leaf[id].inplace)) return net.leaf[id].ptr;
+    if (id < n && cp.leaf[id].cached) return cached_leaf(cp, id);
+    rel = 1;
+    return reinterpret_cast<void*>(static_cast<intptr_t>(cp.buf_off[cp.tensor_buf[id]]));
+  };
+  auto entry = [&](int s) {
+    const StepPlan& sp = cp.steps[s];
+    GroupGemm g;
+    std::memset(&g, 0, sizeof(g));
+    g.d = sp.desc;
+    g.d.A = static_cast<const float2*>(operand(sp.la, g.rel_a));
+    g.d.B = static_cast<const float2*>(operand(sp.lb, g.rel_b));
+    g.d.C = static_cast<float2*>(operand(sp.C, g.rel_c));
+    g.slot_a = sp.la < n && cp.leaf[sp.la].inplace ? cp.leaf[sp.la].base_slot : -1;
+    g.slot_b = sp.lb < n && cp.leaf[sp.lb].inplace ? cp.leaf[sp.lb].base_slot : -1;
+    g.total = outs_of(s);
+    auto log2 = [](int64_t x) {
+      int sh = 0;
+      while ((int64_t{1} << sh) < x) ++sh;
+      return (int64_t{1} << sh) == x ? sh : -1;
+    };
+    g.shift_n = log2(g.d.n);
+    g.shift_mn = log2(g.d.m * g.d.n);
+    bool vec = row_stride(g.d) % 2 == 0 && reinterpret_cast<uintptr_t>(g.d.A) % 16 == 0 &&
+               reinterpret_cast<uintptr_t>(g.d.B) % 16 == 0;
+    for (int q = 0; q < g.d.nbd; ++q) vec = vec && g.d.bsA[q] % 2 == 0 && g.d.bsB[q] % 2 == 0;
+    g.vec = vec ? 1 : 0;
+    return g;
+  };
+  for (size_t li = 0; li < cp.levels.size(); ++li) {
+    LevelPlan& L = cp.levels[li];
+    if (L.chain) {
+      ChainItem* it = reinterpret_cast<ChainItem*>(blob.data() + L.off_chain);
+      int32_t* bounds = reinterpret_cast<int32_t*>(blob.data() + L.off_chain_bounds);
+      int32_t acc = 0;
+      for (int q = 0; q < L.chain; ++q) {
+        bounds[q] = acc;
+        for (int s : cp.levels[li + q].group_steps) {
+          const GroupGemm g = entry(s);
+          const GemmDesc& d = g.d;
+          const std::vector<int64_t>&om = cp.steps[s].offM, &on = cp.steps[s].offN;
+          const int64_t ld = 8 * row_stride(d), a0 = reinterpret_cast<intptr_t>(d.A),
+                        b0 = reinterpret_cast<intptr_t>(d.B), c0 = reinterpret_cast<intptr_t>(d.C);
+          const int32_t k = static_cast<int32_t>(d.k);
+          const int32_t flags = (g.rel_a ? 1 : 0) | (g.rel_b ? 2 : 0) | (g.vec ? 4 : 0);
+          for (int64_t b = 0; b < d.h; ++b) {
+            int64_t oa = a0, ob = b0, oc = c0 + 8 * b * d.m * d.n, rest = b;
+            for (int t = d.nbd - 1; t >= 0; --t) {
+              oa += 8 * (rest % d.bext[t]) * d.bsA[t];
+              ob += 8 * (rest % d.bext[t]) * d.bsB[t];
+              rest /= d.bext[t];
+            }
+            for (int64_t i = 0; i < d.m; ++i)
+              for (int64_t j = 0; j < d.n; ++j)
+                it[acc++] = {oa + i * ld, ob + j * ld, oc + 8 * (om.empty() ? i * d.n + j : om[i] + on[j]), k, flags};
           }
-          if (id < n && cp.leaf[id].cached) {
-            rel = 0;
-            return cached_leaf(cp, id);
-          }
-          rel = 1;
-          return reinterpret_cast<void*>(static_cast<intptr_t>(cp.buf_off[cp.tensor_buf[id]]));
-        };
-        g.d.A = static_cast<const float2*>(operand(sp.la, g.rel_a));
-        g.d.B = static_cast<const float2*>(operand(sp.lb, g.rel_b));
-        g.d.C = static_cast<float2*>(operand(sp.C, g.rel_c));
-        g.slot_a = sp.la < n && cp.leaf[sp.la].inplace ? cp.leaf[sp.la].base_slot : -1;
-        g.slot_b = sp.lb < n && cp.leaf[sp.lb].inplace ? cp.leaf[sp.lb].base_slot : -1;
-        tab[q] = g;
-        pre[q] = acc;
-        acc += sp.desc.h * sp.desc.m * sp.desc.n;
+        }
       }
-      L.gemm_total = acc;
+      bounds[L.chain] = acc;
+    } else if (!L.chained && !L.group_steps.empty()) {
+      GroupGemm* tab = reinterpret_cast<GroupGemm*>(blob.data() + L.off_gemm);
+      GroupBlock* blk = reinterpret_cast<GroupBlock*>(blob.data() + L.off_gemm_blocks);
+      for (size_t q = 0; q < L.group_steps.size(); ++q) {
+        tab[q] = entry(L.group_steps[q]);
+        for (int64_t x = 0; x < tab[q].total; x += L.gemm_per) *blk++ = {static_cast<int32_t>(q), 0, x};
+      }
     }
     if (!L.group_leaves.empty()) {
       GroupGather* tab = reinterpret_cast<GroupGather*>(blob.data() + L.off_gather);
@@ -378,11 +428,15 @@ struct ChunkOps {
     });
   }
   void level_small_gemms(const LevelPlan& lv) {
-    if (lv.group_steps.empty()) return;
+    if (lv.group_steps.empty() || lv.chained) return;
     L.run(t_group, stream, [&] {
+      if (lv.chain)
+        return launch_level_chain(reinterpret_cast<const ChainItem*>(blob + lv.off_chain),
+                                  reinterpret_cast<const int32_t*>(blob + lv.off_chain_bounds), lv.chain, a.arena, prec,
+                                  stream);
       return launch_group_gemm(reinterpret_cast<const GroupGemm*>(blob + lv.off_gemm),
-                               reinterpret_cast<const int64_t*>(blob + lv.off_gemm_prefix),
-                               static_cast<int>(lv.group_steps.size()), lv.gemm_total, a.arena, bases, prec, stream);
+                               reinterpret_cast<const GroupBlock*>(blob + lv.off_gemm_blocks), lv.gemm_blocks,
+                               lv.gemm_per, a.arena, bases, prec, stream);
     });
   }
   void reduce(bool overwrite) {
@@ -660,7 +714,7 @@ LockstepInfo lockstep_info(Plan& plan, int64_t first, int64_t count) {
     if (cp.steps.empty() && !cp.leaf[0].direct) ++nl;
     if (cp.grouped) {
       for (const LevelPlan& lv : cp.levels) {
-        nl += (lv.group_leaves.empty() ? 0 : 1) + (lv.group_steps.empty() ? 0 : 1);
+        nl += (lv.group_leaves.empty() ? 0 : 1) + (lv.group_steps.empty() || lv.chained ? 0 : 1);
         nl += static_cast<int64_t>(lv.single_leaves.size());
         for (int s : lv.single_steps) nl += step_launches(cp.steps[s]);
       }
@@ -677,7 +731,7 @@ LockstepInfo lockstep_info(Plan& plan, int64_t first, int64_t count) {
       }
     if (!cp.grouped) continue;
     for (const LevelPlan& lv : cp.levels) {  // per run: one GroupRun per grouped launch
-      if (!lv.group_steps.empty()) {
+      if (!lv.group_steps.empty() && !lv.chained) {
         t.bytes_per_run += sizeof(GroupRun);
         t.parts += 1;
       }
@@ -733,7 +787,7 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
   struct LevelTabs {
     size_t gemm = 0, gath = 0;   // offsets of the GroupRun tables
     int n_gemm = 0, n_gath = 0;  // runs in them (0: no such launch)
-    int64_t gemm_total = 0, gath_total = 0;
+    int64_t gemm_blocks = 0, gath_total = 0;
   };
   std::map<std::pair<int, int>, std::pair<size_t, int64_t>> grouped;  // (j, step) -> (offset, tiles)
   std::map<std::pair<int, int>, LevelTabs> levtabs;                   // (j, level)
@@ -778,19 +832,21 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
           const LevelPlan& lv = cp.levels[li];
           const char* blob = static_cast<const char*>(cp.blob.ptr);
           std::memset(&gr[r], 0, sizeof(GroupRun));
-          gr[r].table = blob + (gemm_tab ? lv.off_gemm : lv.off_gather);
-          gr[r].prefix = reinterpret_cast<const int64_t*>(blob + (gemm_tab ? lv.off_gemm_prefix : lv.off_gather_prefix));
-          gr[r].n = static_cast<int32_t>(gemm_tab ? lv.group_steps.size() : lv.group_leaves.size());
+          gr[r].table = blob + (!gemm_tab ? lv.off_gather : lv.chain ? lv.off_chain : lv.off_gemm);
+          gr[r].index = blob + (!gemm_tab ? lv.off_gather_prefix : lv.chain ? lv.off_chain_bounds : lv.off_gemm_blocks);
+          gr[r].n = !gemm_tab ? static_cast<int32_t>(lv.group_leaves.size())
+                              : lv.chain ? lv.chain : static_cast<int32_t>(lv.group_steps.size());
+          gr[r].per = lv.gemm_per;
           gr[r].arena = runs[r].a.arena;
           gr[r].bases = rb[r].cur_dev;
           gr[r].first = total;
-          total += gemm_tab ? lv.gemm_total : lv.gather_total;
+          total += gemm_tab ? lv.gemm_blocks : lv.gather_total;
         }
         return off;
       };
-      if (!lv0.group_steps.empty()) {
+      if (!lv0.group_steps.empty() && !lv0.chained) {
         t.n_gemm = K;
-        t.gemm = runs_table(true, t.gemm_total);
+        t.gemm = runs_table(true, t.gemm_blocks);
       }
       if (!lv0.group_leaves.empty()) {
         t.n_gath = K;
@@ -835,8 +891,11 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
                     "grouped gathers");
         for (auto& op : ops)
           for (int tl : op->cp.levels[li].single_leaves) op->prep(tl);
-        if (t.n_gemm)
-          check_hip(launch_group_gemm_runs(reinterpret_cast<const GroupRun*>(dev + t.gemm), t.n_gemm, t.gemm_total,
+        if (t.n_gemm && cp0.levels[li].chain)
+          check_hip(launch_level_chain_runs(reinterpret_cast<const GroupRun*>(dev + t.gemm), t.n_gemm, prec, stream),
+                    "level chains");
+        else if (t.n_gemm)
+          check_hip(launch_group_gemm_runs(reinterpret_cast<const GroupRun*>(dev + t.gemm), t.n_gemm, t.gemm_blocks,
                                            prec, stream),
                     "grouped small GEMMs");
         for (int s : cp0.levels[li].single_steps) gemm(s);

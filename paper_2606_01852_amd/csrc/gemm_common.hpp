@@ -89,6 +89,41 @@ __device__ __forceinline__ void cdot_serial(const float2* A, const float2* B, in
   for (; l < k; ++l) cmac<SPLIT>(A[l], B[l], cr, ci, crx, cix);
 }
 
+// The same sum where rows start on 16 bytes: two elements per load, eight of
+// each operand ahead of their products.
+template <bool SPLIT>
+__device__ __forceinline__ void cdot_pairs(const float2* A, const float2* B, int64_t k, float& cr, float& ci,
+                                           float& crx, float& cix) {
+  const float4* a = reinterpret_cast<const float4*>(A);
+  const float4* b = reinterpret_cast<const float4*>(B);
+  auto mac2 = [&](const float4& x, const float4& y) {
+    cmac<SPLIT>(make_float2(x.x, x.y), make_float2(y.x, y.y), cr, ci, crx, cix);
+    cmac<SPLIT>(make_float2(x.z, x.w), make_float2(y.z, y.w), cr, ci, crx, cix);
+  };
+  int64_t l = 0;
+  for (; l + 8 <= k; l += 8) {
+    float4 x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u] = a[l / 2 + u];
+      y[u] = b[l / 2 + u];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) mac2(x[u], y[u]);
+  }
+  if (l + 4 <= k) {
+    const float4 x0 = a[l / 2], x1 = a[l / 2 + 1], y0 = b[l / 2], y1 = b[l / 2 + 1];
+    mac2(x0, y0);
+    mac2(x1, y1);
+    l += 4;
+  }
+  if (l + 2 <= k) {
+    mac2(a[l / 2], b[l / 2]);
+    l += 2;
+  }
+  if (l < k) cmac<SPLIT>(A[l], B[l], cr, ci, crx, cix);
+}
+
 // The same sum with operands read through tables (an operand without
 // tables is K-contiguous at a0 / b0): element l of the A row at
 // a0[kA[l]], of the B row at b0[kB[l]]; the accumulation order is that of

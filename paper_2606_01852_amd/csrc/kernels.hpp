@@ -270,9 +270,34 @@ hipError_t launch_splitk_reduce(const float2* P, float2* C, int64_t h, int64_t m
 // tables stay valid for any arena.
 struct GroupGemm {
   GemmDesc d;
-  int32_t rel_a, rel_b, rel_c, pad;
+  int32_t rel_a, rel_b, rel_c;
+  int32_t vec;              // rows start on 16 bytes (where the arena does): two elements per load
   int32_t slot_a, slot_b;   // per-chunk base offset of an in-place operand (-1: none)
+  int32_t shift_n, shift_mn;  // log2 of n and m n (-1: no power of two)
+  int64_t total;            // output elements
 };
+// One workgroup of a grouped launch: `per` output elements from `first` on
+// of entry `entry` (per: the launch's, one for all of its workgroups).
+struct GroupBlock {
+  int32_t entry, pad;
+  int64_t first;
+};
+// Output elements per workgroup of a level of `total` of them: one per
+// thread until that takes more than 2^16 workgroups.
+inline int32_t group_per(int64_t total) {
+  int64_t per = 256;
+  while (total / per > 65536) per *= 2;
+  return static_cast<int32_t>(per);
+}
+// One output element of a level in a chain (launch_level_chain): operands by
+// address, or by arena offset where rel is set; C by arena offset.
+struct ChainItem {
+  int64_t a, b, c;
+  int32_t k;
+  int32_t flags;            // 1: a is an arena offset, 2: b is one, 4: vec
+};
+constexpr int kChainThreads = 1024;
+constexpr int64_t kChainOuts = 4096, kChainMacs = 16384;  // of a level, at most
 constexpr int kGroupRank = 32;
 struct GroupGather {
   const float2* in;     // resident leaf
@@ -282,27 +307,33 @@ struct GroupGather {
   int64_t ext[kGroupRank];
   int64_t in_stride[kGroupRank];
 };
-// prefix[i] = first work item of entry i (work items: output elements).
 // An in-place operand's base offset comes from bases[slot_a].
-hipError_t launch_group_gemm(const GroupGemm* table, const int64_t* prefix, int n, int64_t total, char* arena,
-                             const int64_t* bases, Prec prec, hipStream_t s);
+hipError_t launch_group_gemm(const GroupGemm* table, const GroupBlock* blocks, int64_t n_blocks, int32_t per,
+                             char* arena, const int64_t* bases, Prec prec, hipStream_t s);
+// prefix[i] = first work item of entry i (work items: output elements).
 hipError_t launch_group_gather(const GroupGather* table, const int64_t* prefix, int n, int64_t total, char* arena,
                                const int64_t* bases, hipStream_t s);
 // One run's share of a grouped launch over several runs of one structure
 // (a fused serving job): its own device table and prefix sums (those of a
 // launch of its own), its arena, its current leaf base offsets, and its
-// first work item in the launch.  A launch over runs does per work item
-// exactly what the run's own launch does.
+// first work item (workgroup, for GEMMs) in the launch.  A launch over runs
+// does per work item exactly what the run's own launch does.
 struct GroupRun {
-  const void* table;        // GroupGemm[] or GroupGather[]
-  const int64_t* prefix;
+  const void* table;        // GroupGemm[], GroupGather[] or ChainItem[]
+  const void* index;        // GroupBlock[], the gathers' prefix sums, or the chain's bounds
   char* arena;
   const int64_t* bases;
   int64_t first;
-  int32_t n;
-  int32_t pad;
+  int32_t n;                // entries (levels of a chain)
+  int32_t per;              // GEMMs: elements per workgroup
 };
-hipError_t launch_group_gemm_runs(const GroupRun* runs, int n_runs, int64_t total, Prec prec, hipStream_t s);
+hipError_t launch_group_gemm_runs(const GroupRun* runs, int n_runs, int64_t n_blocks, Prec prec, hipStream_t s);
+// Consecutive levels with little work each (kChainOuts, kChainMacs) in one
+// launch of one workgroup, a barrier between two levels: level l's items are
+// [bounds[l], bounds[l + 1]).  The runs form takes one workgroup per run.
+hipError_t launch_level_chain(const ChainItem* items, const int32_t* bounds, int levels, char* arena, Prec prec,
+                              hipStream_t s);
+hipError_t launch_level_chain_runs(const GroupRun* runs, int n_runs, Prec prec, hipStream_t s);
 hipError_t launch_group_gather_runs(const GroupRun* runs, int n_runs, int64_t total, hipStream_t s);
 
 hipError_t launch_permute(const PermuteDesc& d, hipStream_t s);

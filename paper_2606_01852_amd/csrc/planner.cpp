@@ -715,6 +715,34 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
     }
   }
 
+  // chains: runs of two or more levels that hold small GEMMs only, with so
+  // little work that one workgroup does a level in less time than a launch
+  // takes.  Operands read through tables keep a level out of a chain.
+  auto chainable = [&](const LevelPlan& lv) {
+    if (lv.group_steps.empty() || !lv.single_steps.empty() || !lv.single_leaves.empty() || !lv.group_leaves.empty())
+      return false;
+    int64_t outs = 0, macs = 0;
+    for (int s : lv.group_steps) {
+      const StepPlan& sp = cp->steps[s];
+      for (int x : {sp.A, sp.B})
+        if (x < n && cp->leaf[x].inplace) return false;
+      const int64_t o = sp.h * sp.m * sp.n;
+      if (o > kChainOuts || sp.k > kChainMacs) return false;
+      outs += o;
+      macs += o * sp.k;
+    }
+    return outs <= kChainOuts && macs <= kChainMacs;
+  };
+  for (size_t l = 0; l < cp->levels.size();) {
+    size_t e = l;
+    while (e < cp->levels.size() && chainable(cp->levels[e])) ++e;
+    if (e - l >= 2) {
+      cp->levels[l].chain = static_cast<int>(e - l);
+      for (size_t q = l + 1; q < e; ++q) cp->levels[q].chained = true;
+    }
+    l = std::max(e, l + 1);
+  }
+
   // arena buffers: live ranges in execution time, first fit by decreasing size
   struct Iv {
     int64_t bytes;
