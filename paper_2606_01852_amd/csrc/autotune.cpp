@@ -37,7 +37,7 @@ double padding_waste(int variant, int64_t m, int64_t n) {
 
 // Ranking of the variants by measured per-tile throughput on large shapes.
 const std::vector<int>& ranking(tnc_prec prec, tnc_cgemm form) {
-  static const std::vector<int> r4m = {3, 2, 0, 1, 4, 5, 6};
+  static const std::vector<int> r4m = {3, 2, 0, 1, 4, 5, 6, kDirect64x32, kDirect32x32, kDirect32x16};
   static const std::vector<int> r3m = {0, 2, 4, 1, 5, 6};  // 0: three (2,2) workgroups per CU
   static const std::vector<int> rbf = {3, 0, 2, 1, 4, 5, 6};  // 3: the wide-wave 256 x 128 tile
   if (form == TNC_GEMM_3M) return r3m;  // complex64 and split precision alike
@@ -46,15 +46,50 @@ const std::vector<int>& ranking(tnc_prec prec, tnc_cgemm form) {
 
 std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n) {
   std::vector<int> out;
-  for (int v : ranking(prec, form))
+  for (int v : ranking(prec, form)) {
+    if (v >= kGemmVariants && tiles_for(v, h, m, n) > 2048) continue;  // the few-tile shapes
     if (tiles_for(v, h, m, n) * 64 < (int64_t{1} << 32) && padding_waste(v, m, n) < 0.5) out.push_back(v);
+  }
   if (out.empty()) out.push_back(0);
   return out;
 }
 
 }  // namespace
 
+// complex64 4M.  With few tiles the shapes that share K out: the largest of
+// them that still has no more than one workgroup per CU (us per launch,
+// 128 x 64 tile before and the chosen shape: 256 x 256 x 256 26.6, 7.0;
+// 512 x 512 x 512 47, 14.6; 8 x 1024 x 64 x 128 17.3, 10.7; from 2048
+// 32 x 16 tiles on the tiles win: 1024 x 1024 x 64 12.5, 13.4).  Else the
+// tile with the largest product of what it reaches on large shapes (relative
+// to 256 x 128), the share of it that is not padding, how evenly its
+// workgroups fill 256 CUs, and how well one CU's waves hide each other's
+// latency (fewer than two per SIMD do not: 2 x 4096 x 256 x 128 runs 20.5 us
+// on 256 workgroups of four waves, 28.0 on 512 of two, 24.8 on 128 of eight).
+static int default_variant_c64_4m(int64_t h, int64_t m, int64_t n) {
+  const int64_t few = tiles_for(kDirect32x16, h, m, n);
+  if (few <= 256) return kDirect32x16;
+  if (few <= 512) return kDirect32x32;
+  if (few <= 1024) return kDirect64x32;
+  static const double rate[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};
+  static const int waves[kGemmVariants] = {4, 4, 8, 8, 2, 2, 1};
+  int best = 4;
+  double top = 0.0;
+  for (int v : {3, 2, 0, 1, 4, 5, 6}) {
+    const int64_t t = tiles_for(v, h, m, n), q = (t + 255) / 256;
+    const int64_t w = q * waves[v];
+    const double hide = w >= 8 ? 1.0 : w >= 4 ? 0.58 : w >= 2 ? 0.35 : 0.2;
+    const double e = rate[v] * (1.0 - padding_waste(v, m, n)) * (static_cast<double>(t) / (256.0 * q)) * hide;
+    if (e > 1.01 * top) {
+      top = e;
+      best = v;
+    }
+  }
+  return best;
+}
+
 int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n) {
+  if (prec == TNC_PREC_C64 && form == TNC_GEMM_4M) return default_variant_c64_4m(h, m, n);
   // the best-ranked shape that still gives every CU a few tiles and wastes
   // little on padding; small problems fall through to the small shapes
   for (int v : ranking(prec, form))
@@ -75,7 +110,8 @@ void load_tune_cache(Ctx& c) {
   TuneKey key;
   int v = 0;
   while (f >> key.prec >> key.form >> key.perm >> key.h >> key.m >> key.n >> key.k >> v)
-    if (v >= 0 && v < kGemmVariants) c.tune_cache[key] = v;
+    if (v >= 0 && v < (key.prec == TNC_PREC_C64 && key.form == TNC_GEMM_4M ? kAllVariants : kGemmVariants))
+      c.tune_cache[key] = v;
 }
 
 static void save_tune_entry(const TuneKey& key, int v) {

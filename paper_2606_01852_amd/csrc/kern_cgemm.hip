@@ -1129,11 +1129,11 @@ void prepare_gemm_kernels() {
 }
 
 void gemm_variant_tile(int variant, int* bm, int* bnc) {
-  static const int wm[kGemmVariants] = {2, 4, 2, 4, 1, 2, 1};
-  static const int wn[kGemmVariants] = {2, 2, 4, 4, 2, 1, 1};
-  if (variant < 0 || variant >= kGemmVariants) variant = 0;
-  *bm = 64 * wm[variant];
-  *bnc = 32 * wn[variant];
+  static const int rows[kAllVariants] = {128, 256, 128, 256, 64, 128, 64, 32, 32, 64};
+  static const int cols[kAllVariants] = {64, 64, 128, 128, 64, 32, 32, 16, 32, 32};
+  if (variant < 0 || variant >= kAllVariants) variant = 0;
+  *bm = rows[variant];
+  *bnc = cols[variant];
 }
 
 int64_t grouped_layout(GroupedEntry* e, int n, int variant) {
@@ -1155,7 +1155,7 @@ bool grouped_variant_ok(Form form, Prec prec, int variant) {
   if (prec == Prec::BF16X3)
     return form == Form::M3 ? grouped_ok<Ops3MBF16>(variant) : grouped_ok<OpsBF16x3>(variant);
   if (form == Form::M3) return grouped_ok<Ops3M>(variant);
-  return variant >= 0 && variant < kGemmVariants;
+  return variant >= 0 && variant < kAllVariants;
 }
 
 hipError_t launch_gemm_grouped(const GroupedEntry* dev, int n, int64_t total, int variant, Form form, Prec prec,

@@ -93,6 +93,46 @@ __device__ __forceinline__ TileCoord uniform(const TileCoord& t) {
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));  // rows of odd length start on 8 bytes
 
+// A 32 x 16 complex block of C again, on the FP32 pipe, straight from global
+// memory and back: right for every float32, and only as fast as such tiles
+// are rare.
+__device__ __forceinline__ void fp32_block(const GemmDesc& d, int64_t b, int64_t row0, int64_t col0, int lane) {
+  int64_t oa, ob;
+  batch_offsets(d, b, oa, ob);
+  const int64_t ld = row_stride(d);
+  const int h = lane >> 5, l32 = lane & 31;
+  const int64_t col = col0 + (l32 >> 1);
+  const float2* x = d.A + oa + (row0 + l32 < d.m ? row0 + l32 : d.m - 1) * ld + h;
+  const float2* y = d.B + ob + (col < d.n ? col : d.n - 1) * ld + h;
+  f16v c = {};
+#pragma unroll 1
+  for (int64_t l = 0; l < d.k; l += 2) {
+    float2 u = make_float2(0.f, 0.f), w = u;
+    if (l + h < d.k) {
+      u = x[l];
+      w = y[l];
+    }
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.x, lane & 1 ? w.y : w.x, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.y, lane & 1 ? w.x : -w.y, c, 0, 0, 0);
+  }
+  if (col >= d.n) return;
+  float* C = reinterpret_cast<float*>(d.C + b * d.m * d.n) + (l32 & 1);
+  const int64_t co = d.offM ? d.offN[col] : col;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int64_t row = row0 + 8 * (v >> 2) + 4 * h + (v & 3);
+    if (row < d.m) C[2 * ((d.offM ? d.offM[row] : row * d.n) + co)] = c[v];
+  }
+}
+
+// packed parts -> one MFMA operand's product with another
+__device__ __forceinline__ f16v mm(const s8v& a, const s8v& b, const f16v& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+// The six products: parts of A and of B, hi hi last; each shares an operand
+// with the one before.
+constexpr int kPartA[6] = {0, 0, 1, 1, 2, 0}, kPartB[6] = {2, 1, 1, 0, 0, 0};
+
 template <int WM, int WN, int PW>
 struct XTile {
   static constexpr int BM = 64 * WM, BNC = 32 * WN * PW, NT = 64 * WM * WN;
@@ -227,10 +267,6 @@ struct XTile {
     each<U * PIECES>([&](auto q) { piece<q / PIECES, q % PIECES>(lds, tid); });
   }
 
-  __device__ __forceinline__ static f16v mm(const s8v& a, const s8v& b, const f16v& c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
-  }
-
   // One stage: the products of `cur`; with NEXT the staged registers are
   // split into `nxt` and loaded again (whole stages).  Each 32 x 32 block's
   // six products of the stage are summed from zero and then added to its
@@ -254,10 +290,8 @@ struct XTile {
     __builtin_amdgcn_sched_barrier(0);
     each<SLOTS>([&](auto slot) {
       constexpr int s = slot, c = s / 6, k6 = s % 6, i = c & 1, j = c >> 1;
-      // hi hi last; each product shares a fragment with the one before
-      constexpr int xa[6] = {0, 0, 1, 1, 2, 0}, xb[6] = {2, 1, 1, 0, 0, 0};
       if constexpr (k6 == 0) t[i] = f16v{};
-      t[i] = mm(fa[i][xa[k6]], fb[j & 1][xb[k6]], t[i]);
+      t[i] = mm(fa[i][kPartA[k6]], fb[j & 1][kPartB[k6]], t[i]);
       if constexpr (c == 0 && k6 < 3) read_a(1, k6);
       if constexpr (i == 1 && j + 1 < NJ) {  // the next block's, once this one's part is done with
         if constexpr (k6 == 0) read_b(j + 1, 0);
@@ -278,39 +312,10 @@ struct XTile {
     });
   }
 
-  // The tile again, on the FP32 pipe, straight from global memory and back:
-  // right for every float32, and only as fast as such tiles are rare.
   __device__ __forceinline__ static void fp32_tile(const GemmDesc& d, const TileCoord& tc, int wm, int wn, int lane) {
-    int64_t oa, ob;
-    batch_offsets(d, tc.b, oa, ob);
-    const int64_t ld = row_stride(d);
-    const int h = lane >> 5, l32 = lane & 31;
-    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
 #pragma unroll 1
-    for (int ij = 0; ij < 2 * NJ; ++ij) {
-      const int64_t row0 = tc.row0 + wm * 64 + (ij & 1) * 32;
-      const int64_t col = tc.col0 + wn * 32 * PW + (ij >> 1) * 16 + (l32 >> 1);
-      const float2* x = d.A + oa + (row0 + l32 < d.m ? row0 + l32 : d.m - 1) * ld + h;
-      const float2* y = d.B + ob + (col < d.n ? col : d.n - 1) * ld + h;
-      f16v c = {};
-#pragma unroll 1
-      for (int64_t l = 0; l < d.k; l += 2) {
-        float2 u = make_float2(0.f, 0.f), w = u;
-        if (l + h < d.k) {
-          u = x[l];
-          w = y[l];
-        }
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.x, lane & 1 ? w.y : w.x, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.y, lane & 1 ? w.x : -w.y, c, 0, 0, 0);
-      }
-      if (col >= d.n) continue;
-      const int64_t co = d.offM ? d.offN[col] : col;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t row = row0 + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (row < d.m) C[2 * ((d.offM ? d.offM[row] : row * d.n) + co)] = c[v];
-      }
-    }
+    for (int ij = 0; ij < 2 * NJ; ++ij)
+      fp32_block(d, tc.b, tc.row0 + wm * 64 + (ij & 1) * 32, tc.col0 + wn * 32 * PW + (ij >> 1) * 16, lane);
   }
 
   // The tile's sums; false if they have to come from the FP32 pipe.
@@ -422,6 +427,187 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void cgemm_c64_
   }
 }
 
+// ---------------------------------------------------------- few tiles
+// Launches with few tiles do not fill the chip and are bound by latency: a
+// stage of the kernel above costs a wave or two on a CU of their own 0.6 us
+// and more.  Here a workgroup is one tile of BI x BJ MFMA blocks (32 x 16
+// complex each) and its W waves share out K: wave w takes the stages w, w + W,
+// ..., reads its fragments straight from global memory (lane (h, r) needs
+// four consecutive complex values of row r), splits them in registers, and
+// meets the others only to add the W sums up, in LDS, in order.  No staging,
+// no barrier in the loop.  It splits every value once per wave that reads it,
+// so it loses where tiles are many.  256 x 256 x 256 26.6 -> 7.0 us, 1024 x
+// 128 x 128 16.5 -> 5.5, 16 x 256 x 256 25.8 -> 6.7 (launches back to back, 4.6
+// of it the launch).
+template <int W, int BI, int BJ>
+struct XDirect {
+  static constexpr int BM = 32 * BI, BNC = 16 * BJ, NT = 64 * W;
+  static constexpr int REGS = 16 * BI * BJ;                  // sums per lane
+  static constexpr size_t kLds = size_t{W} * REGS * 64 * 4;  // one wave's sums after the other's
+  static constexpr int N = REGS / W;                         // of them, added up and stored by one wave
+  static_assert(N >= 1 && N <= 16 && 16 % N == 0, "a wave stores part of one block");
+
+  f4 x[BI][2], y[BJ][2];  // this lane's four complex values of its rows of A and columns of B
+
+  template <bool CHECK>
+  __device__ __forceinline__ static void fetch(f4 (&v)[2], const float2* row, int64_t l, int64_t k) {
+    if constexpr (CHECK) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float2 z = row[l + e < k ? l + e : k - 1];
+        const bool in = l + e < k;
+        v[e >> 1][2 * (e & 1)] = in ? z.x : 0.f;
+        v[e >> 1][2 * (e & 1) + 1] = in ? z.y : 0.f;
+      }
+    } else {
+      v[0] = *reinterpret_cast<const f4u*>(row + l);
+      v[1] = *reinterpret_cast<const f4u*>(row + l + 2);
+    }
+  }
+
+  __device__ __forceinline__ static void split(const f4 (&v)[2], s8v (&part)[3], uint32_t& tiny) {
+    uint32_t w[3][4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float a = v[e >> 1][2 * (e & 1)], b = v[e >> 1][2 * (e & 1) + 1];
+      w[0][e] = take_part(a, b);
+      w[1][e] = take_part(a, b);
+      w[2][e] = last_part(a, b, tiny);
+    }
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int q = 0; q < 3; ++q) part[q] = __builtin_bit_cast(s8v, (u4){w[q][0], w[q][1], w[q][2], w[q][3]});
+  }
+
+  template <bool CHECK>
+  __device__ __forceinline__ void load(const float2* const (&pa)[BI], const float2* const (&pb)[BJ], int64_t l,
+                                       int64_t k) {
+#pragma unroll
+    for (int i = 0; i < BI; ++i) fetch<CHECK>(x[i], pa[i], l, k);
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) fetch<CHECK>(y[j], pb[j], l, k);
+  }
+
+  __device__ __forceinline__ void run(const GemmDesc& d, const TileCoord& tc, char* lds, int wave, int lane) {
+    int64_t oa, ob;
+    batch_offsets(d, tc.b, oa, ob);
+    const int64_t ld = row_stride(d), k = d.k;
+    const int h = lane >> 5, r = lane & 31;
+    const bool odd = r & 1;
+    const float2 *pa[BI], *pb[BJ];
+#pragma unroll
+    for (int i = 0; i < BI; ++i) {
+      const int64_t row = tc.row0 + 32 * i + r;
+      pa[i] = d.A + uniform(oa) + (row < d.m ? row : d.m - 1) * ld;
+    }
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+      const int64_t col = tc.col0 + 16 * j + (r >> 1);
+      pb[j] = d.B + uniform(ob) + (col < d.n ? col : d.n - 1) * ld;
+    }
+    uint32_t tiny = 0xFFFFFFFFu;
+    f16v acc[BI][BJ] = {};
+    auto load_stage = [&](int64_t st) {
+      const int64_t l = st * XK + 4 * h;
+      if ((st + 1) * XK <= k)
+        load<false>(pa, pb, l, k);
+      else
+        load<true>(pa, pb, l, k);
+    };
+    const int64_t nk = (k + XK - 1) / XK;
+    if (wave < nk) load_stage(wave);
+    for (int64_t st = wave; st < nk; st += W) {
+      s8v fa[BI][3], fb[BJ][3];
+#pragma unroll
+      for (int i = 0; i < BI; ++i) split(x[i], fa[i], tiny);
+#pragma unroll
+      for (int j = 0; j < BJ; ++j) {
+        f4 z[2];  // B': (br, -bi) for even real columns, (bi, br) for odd ones
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          z[e].x = odd ? y[j][e].y : y[j][e].x;
+          z[e].y = odd ? y[j][e].x : -y[j][e].y;
+          z[e].z = odd ? y[j][e].w : y[j][e].z;
+          z[e].w = odd ? y[j][e].z : -y[j][e].w;
+        }
+        split(z, fb[j], tiny);
+      }
+      if (st + W < nk) load_stage(st + W);
+      f16v c[BI][BJ] = {};
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int j = 0; j < BJ; ++j)
+#pragma unroll
+          for (int i = 0; i < BI; ++i) c[i][j] = mm(fa[i][kPartA[q]], fb[j][kPartB[q]], c[i][j]);
+#pragma unroll
+      for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int j = 0; j < BJ; ++j) acc[i][j] += c[i][j];
+    }
+    float s = 0.f;  // NaN if any sum is not finite
+    float* mine = reinterpret_cast<float*>(lds) + wave * REGS * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+#pragma unroll
+      for (int j = 0; j < BJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          s = fmaf(acc[i][j][v], 0.f, s);
+          mine[(16 * (i * BJ + j) + v) * 64] = acc[i][j][v];
+        }
+    // (the vote is a barrier: every wave's sums are in LDS behind it)
+    if (__syncthreads_or(tiny < 0x00FFFFFFu || !(s == 0.f))) {
+      if (wave < BI * BJ) fp32_block(d, tc.b, tc.row0 + 32 * (wave / BJ), tc.col0 + 16 * (wave % BJ), lane);
+      return;
+    }
+    const float* part = reinterpret_cast<const float*>(lds) + wave * N * 64 + lane;
+    const int ij = wave * N / 16, v0 = wave * N & 15;
+    const int64_t row0 = tc.row0 + 32 * (ij / BJ), col = tc.col0 + 16 * (ij % BJ) + (r >> 1);
+    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (r & 1);
+    const int64_t co = col < d.n ? (d.offM ? d.offN[col] : col) : -1;
+    float sum[N];
+    int64_t ro[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int v = v0 + u;
+      const int64_t row = row0 + 8 * (v >> 2) + 4 * h + (v & 3);
+      ro[u] = row < d.m ? (d.offM ? d.offM[row] : row * d.n) : -1;
+      sum[u] = part[u * 64];
+#pragma unroll
+      for (int w = 1; w < W; ++w) sum[u] += part[u * 64 + w * REGS * 64];
+    }
+    if (co >= 0)
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        if (ro[u] >= 0) C[2 * (ro[u] + co)] = sum[u];
+  }
+};
+
+template <int W, int BI, int BJ>
+__global__ __launch_bounds__(64 * W) void cgemm_c64_direct(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
+                                                           int64_t total) {
+  using T = XDirect<W, BI, BJ>;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int tid = threadIdx.x;
+  const TileCoord tc = uniform(map_tile_shared<T::BM, T::BNC>(tiles_m, tiles_n, total));
+  T t;
+  t.run(d, tc, lds, __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63);
+}
+
+// one workgroup per tile of the launch's entries
+template <int W, int BI, int BJ>
+__global__ __launch_bounds__(64 * W) void cgemm_c64_direct_grouped(const GroupedEntry* __restrict__ tab, int n) {
+  using T = XDirect<W, BI, BJ>;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int tid = threadIdx.x;
+  int e = 0;
+  while (e + 1 < n && tab[e + 1].tile0 <= blockIdx.x) ++e;
+  const TileCoord tc = uniform(tile_of<T::BM, T::BNC>(blockIdx.x - tab[e].tile0, tab[e].tiles_m, tab[e].tiles_n));
+  T t;
+  t.run(tab[e].d, tc, lds, __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63);
+}
+
 // LDS above 64 KiB must be allowed per kernel, once per device.
 template <class F>
 hipError_t allow_lds(F* kernel, size_t lds, std::atomic<uint64_t>& done) {
@@ -483,6 +669,37 @@ hipError_t launch_grouped_shape(const GroupedEntry* tab, int n, int64_t total, h
   return hipGetLastError();
 }
 
+template <int W, int BI, int BJ>
+hipError_t ready_direct() {
+  static std::atomic<uint64_t> done{0}, done_grouped{0};
+  const size_t lds = XDirect<W, BI, BJ>::kLds;
+  const hipError_t e = allow_lds(cgemm_c64_direct<W, BI, BJ>, lds, done);
+  return e != hipSuccess ? e : allow_lds(cgemm_c64_direct_grouped<W, BI, BJ>, lds, done_grouped);
+}
+template <int W, int BI, int BJ>
+hipError_t launch_direct(const GemmDesc& d, hipStream_t s) {
+  using T = XDirect<W, BI, BJ>;
+  const int64_t tiles_m = (d.m + T::BM - 1) / T::BM, tiles_n = (d.n + T::BNC - 1) / T::BNC;
+  const int64_t total = tiles_m * tiles_n * d.h;
+  if (total * T::NT > 0xFFFFFFFFLL) return hipErrorInvalidValue;
+  const hipError_t e = ready_direct<W, BI, BJ>();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((cgemm_c64_direct<W, BI, BJ>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s, d,
+                     tiles_m, tiles_n, total);
+  return hipGetLastError();
+}
+
+template <int W, int BI, int BJ>
+hipError_t launch_direct_grouped(const GroupedEntry* tab, int n, int64_t total, hipStream_t s) {
+  using T = XDirect<W, BI, BJ>;
+  if (total * T::NT > 0xFFFFFFFFLL) return hipErrorInvalidValue;
+  const hipError_t e = ready_direct<W, BI, BJ>();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((cgemm_c64_direct_grouped<W, BI, BJ>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s,
+                     tab, n);
+  return hipGetLastError();
+}
+
 template <int WM, int WN, int PW>
 void prepare_shape() {
   (void)ready_one<WM, WN, PW, false>();
@@ -497,6 +714,9 @@ void prepare_gemm_c64() {
   prepare_shape<2, 2, 2>();
   prepare_shape<4, 2, 2>();
   prepare_shape<2, 4, 1>();
+  (void)ready_direct<8, 1, 1>();
+  (void)ready_direct<8, 1, 2>();
+  (void)ready_direct<8, 2, 2>();
 }
 
 // The 128 x 128 tile runs as four wide waves (each A fragment feeds four
@@ -516,6 +736,9 @@ hipError_t launch_gemm_c64_4m(const GemmDesc& d, int variant, hipStream_t s) {
     case 4: return launch_shape<1, 2, 1>(d, s);
     case 5: return launch_shape<2, 1, 1>(d, s);
     case 6: return launch_shape<1, 1, 1>(d, s);
+    case kDirect32x16: return launch_direct<8, 1, 1>(d, s);
+    case kDirect32x32: return launch_direct<8, 1, 2>(d, s);
+    case kDirect64x32: return launch_direct<8, 2, 2>(d, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -531,6 +754,9 @@ hipError_t launch_gemm_c64_4m_grouped(const GroupedEntry* tab, int n, int64_t to
     case 4: return launch_grouped_shape<1, 2, 1>(tab, n, total, s);
     case 5: return launch_grouped_shape<2, 1, 1>(tab, n, total, s);
     case 6: return launch_grouped_shape<1, 1, 1>(tab, n, total, s);
+    case kDirect32x16: return launch_direct_grouped<8, 1, 1>(tab, n, total, s);
+    case kDirect32x32: return launch_direct_grouped<8, 1, 2>(tab, n, total, s);
+    case kDirect64x32: return launch_direct_grouped<8, 2, 2>(tab, n, total, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -6,7 +6,8 @@
 // the many tiny steps of circuit networks (m, n or k of a few elements).
 // cgemm_dot:   one wave64 per output element for long reductions with few
 // outputs (k large, m*n tiny); 4 x 64 partial sums are combined by a fixed
-// tree, so the summation error grows like k/256 + 8 roundings, not k.
+// tree, so the summation error grows like k/256 + 8 roundings, not k
+// (cgemm_dot_few: one workgroup per output where there are few of them).
 // Both honour the split-bf16 precision with the same products as the MFMA
 // kernel (hi*hi and the two cross products accumulated separately).
 #include "gemm_common.hpp"
@@ -48,6 +49,8 @@ __global__ __launch_bounds__(256) void cgemm_small(GemmDesc d) {
 // independent partial sums (four loads per operand in flight), and the
 // 64 x 4 partial sums are combined by a fixed tree, so the summation error
 // grows like (k/256 + 8) roundings instead of k.
+constexpr int64_t kDotFewOutputs = 1024;  // four waves each fill the chip at most twice
+
 template <bool SPLIT>
 struct DotAcc {
   float cr = 0.f, ci = 0.f, crx = 0.f, cix = 0.f;
@@ -103,6 +106,54 @@ __global__ __launch_bounds__(256) void cgemm_dot(GemmDesc d) {
   }
 }
 
+// The same for a launch with few outputs: one workgroup per output (as a
+// wave per output, k = 4096 took 7.4 us for 16 outputs on four CUs, now
+// 3.9).  The four waves' sums are added in order.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void cgemm_dot_few(GemmDesc d) {
+  __shared__ float2 part[4];
+  const int tid = threadIdx.x;
+  const int64_t mn = d.m * d.n, out = blockIdx.x;
+  const int64_t b = out / mn, r = out - b * mn, i = r / d.n, j = r - i * d.n;
+  int64_t oa, ob;
+  batch_offsets(d, b, oa, ob);
+  const float2* a = d.A + oa + i * row_stride(d);
+  const float2* bb = d.B + ob + j * row_stride(d);
+  DotAcc<SPLIT> acc[4];
+  int64_t l = tid;
+  for (; l + 768 < d.k; l += 1024) {
+    float2 x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u] = a[l + 256 * u];
+      y[u] = bb[l + 256 * u];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u].add(x[u], y[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < 3; ++u)  // the last < 1024 elements
+    if (l + 256 * u < d.k) acc[u].add(a[l + 256 * u], bb[l + 256 * u]);
+  float sr = 0.f, si = 0.f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    sr += acc[u].cr + acc[u].crx;
+    si += acc[u].ci + acc[u].cix;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    sr += __shfl_xor(sr, off, 64);
+    si += __shfl_xor(si, off, 64);
+  }
+  if ((tid & 63) == 0) part[tid >> 6] = make_float2(sr, si);
+  __syncthreads();
+  if (tid == 0) {
+    const int64_t c = b * mn + (d.offM ? d.offM[i] + d.offN[j] : r);
+    d.C[c] = make_float2((part[0].x + part[1].x) + (part[2].x + part[3].x),
+                         (part[0].y + part[1].y) + (part[2].y + part[3].y));
+  }
+}
+
 __global__ __launch_bounds__(256) void splitk_reduce(const float2* __restrict__ P, float2* __restrict__ C,
                                                      int64_t h, int64_t m, int64_t n, int64_t S,
                                                      const int64_t* __restrict__ offM,
@@ -111,16 +162,35 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float2* __restrict__ 
   const int64_t total = h * mn;
   for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < total;
        idx += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t b = idx / mn;
-    const int64_t r = idx - b * mn;
+    int64_t b, r, i;
+    if (total <= 0xFFFFFFFFll) {  // 32-bit divisions
+      const uint32_t x = static_cast<uint32_t>(idx), xm = static_cast<uint32_t>(mn);
+      b = x / xm;
+      r = x - static_cast<uint32_t>(b) * xm;
+      i = static_cast<uint32_t>(r) / static_cast<uint32_t>(n);
+    } else {
+      b = idx / mn;
+      r = idx - b * mn;
+      i = r / n;
+    }
     const float2* p = P + b * S * mn + r;
     float cr = 0.f, ci = 0.f;
-    for (int64_t q = 0; q < S; ++q) {
+    int64_t q = 0;
+    for (; q + 8 <= S; q += 8) {  // eight reads in flight, added in order
+      float2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = p[(q + u) * mn];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        cr += v[u].x;
+        ci += v[u].y;
+      }
+    }
+    for (; q < S; ++q) {
       const float2 v = p[q * mn];
       cr += v.x;
       ci += v.y;
     }
-    const int64_t i = r / n;
     const int64_t j = r - i * n;
     C[b * mn + (offM ? offM[i] + offN[j] : r)] = make_float2(cr, ci);
   }
@@ -146,6 +216,13 @@ hipError_t launch_gemm_valu(const GemmDesc& d, GemmKernel kind, Prec prec, hipSt
     const int64_t total = d.h * d.m * d.n;
     const int64_t grid = (total + 3) / 4;
     if (grid > 0x7FFFFFLL) return hipErrorInvalidValue;
+    if (total <= kDotFewOutputs) {
+      if (prec == Prec::BF16X3)
+        hipLaunchKernelGGL(cgemm_dot_few<true>, dim3(total), dim3(256), 0, s, d);
+      else
+        hipLaunchKernelGGL(cgemm_dot_few<false>, dim3(total), dim3(256), 0, s, d);
+      return hipGetLastError();
+    }
     if (prec == Prec::BF16X3)
       hipLaunchKernelGGL(cgemm_dot<true>, dim3(grid), dim3(256), 0, s, d);
     else

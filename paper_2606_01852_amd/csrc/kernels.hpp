@@ -55,8 +55,9 @@ enum class GemmKernel : int { MFMA = 0, SMALL = 1, DOT = 2 };
 // Kernel choice for one step's shape (shared by the planner and the
 // stand-alone GEMM entry point).
 //  * MFMA for shapes that fill its 64 x 32 wave tiles, and for skinny shapes
-//    (m >= 16, n >= 8) with enough work (2^22 complex MACs) that running
-//    MFMA on padded tiles still beats one thread per output;
+//    (m >= 16, n >= 8) with enough work (2^22 complex MACs, or 2^18 with a
+//    long K) that running MFMA on padded tiles still beats one thread per
+//    output;
 //  * DOT (one wave64 per output) for long reductions with few outputs;
 //  * SMALL (one thread per output) for the rest: tiny steps.
 inline GemmKernel choose_gemm_kernel(int64_t h, int64_t m, int64_t n, int64_t k) {
@@ -68,6 +69,9 @@ inline GemmKernel choose_gemm_kernel(int64_t h, int64_t m, int64_t n, int64_t k)
     // 64: 11.7 vs 14.9 us) and joins its tree level's grouped launch
     if (m >= 64 && n >= 32 && (work >= (int64_t{1} << 22) || k > 128)) return GemmKernel::MFMA;
     if (m >= 16 && n >= 8 && work >= (int64_t{1} << 22)) return GemmKernel::MFMA;
+    // a long serial K on few outputs (16 x 256 x 256: 20.7 us one thread per
+    // output, 6.7 us on MFMA with K shared out)
+    if (m >= 16 && n >= 16 && k >= 128 && work >= (int64_t{1} << 18)) return GemmKernel::MFMA;
   }
   if (k >= 256 && m * n <= 64 && (h * m * n + 3) / 4 < 0x7FFFFF) return GemmKernel::DOT;
   return GemmKernel::SMALL;
@@ -183,6 +187,10 @@ struct GatherDesc {
 // MFMA tile variants: variant v uses workgroups of WM x WN wave64, each
 // wave owning 64 x 32 complex of C (gemm_variant_tile gives the block tile).
 constexpr int kGemmVariants = 7;
+// Beside them the complex64 4M form has three shapes for launches with few
+// tiles, whose waves share out K instead of the tile (named by their complex
+// tile; chosen by default_variant and the autotuner, never forced).
+constexpr int kDirect32x16 = 7, kDirect32x32 = 8, kDirect64x32 = 9, kAllVariants = 10;
 void gemm_variant_tile(int variant, int* bm, int* bnc);
 // Allow every MFMA kernel instance its LDS on the current device (best
 // effort; launches do it lazily as well).

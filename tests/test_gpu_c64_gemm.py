@@ -100,3 +100,28 @@ def test_values_the_split_cannot_hold(ctx, variant):
     assert np.all(within[finite_rows])
     assert got[4, 10, 20] == np.complex64(2.0 ** -40)
     assert not np.any(got[5, 17])
+
+
+# the shapes with few tiles (32 x 16, 32 x 32, 64 x 32 complex; eight waves
+# share K out in stages of 8): edges of the tiles, a K shorter than the waves'
+# first round, one that ends inside a stage, and one element more
+FEW_TILES = [(1, 64, 32, 129), (1, 65, 33, 136), (3, 90, 50, 321), (1, 200, 100, 210), (1, 512, 512, 24), (1, 500, 509, 67),
+             (9, 250, 130, 17), (8, 1000, 61, 130), (1, 16, 256, 256), (1, 33, 47, 4099)]
+
+
+@pytest.mark.parametrize("shape", FEW_TILES, ids=str)
+def test_few_tiles(ctx, shape):
+    h, m, n, k = shape
+    rng = np.random.Generator(np.random.PCG64(m * 7 + k))
+    A, B = cn(rng, (h, m, k)), cn(rng, (h, n, k))
+    print(shape, flush=True)
+    got = gemm(ctx, A, B)
+    assert_gemm_close(got, exact(A, B), A, B, tol=2 * np.sqrt(k) * 2.0 ** -24 + 2.0 ** -24)
+    A[0, m - 1, k - 1] = np.inf       # the last element of the last row's last stage
+    B[0, n - 1, 0] = np.float32(2.0 ** -140)
+    got2 = gemm(ctx, A, B)
+    assert not np.any(np.isfinite(got2[0, m - 1, :-1].real))
+    rows = np.ones((h, m), dtype=bool)
+    rows[0, m - 1] = False
+    assert np.all(np.abs(got2 - exact(np.where(np.isfinite(A), A, 0), B))[rows] <=
+                  gemm_elem_bound(np.where(np.isfinite(A), A, 0), B)[rows])
