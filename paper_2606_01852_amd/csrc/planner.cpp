@@ -248,11 +248,21 @@ PermuteShape permute_shape(const std::vector<int64_t>& ext0, const std::vector<i
   }
   P.n_hi = P.n_tiles / P.L;
   if (P.L > INT32_MAX || P.n_hi > INT32_MAX) return PermuteShape{};
-  // pairs: the same innermost mode, of even extent, in both orders, and every
-  // other stride even
-  bool pairs = rfast[0] == wfast[0] && st[rfast[0]] == 1 && ost[rfast[0]] == 1 && ext[rfast[0]] % 2 == 0;
-  for (int d = 0; d < r; ++d)
-    if (d != rfast[0]) pairs = pairs && st[d] % 2 == 0 && ost[d] % 2 == 0;
+  // pairs: elements 2x, 2x + 1 of the read order are adjacent in the input
+  // and those of the write order in the output, at even offsets.  An order's
+  // fastest modes are one contiguous run until its length is even; every
+  // other stride is even.  (The two orders' fastest modes may differ.)
+  auto paired = [&](const std::vector<int>& order, const std::vector<int64_t>& stride) {
+    int64_t run = 1;
+    for (int d : order) {
+      if (run % 2 ? stride[d] != run : stride[d] % 2 != 0) return false;
+      if (run % 2) run *= ext[d];
+    }
+    for (int d : outer)
+      if (stride[d] % 2 != 0) return false;
+    return run % 2 == 0;
+  };
+  const bool pairs = paired(rfast, st) && paired(wfast, ost);
   P.pairs = pairs ? 1 : 0;
   for (int q = 0; q < P.n_outer; ++q) {
     P.oext[q] = static_cast<uint32_t>(ext[outer[q]]);

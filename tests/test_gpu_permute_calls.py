@@ -18,6 +18,7 @@ CASES = [
     ((5, 7, 11, 13, 3), (4, 1, 3, 0, 2)),
     ((64, 128, 96), (2, 0, 1)),
     ((100, 6, 90, 2), (1, 2, 0, 3)),          # the innermost pair stays: 16-byte pairs
+    ((40, 10, 9, 2, 3), (1, 0, 2, 4, 3)),     # pairs of one run of 3 * 2, of different innermost modes
     ((9, 350, 33), (2, 1, 0)),                # 350 = 50 * 7, odd extents
     ((17, 8, 1, 24, 10), (3, 2, 0, 4, 1)),
     ((3, 4, 5), (2, 0, 1)),                   # plain gather
