@@ -60,23 +60,24 @@ typedef enum {
 } tnc_status;
 
 /* Arithmetic of the GEMMs.  C64: complex64 operands, float32 products and
- * accumulation (the paper's setting, Sec. V).  Its 4M form runs on the bf16
- * matrix pipe with every operand split exactly into three bf16 parts; its
+ * accumulation (the paper's setting, Sec. V).  MFMA steps run on the bf16
+ * matrix pipe with every operand split exactly into three bf16 parts; the
  * error against exact arithmetic is below that of a chain of float32 FMAs,
  * and values that such a split cannot hold (infinities, NaNs, the far ends
- * of the exponent range) are computed on the FP32 pipe.  BF16X3: each float32 operand
- * plane is split into bf16 hi + lo (round to nearest even) and every real
- * product is a_hi*b_hi + a_hi*b_lo + a_lo*b_hi on bf16 MFMA with FP32
- * accumulate (an extension, not in the paper). */
+ * of the exponent range) are computed on the FP32 pipe.  BF16X3: each
+ * float32 operand plane is split into bf16 hi + lo (round to nearest even)
+ * and every real product is a_hi*b_hi + a_hi*b_lo + a_lo*b_hi on bf16 MFMA
+ * with FP32 accumulate (an extension, not in the paper). */
 typedef enum { TNC_PREC_C64 = 0, TNC_PREC_BF16X3 = 1 } tnc_prec;
 
 /* Complex-GEMM form.  4M: four real products (re = ar*br - ai*bi,
- * im = ar*bi + ai*br), 8 real FLOPs per complex MAC.  3M: three real
- * products (T1 = ar*br, T2 = ai*bi, T3 = (ar+ai)(br+bi); re = T1 - T2,
- * im = T3 - T1 - T2), 6 executed FLOPs per complex MAC.  Both compose with
- * either precision on MFMA steps (BF16X3 + 3M: 9 bf16 products per complex
+ * im = ar*bi + ai*br), 8 real FLOPs per complex MAC.  3M: leave to use three
+ * (T1 = ar*br, T2 = ai*bi, T3 = (ar+ai)(br+bi); re = T1 - T2,
+ * im = T3 - T1 - T2).  BF16X3 MFMA steps do (9 bf16 products per complex
  * product instead of 12, the sums ar+ai and br+bi formed in float32 before
- * their split); the VALU kernels of small steps always use the 4M form. */
+ * their split); C64 MFMA steps compute 4M under either name, which is the
+ * faster and the more accurate of the two there, and so do the VALU kernels
+ * of small steps. */
 typedef enum { TNC_GEMM_4M = 0, TNC_GEMM_3M = 1 } tnc_cgemm;
 
 /* Element type of host leaf data handed to the library. */
@@ -385,9 +386,8 @@ tnc_status tnc_serve_set_heavy(tnc_ctx ctx, double heavy_flops, int32_t heavy_sl
  * (default 8; 1 disables fusion) and run in lockstep with the launches of
  * one run: every MFMA step is one grouped launch over the requests' GEMMs
  * of that step (one persistent kernel whose workgroups loop over the tiles
- * of all of them; every tile variant in 4M, all but 3 in 3M, 0 and 4-6 in
- * split precision's 4M form, all but 3 in its 3M form, other steps one
- * launch per request), and every tree level's small GEMMs and leaf gathers of
+ * of all of them; every tile variant but split precision's 3 in 3M, whose
+ * steps are one launch per request), and every tree level's small GEMMs and leaf gathers of
  * all the requests are one launch each.  Only requests that wait on their
  * launches more than on their arithmetic are fused: planned FLOP below
  * flops_per_launch times the launches of the request's own run

@@ -35,13 +35,14 @@ double padding_waste(int variant, int64_t m, int64_t n) {
   return 1.0 - static_cast<double>(m) * n / (pm * pn);
 }
 
+// complex64 runs the 4M kernels in both forms
+bool runs_4m(int prec, int form) { return prec == TNC_PREC_C64 || form == TNC_GEMM_4M; }
+
 // Ranking of the variants by measured per-tile throughput on large shapes.
 const std::vector<int>& ranking(tnc_prec prec, tnc_cgemm form) {
   static const std::vector<int> r4m = {3, 2, 0, 1, 4, 5, 6, kDirect64x32, kDirect32x32, kDirect32x16};
-  static const std::vector<int> r3m = {0, 2, 4, 1, 5, 6};  // 0: three (2,2) workgroups per CU
-  static const std::vector<int> rbf = {3, 0, 2, 1, 4, 5, 6};  // 3: the wide-wave 256 x 128 tile
-  if (form == TNC_GEMM_3M) return r3m;  // complex64 and split precision alike
-  return prec == TNC_PREC_BF16X3 ? rbf : r4m;
+  static const std::vector<int> r3m = {0, 2, 4, 1, 5, 6};
+  return runs_4m(prec, form) ? r4m : r3m;
 }
 
 std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n) {
@@ -56,7 +57,7 @@ std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m,
 
 }  // namespace
 
-// complex64 4M.  With few tiles the shapes that share K out: the largest of
+// 4M kernels.  With few tiles the shapes that share K out: the largest of
 // them that still has no more than one workgroup per CU (us per launch,
 // 128 x 64 tile before and the chosen shape: 256 x 256 x 256 26.6, 7.0;
 // 512 x 512 x 512 47, 14.6; 8 x 1024 x 64 x 128 17.3, 10.7; from 2048
@@ -66,12 +67,15 @@ std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m,
 // workgroups fill 256 CUs, and how well one CU's waves hide each other's
 // latency (fewer than two per SIMD do not: 2 x 4096 x 256 x 128 runs 20.5 us
 // on 256 workgroups of four waves, 28.0 on 512 of two, 24.8 on 128 of eight).
-static int default_variant_c64_4m(int64_t h, int64_t m, int64_t n) {
+static int default_variant_4m(tnc_prec prec, int64_t h, int64_t m, int64_t n) {
   const int64_t few = tiles_for(kDirect32x16, h, m, n);
   if (few <= 256) return kDirect32x16;
   if (few <= 512) return kDirect32x32;
   if (few <= 1024) return kDirect64x32;
-  static const double rate[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};
+  // (8192 x 8192 x 4096 in complex64, 64 x 1024 x 256 x 1024 in split precision)
+  static const double c64[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};
+  static const double bf16x3[kGemmVariants] = {0.83, 0.87, 0.875, 1.0, 0.70, 0.52, 0.495};
+  const double* rate = prec == TNC_PREC_BF16X3 ? bf16x3 : c64;
   static const int waves[kGemmVariants] = {4, 4, 8, 8, 2, 2, 1};
   int best = 4;
   double top = 0.0;
@@ -89,7 +93,7 @@ static int default_variant_c64_4m(int64_t h, int64_t m, int64_t n) {
 }
 
 int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n) {
-  if (prec == TNC_PREC_C64 && form == TNC_GEMM_4M) return default_variant_c64_4m(h, m, n);
+  if (runs_4m(prec, form)) return default_variant_4m(prec, h, m, n);
   // the best-ranked shape that still gives every CU a few tiles and wastes
   // little on padding; small problems fall through to the small shapes
   for (int v : ranking(prec, form))
@@ -110,7 +114,7 @@ void load_tune_cache(Ctx& c) {
   TuneKey key;
   int v = 0;
   while (f >> key.prec >> key.form >> key.perm >> key.h >> key.m >> key.n >> key.k >> v)
-    if (v >= 0 && v < (key.prec == TNC_PREC_C64 && key.form == TNC_GEMM_4M ? kAllVariants : kGemmVariants))
+    if (v >= 0 && v < (runs_4m(key.prec, key.form) ? kAllVariants : kGemmVariants))
       c.tune_cache[key] = v;
 }
 

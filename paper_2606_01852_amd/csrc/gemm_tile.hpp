@@ -130,6 +130,32 @@ __device__ __forceinline__ void store_perm_pairs(const GemmDesc& d, const TileCo
     }
 }
 
+// Store of a wave's 64 x 32 PW complex block held in the 4M layout, row-major
+// or through the offset tables; val as for store_perm_pairs.
+template <int PW, class Val>
+__device__ __forceinline__ void store_4m(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn, int lane,
+                                         Val val) {
+  if (perm) {
+    store_perm_pairs<PW>(d, tc, wm, wn, lane, val);
+    return;
+  }
+  const int h = lane >> 5, l32 = lane & 31;
+  // real column tc.col0 * 2 + 64 PW wn + 32 j + l32: complex column >> 1, re/im by parity
+  float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2 * PW; ++j) {
+      const int64_t col = (tc.col0 * 2 + wn * 64 * PW + j * 32 + l32) >> 1;
+      if (col >= d.n) continue;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+        if (row < d.m) C[2 * (row * d.n + col)] = val(i, j, v);
+      }
+    }
+}
+
 // Store of a wave's 64 x 32 complex block from the 3M products (one 32x32
 // accumulator block per 32 rows: T1 = Ar Br, T2 = Ai Bi, T3 = (Ar+Ai)(Br+Bi);
 // Re = T1 - T2, Im = T3 - T1 - T2), row-major or through the offset tables.

@@ -5,8 +5,9 @@
 // Sec. IV-A: the canonical operand layout maps directly to a GEMM).  Both
 // operands are K-contiguous, so the product is A * B^T per batch entry.
 //
-// Here are the 3M form of complex64 and both forms of split precision; the
-// 4M form of complex64 has a file of its own (kern_cgemm_c64.hip).
+// Here are split precision's 3M form, its pre-split planes (both forms) and
+// the choice between kernels; the 4M kernels have a file of their own
+// (kern_cgemm_4m.hip).
 //
 // 4M form.  A complex row of A, read as 2k floats (ar0, ai0, ar1, ai1, ...),
 // times the real 2k-vector
@@ -22,34 +23,25 @@
 //
 // BF16x3: each float32 plane is split into bf16 hi/lo (round to nearest
 // even) while it is staged into LDS; every real product becomes
-// a_hi b_hi + (a_hi b_lo + a_lo b_hi) on bf16 MFMA with FP32 accumulation
-// (hi and cross terms in separate accumulators; in the wide-wave variant
-// and the 3M form, one accumulator per real product).  It composes with
-// both forms: 12 bf16 products per complex product in the 4M form, 9 in
-// the 3M form (the sum planes Ar+Ai, Br+Bi formed in float32, then split).
-// Large single GEMMs split their operands once into bf16 planes in global
-// memory instead and stage them straight into LDS (the pre-split section
-// below); in the 3M form as three real GEMMs plus a combining pass.
+// a_hi b_hi + (a_hi b_lo + a_lo b_hi) on bf16 MFMA with FP32 accumulation.
+// 12 bf16 products per complex product in the 4M form, 9 in the 3M form (the
+// sum planes Ar+Ai, Br+Bi formed in float32, then split).  Large single
+// GEMMs split their operands once into bf16 planes in global memory instead
+// and stage them straight into LDS (the pre-split section below); in the 3M
+// form as three real GEMMs plus a combining pass.
 //
-// Tiling.  A wave64 owns a 64 x 32 complex tile of C (2x2 MFMA 32x32 blocks
-// of the real view, or 2x1 complex blocks in 3M); a workgroup is WM x WN
-// waves, so its tile is 64*WM x 32*WN complex.  The split-bf16 256 x 128
-// tile instead runs 4x2 waves of 64 x 64 complex each (2x4 blocks).  K advances 16
-// complex per stage through double-buffered LDS (rows padded to 144 B: the
-// 16-byte fragment reads of 16 lanes hit 16 distinct 4-bank groups).  Each
-// lane reads 4 consecutive real k and feeds them to 4 successive MFMAs; the
-// K order inside a stage is permuted the same way for A and B.  Interior
-// tiles run a copy of the main loop without bounds checks.  Tiles sweep N
-// in groups of 8 M-tiles, and workgroups are remapped (the hardware deals
-// them round-robin over the 8 XCDs, each with its own L2) so that the tiles
-// one XCD runs at once form 8 x 4 blocks: 12 operand panels per 32 tiles
-// through its L2.  Where the tile counts allow, the eight XCDs' blocks share
-// their 8 M-tiles, so the memory-side cache serves each A panel to all of
-// them from one HBM read (split precision on pair30: 316.7 -> 314.5 ms,
-// where the chip's power sets its clock; complex64 unchanged).
+// Tiling of the 3M form.  A wave64 owns a 64 x 32 complex tile of C (2x1
+// complex blocks of 32 x 32); a workgroup is WM x WN waves.  K advances 16
+// complex per stage through double-buffered LDS.  Interior tiles run a copy
+// of the main loop without bounds checks.  Tiles sweep N in groups of 8
+// M-tiles, and workgroups are remapped (the hardware deals them round-robin
+// over the 8 XCDs, each with its own L2) so that the tiles one XCD runs at
+// once form 8 x 4 blocks: 12 operand panels per 32 tiles through its L2.
+// Where the tile counts allow, the eight XCDs' blocks share their 8 M-tiles,
+// so the memory-side cache serves each A panel to all of them from one HBM
+// read (pre-split kernel on pair30's shape: 316.7 -> 314.5 ms).
 #include <atomic>
 #include <cstring>
-#include <type_traits>
 
 #include "bf16_split.hpp"
 #include "gemm_common.hpp"
@@ -59,46 +51,20 @@ namespace tnc {
 
 namespace {
 
+constexpr int BKC = 16;  // complex k per LDS stage
 
-constexpr int BKC = 16;     // complex k per LDS stage
-constexpr int SPITCH = 40;  // uint16 per LDS row of a bf16 plane (32 data + 8 pad)
-
-template <int WM, int WN, int PW = 1>
+template <int WM, int WN>
 struct Shape {
-  static constexpr int BM = 64 * WM;        // rows of C per workgroup
-  static constexpr int BNC = 32 * WN * PW;  // complex columns of C per workgroup (PW per wave)
+  static constexpr int BM = 64 * WM;   // rows of C per workgroup
+  static constexpr int BNC = 32 * WN;  // complex columns of C per workgroup
   static constexpr int NT = 64 * WM * WN;
-  // bf16 stage: A hi/lo planes of BM rows, B' hi/lo planes of 2*BNC real
-  // columns (the 4M real operand, built at staging), two buffers
-  static constexpr int BF16_STAGE = (2 * BM + 4 * BNC) * SPITCH;  // uint16 per buffer
-  static constexpr size_t lds_bf16 = 2 * BF16_STAGE * sizeof(uint16_t);
 };
 
-// Global -> register staging of one K stage (VW complex per load).  With
-// SWZ the rows are dealt to the 8-lane groups in a permuted order within
-// each block of 8 rows, so that the two groups of a 16-lane 8-byte LDS store
-// cycle hit disjoint banks (rows 80 bytes apart: A rows 4 apart, B' rows 4
-// apart = complex columns 2 apart); the data layout itself is unchanged.
-template <int WM, int WN, int VW, bool SWZ = false, int PW = 1>
+// Global -> register staging of one K stage (VW complex per load).
+template <int WM, int WN, int VW>
 struct Stage {
-  using S = Shape<WM, WN, PW>;
+  using S = Shape<WM, WN>;
   static constexpr int PER_ROW = BKC / VW;
-  __device__ __forceinline__ static int row_a(int idx) {
-    const int g = idx / PER_ROW;
-    if constexpr (SWZ && VW == 2) {
-      constexpr int p[8] = {0, 4, 1, 5, 2, 6, 3, 7};
-      return (g & ~7) | p[g & 7];
-    }
-    return g;
-  }
-  __device__ __forceinline__ static int row_b(int idx) {
-    const int g = idx / PER_ROW;
-    if constexpr (SWZ && VW == 2) {
-      constexpr int p[8] = {0, 2, 1, 3, 4, 6, 5, 7};
-      return (g & ~7) | p[g & 7];
-    }
-    return g;
-  }
   static constexpr int A_LOADS = S::BM * PER_ROW / S::NT;
   static constexpr int B_LOADS = S::BNC * PER_ROW / S::NT;
   static_assert(A_LOADS >= 1 && A_LOADS * S::NT == S::BM * PER_ROW, "A staging must tile evenly");
@@ -130,344 +96,13 @@ struct Stage {
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i) {
       const int idx = tid + S::NT * i;
-      a[i] = fetch<CHECK>(A, row0 + row_a(idx), kk + (idx % PER_ROW) * VW, m, k, ld);
+      a[i] = fetch<CHECK>(A, row0 + (idx / PER_ROW), kk + (idx % PER_ROW) * VW, m, k, ld);
     }
 #pragma unroll
     for (int i = 0; i < B_LOADS; ++i) {
       const int idx = tid + S::NT * i;
-      b[i] = fetch<CHECK>(B, col0 + row_b(idx), kk + (idx % PER_ROW) * VW, n, k, ld);
+      b[i] = fetch<CHECK>(B, col0 + (idx / PER_ROW), kk + (idx % PER_ROW) * VW, n, k, ld);
     }
-  }
-
-  // bf16 planes: the hi and lo halves of every float go to separate planes
-  // (hardware round-to-nearest-even conversion of two floats at a time,
-  // packed [first | second << 16]; lo = rne(x - hi), x - hi exact in
-  // float32).
-  __device__ __forceinline__ static void split2(float x, float y, uint32_t& hi, uint32_t& lo) {
-    bf16_split2(x, y, hi, lo);
-  }
-
-  // A: the staged floats in place (real k index = 2 * complex k + re/im).
-  __device__ __forceinline__ static void put_split(uint16_t* hi, uint16_t* lo, int idx, const f4& v) {
-    const int pos = row_a(idx) * SPITCH + 2 * (idx % PER_ROW) * VW;
-    uint32_t h01, l01;
-    split2(v.x, v.y, h01, l01);
-    if constexpr (VW == 2) {
-      uint32_t h23, l23;
-      split2(v.z, v.w, h23, l23);
-      *reinterpret_cast<uint2*>(hi + pos) = make_uint2(h01, h23);
-      *reinterpret_cast<uint2*>(lo + pos) = make_uint2(l01, l23);
-    } else {
-      *reinterpret_cast<uint32_t*>(hi + pos) = h01;
-      *reinterpret_cast<uint32_t*>(lo + pos) = l01;
-    }
-  }
-
-  // B: complex column c becomes the real columns 2c = (br, -bi, ...) and
-  // 2c + 1 = (bi, br, ...) of the 4M operand; negating a bf16 flips its
-  // sign bit (which commutes with the split), swapping re/im rotates the
-  // packed pair by 16 bits.
-  __device__ __forceinline__ static void put_split_b(uint16_t* hi, uint16_t* lo, int idx, const f4& v) {
-    const int c = row_b(idx);
-    const int pos0 = (2 * c) * SPITCH + 2 * (idx % PER_ROW) * VW;
-    const int pos1 = pos0 + SPITCH;
-    constexpr uint32_t NEG_IM = 0x80000000u;
-    auto swap = [](uint32_t w) { return (w >> 16) | (w << 16); };
-    uint32_t h01, l01;
-    split2(v.x, v.y, h01, l01);
-    if constexpr (VW == 2) {
-      uint32_t h23, l23;
-      split2(v.z, v.w, h23, l23);
-      *reinterpret_cast<uint2*>(hi + pos0) = make_uint2(h01 ^ NEG_IM, h23 ^ NEG_IM);
-      *reinterpret_cast<uint2*>(lo + pos0) = make_uint2(l01 ^ NEG_IM, l23 ^ NEG_IM);
-      *reinterpret_cast<uint2*>(hi + pos1) = make_uint2(swap(h01), swap(h23));
-      *reinterpret_cast<uint2*>(lo + pos1) = make_uint2(swap(l01), swap(l23));
-    } else {
-      *reinterpret_cast<uint32_t*>(hi + pos0) = h01 ^ NEG_IM;
-      *reinterpret_cast<uint32_t*>(lo + pos0) = l01 ^ NEG_IM;
-      *reinterpret_cast<uint32_t*>(hi + pos1) = swap(h01);
-      *reinterpret_cast<uint32_t*>(lo + pos1) = swap(l01);
-    }
-  }
-
-  __device__ __forceinline__ void store_split(uint16_t* Ah, uint16_t* Al, uint16_t* Bh, uint16_t* Bl,
-                                              int tid) const {
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) put_split(Ah, Al, tid + S::NT * i, a[i]);
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i) put_split_b(Bh, Bl, tid + S::NT * i, b[i]);
-  }
-};
-
-// ------------------------------------------------------------------ 3M, FP32 MFMA
-// LDS rows are unpadded (32 floats) with their eight 16-byte slots permuted
-// by row (slot = chunk ^ ((row >> 1) & 7)): the fragment reads of 16 lanes
-// (16 consecutive rows, one chunk) and the staging stores of 16 lanes (two
-// rows) each hit 16 distinct 4-bank groups, as the padded rows of the other
-// kernels do, in 49152 instead of 55296 bytes for the (2,2) tile, so three
-// of its workgroups fit a CU (two with padded rows).
-template <int WM, int WN, int VW>
-struct Ops3M {
-  using S = Shape<WM, WN>;
-  static constexpr bool kSwizzle = false;
-  static constexpr int kPW = 1;
-  static constexpr int P3 = 32;  // floats per LDS row
-  static constexpr size_t kLds = 2 * (S::BM + S::BNC) * P3 * sizeof(float);
-  f16v t1[2], t2[2], t3[2];
-
-  // float offset of float fo (even) of LDS row `row`
-  __device__ __forceinline__ static int at(int row, int fo) {
-    return row * P3 + ((((fo >> 2) ^ ((row >> 1) & 7)) << 2) | (fo & 3));
-  }
-
-  __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) t1[i][v] = t2[i][v] = t3[i][v] = 0.f;
-  }
-
-  template <class St>
-  __device__ __forceinline__ static void put(float* base, int row, int idx, const f4& v) {
-    float* p = base + at(row, 2 * (idx % St::PER_ROW) * VW);
-    if constexpr (VW == 2) {
-      *reinterpret_cast<f4*>(p) = v;
-    } else {
-      p[0] = v.x;
-      p[1] = v.y;
-    }
-  }
-
-  template <class St>
-  __device__ __forceinline__ void stage(const St& st, char* lds, int buf, int tid) const {
-    float* As = reinterpret_cast<float*>(lds) + buf * (S::BM + S::BNC) * P3;
-    float* Bs = As + S::BM * P3;
-#pragma unroll
-    for (int i = 0; i < St::A_LOADS; ++i) put<St>(As, St::row_a(tid + S::NT * i), tid + S::NT * i, st.a[i]);
-#pragma unroll
-    for (int i = 0; i < St::B_LOADS; ++i) put<St>(Bs, St::row_b(tid + S::NT * i), tid + S::NT * i, st.b[i]);
-  }
-
-  __device__ __forceinline__ void compute(const char* lds, int buf, int wm, int wn, int lane) {
-    const float* as = reinterpret_cast<const float*>(lds) + buf * (S::BM + S::BNC) * P3;
-    const float* bs = as + S::BM * P3;
-    const int h = lane >> 5, l32 = lane & 31;
-#pragma unroll
-    for (int g = 0; g < BKC / 4; ++g) {
-      const int koff = (4 * g + 2 * h) * 2;
-      const f4 rb = *reinterpret_cast<const f4*>(bs + at(wn * 32 + l32, koff));
-      const float bs0 = rb.x + rb.y, bs1 = rb.z + rb.w;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const f4 ra = *reinterpret_cast<const f4*>(as + at(wm * 64 + i * 32 + l32, koff));
-        const float as0 = ra.x + ra.y, as1 = ra.z + ra.w;
-        t1[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra.x, rb.x, t1[i], 0, 0, 0);
-        t2[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra.y, rb.y, t2[i], 0, 0, 0);
-        t3[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(as0, bs0, t3[i], 0, 0, 0);
-        t1[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra.z, rb.z, t1[i], 0, 0, 0);
-        t2[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra.w, rb.w, t2[i], 0, 0, 0);
-        t3[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(as1, bs1, t3[i], 0, 0, 0);
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn,
-                                        int lane) const {
-    store_3m(d, perm, tc, wm, wn, lane, t1, t2, t3);
-  }
-};
-
-// ------------------------------------------------------------------ split BF16x3, 4M form
-template <int WM, int WN, int VW>
-struct OpsBF16x3 {
-  using S = Shape<WM, WN>;
-  static constexpr bool kSwizzle = true;
-  static constexpr int kPW = 1;
-  static constexpr size_t kLds = S::lds_bf16;
-  // hi*hi products and the two cross products accumulate separately: the
-  // cross terms are ~2^-8 smaller, so their rounding barely adds to that of
-  // the main sum
-  f16v acc[2][2], accx[2][2];
-
-  __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = accx[i][j][v] = 0.f;
-  }
-
-  __device__ __forceinline__ static const uint16_t* planes(const char* lds, int buf) {
-    return reinterpret_cast<const uint16_t*>(lds) + buf * S::BF16_STAGE;
-  }
-
-  template <class St>
-  __device__ __forceinline__ void stage(const St& st, char* lds, int buf, int tid) const {
-    uint16_t* Ah = const_cast<uint16_t*>(planes(lds, buf));
-    uint16_t* Al = Ah + S::BM * SPITCH;
-    uint16_t* Bh = Al + S::BM * SPITCH;
-    uint16_t* Bl = Bh + 2 * S::BNC * SPITCH;
-    st.store_split(Ah, Al, Bh, Bl, tid);
-  }
-
-  // bf16 MFMA 32x32x16: lane (h, r) supplies 8 consecutive K values of row
-  // r (A) or real column r (B'); the stage's 32 real k are two sub-steps,
-  // lane half h taking k = 8 * (2s + h) .. +7.
-  __device__ __forceinline__ void compute(const char* lds, int buf, int wm, int wn, int lane) {
-    const uint16_t* Ah = planes(lds, buf);
-    const uint16_t* Al = Ah + S::BM * SPITCH;
-    const uint16_t* Bh = Al + S::BM * SPITCH;
-    const uint16_t* Bl = Bh + 2 * S::BNC * SPITCH;
-    const int h = lane >> 5, l32 = lane & 31;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int koff = 8 * (2 * s + h);
-      s8v ah[2], al[2], bh[2], bl[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = wm * 64 + i * 32 + l32;
-        ah[i] = *reinterpret_cast<const s8v*>(Ah + row * SPITCH + koff);
-        al[i] = *reinterpret_cast<const s8v*>(Al + row * SPITCH + koff);
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int row = 2 * (wn * 32 + j * 16) + l32;  // real column of B'
-        bh[j] = *reinterpret_cast<const s8v*>(Bh + row * SPITCH + koff);
-        bl[j] = *reinterpret_cast<const s8v*>(Bl + row * SPITCH + koff);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          accx[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, ah[i]),
-                                                               __builtin_bit_cast(bf8, bl[j]), accx[i][j], 0, 0, 0);
-          accx[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, al[i]),
-                                                               __builtin_bit_cast(bf8, bh[j]), accx[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, ah[i]),
-                                                              __builtin_bit_cast(bf8, bh[j]), acc[i][j], 0, 0, 0);
-        }
-    }
-  }
-
-  __device__ __forceinline__ void store(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn,
-                                        int lane) const {
-    const int h = lane >> 5, l32 = lane & 31;
-    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
-    if (!perm) {  // row-major [M|N]: addresses from the indices alone
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int64_t col = (tc.col0 * 2 + wn * 64 + j * 32 + l32) >> 1;
-          if (col >= d.n) continue;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-            if (row < d.m) C[2 * (row * d.n + col)] = acc[i][j][v] + accx[i][j][v];
-          }
-        }
-      return;
-    }
-    store_perm_pairs(d, tc, wm, wn, lane, [&](int i, int j, int v) { return acc[i][j][v] + accx[i][j][v]; });
-  }
-};
-
-// ------------------------------------------------------------------ split BF16x3, wide waves
-// The same products with each wave covering 64 complex columns (four
-// 32-column blocks of the real 4M operand) instead of 32: every A fragment
-// read from LDS feeds four blocks instead of two and the workgroup's staging
-// (and its split) is shared by twice the MFMA work, so the kernel issues
-// about 40 % fewer instructions per MFMA.  The accumulator budget of the
-// wider tile allows one accumulator set: hi*hi and the two cross products
-// accumulate together (FP32, as in the 4M kernel).
-template <int WM, int WN, int VW>
-struct OpsBF16x3W {
-  using S = Shape<WM, WN, 2>;
-  static constexpr bool kSwizzle = true;
-  static constexpr int kPW = 2;
-  static constexpr size_t kLds = S::lds_bf16;
-  f16v acc[2][4];
-
-  __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  }
-
-  __device__ __forceinline__ static const uint16_t* planes(const char* lds, int buf) {
-    return reinterpret_cast<const uint16_t*>(lds) + buf * S::BF16_STAGE;
-  }
-
-  template <class St>
-  __device__ __forceinline__ void stage(const St& st, char* lds, int buf, int tid) const {
-    uint16_t* Ah = const_cast<uint16_t*>(planes(lds, buf));
-    uint16_t* Al = Ah + S::BM * SPITCH;
-    uint16_t* Bh = Al + S::BM * SPITCH;
-    uint16_t* Bl = Bh + 2 * S::BNC * SPITCH;
-    st.store_split(Ah, Al, Bh, Bl, tid);
-  }
-
-  // lane (h, r) supplies 8 consecutive K values of row r (A) or real column
-  // r (B') per 32x32x16 MFMA, as in OpsBF16x3; this wave's real columns of
-  // B' are 128 * wn + 32 * j + r, j = 0..3.
-  __device__ __forceinline__ void compute(const char* lds, int buf, int wm, int wn, int lane) {
-    const uint16_t* Ah = planes(lds, buf);
-    const uint16_t* Al = Ah + S::BM * SPITCH;
-    const uint16_t* Bh = Al + S::BM * SPITCH;
-    const uint16_t* Bl = Bh + 2 * S::BNC * SPITCH;
-    const int h = lane >> 5, l32 = lane & 31;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int koff = 8 * (2 * s + h);
-      s8v ah[2], al[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = wm * 64 + i * 32 + l32;
-        ah[i] = *reinterpret_cast<const s8v*>(Ah + row * SPITCH + koff);
-        al[i] = *reinterpret_cast<const s8v*>(Al + row * SPITCH + koff);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = 128 * wn + 32 * j + l32;
-        const s8v bh = *reinterpret_cast<const s8v*>(Bh + row * SPITCH + koff);
-        const s8v bl = *reinterpret_cast<const s8v*>(Bl + row * SPITCH + koff);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, ah[i]),
-                                                              __builtin_bit_cast(bf8, bl), acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, al[i]),
-                                                              __builtin_bit_cast(bf8, bh), acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, ah[i]),
-                                                              __builtin_bit_cast(bf8, bh), acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn,
-                                        int lane) const {
-    const int h = lane >> 5, l32 = lane & 31;
-    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
-    if (!perm) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int64_t col = (tc.col0 * 2 + wn * 128 + j * 32 + l32) >> 1;
-          if (col >= d.n) continue;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-            if (row < d.m) C[2 * (row * d.n + col)] = acc[i][j][v];
-          }
-        }
-      return;
-    }
-    store_perm_pairs<2>(d, tc, wm, wn, lane, [&](int i, int j, int v) { return acc[i][j][v]; });
   }
 };
 
@@ -486,8 +121,6 @@ struct OpsBF16x3W {
 template <int WM, int WN, int VW>
 struct Ops3MBF16 {
   using S = Shape<WM, WN>;
-  static constexpr bool kSwizzle = false;
-  static constexpr int kPW = 1;
   static constexpr int ROWB = 32;  // bytes per plane row
   static constexpr int PLANE_A = S::BM * ROWB, PLANE_B = S::BNC * ROWB;
   static constexpr int STAGE = 6 * (PLANE_A + PLANE_B);
@@ -539,9 +172,9 @@ struct Ops3MBF16 {
     char* As = lds + buf * STAGE;
     char* Bs = As + 6 * PLANE_A;
 #pragma unroll
-    for (int i = 0; i < St::A_LOADS; ++i) put<St>(As, PLANE_A, St::row_a(tid + S::NT * i), tid + S::NT * i, st.a[i]);
+    for (int i = 0; i < St::A_LOADS; ++i) put<St>(As, PLANE_A, (tid + S::NT * i) / St::PER_ROW, tid + S::NT * i, st.a[i]);
 #pragma unroll
-    for (int i = 0; i < St::B_LOADS; ++i) put<St>(Bs, PLANE_B, St::row_b(tid + S::NT * i), tid + S::NT * i, st.b[i]);
+    for (int i = 0; i < St::B_LOADS; ++i) put<St>(Bs, PLANE_B, (tid + S::NT * i) / St::PER_ROW, tid + S::NT * i, st.b[i]);
   }
 
   __device__ __forceinline__ static void mm(f16v& t, const s8v& ah, const s8v& al, const s8v& bh, const s8v& bl) {
@@ -583,12 +216,12 @@ struct Ops3MBF16 {
 };
 
 // ------------------------------------------------------------------ driver
-template <int WM, int WN, int VW, bool CHECK, class Ops>
+template <int WM, int WN, int VW, bool CHECK>
 __device__ __forceinline__ void main_loop(const GemmDesc& d, const float2* A, const float2* B, const TileCoord& tc,
-                                          char* lds, Ops& ops, int tid, int wm, int wn, int lane) {
+                                          char* lds, Ops3MBF16<WM, WN, VW>& ops, int tid, int wm, int wn, int lane) {
   const int64_t nk = (d.k + BKC - 1) / BKC;
   const int64_t ld = row_stride(d);
-  Stage<WM, WN, VW, Ops::kSwizzle, Ops::kPW> st;
+  Stage<WM, WN, VW> st;
   st.template load<CHECK>(A, B, d.m, d.n, d.k, ld, tc.row0, tc.col0, 0, tid);
   ops.stage(st, lds, 0, tid);
   __syncthreads();
@@ -601,20 +234,10 @@ __device__ __forceinline__ void main_loop(const GemmDesc& d, const float2* A, co
   }
 }
 
-// Workgroups per CU the compiler must allow for: two for shapes of up to
-// four waves, three for 3M's (2,2) with 16-byte loads (its LDS admits
-// three; 168 VGPRs each; the 8-byte-load path needs more registers).
-template <template <int, int, int> class OpsT, int WM, int WN, int VW>
-constexpr int min_blocks() {
-  if constexpr (std::is_same_v<OpsT<2, 2, 2>, Ops3M<2, 2, 2>>)
-    if (WM * WN == 4 && VW == 2) return 3;
-  return WM * WN <= 4 ? 2 : 1;
-}
-
-template <template <int, int, int> class OpsT, int WM, int WN, int VW, bool PERM>
-__global__ __launch_bounds__(64 * WM * WN, (min_blocks<OpsT, WM, WN, VW>())) void cgemm_mfma(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
-                                                           int64_t total) {
-  using S = Shape<WM, WN, OpsT<WM, WN, VW>::kPW>;
+template <int WM, int WN, int VW, bool PERM>
+__global__ __launch_bounds__(64 * WM * WN, WM * WN <= 4 ? 2 : 1) void cgemm_mfma(GemmDesc d, int64_t tiles_m,
+                                                                                 int64_t tiles_n, int64_t total) {
+  using S = Shape<WM, WN>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -624,7 +247,7 @@ __global__ __launch_bounds__(64 * WM * WN, (min_blocks<OpsT, WM, WN, VW>())) voi
   batch_offsets(d, tc.b, oa, ob);
   const float2* __restrict__ A = d.A + oa;
   const float2* __restrict__ B = d.B + ob;
-  OpsT<WM, WN, VW> ops;
+  Ops3MBF16<WM, WN, VW> ops;
   ops.init();
   const bool interior = tc.row0 + S::BM <= d.m && tc.col0 + S::BNC <= d.n && d.k % BKC == 0;
   if (interior)
@@ -641,17 +264,11 @@ __global__ __launch_bounds__(64 * WM * WN, (min_blocks<OpsT, WM, WN, VW>())) voi
 // single-GEMM kernel's, line for line.  The tile loop keeps more values
 // live than one tile does, so most instances are built for one workgroup
 // per CU, which lets the compiler keep accumulators in AGPRs instead of
-// spilling (the persistent grid runs a fixed number of workgroups anyway);
-// the complex64 (2,2) tile fits two.
-template <template <int, int, int> class OpsT, int WM, int WN>
-constexpr int grouped_min_blocks() {
-  return WM * WN == 4 && !std::is_same_v<OpsT<2, 2, 2>, OpsBF16x3<2, 2, 2>> ? 2 : 1;
-}
-
-template <template <int, int, int> class OpsT, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN, (grouped_min_blocks<OpsT, WM, WN>())) void cgemm_mfma_grouped(
+// spilling (the persistent grid runs a fixed number of workgroups anyway).
+template <int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void cgemm_mfma_grouped(
     const GroupedEntry* __restrict__ tab, int n, int64_t total) {
-  using S = Shape<WM, WN, OpsT<WM, WN, 2>::kPW>;
+  using S = Shape<WM, WN>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -669,7 +286,7 @@ __global__ __launch_bounds__(64 * WM * WN, (grouped_min_blocks<OpsT, WM, WN>()))
     batch_offsets(d, tc.b, oa, ob);
     const float2* __restrict__ A = d.A + oa;
     const float2* __restrict__ B = d.B + ob;
-    OpsT<WM, WN, 2> ops;
+    Ops3MBF16<WM, WN, 2> ops;
     ops.init();
     const bool interior = tc.row0 + S::BM <= d.m && tc.col0 + S::BNC <= d.n && d.k % BKC == 0;
     if (interior)
@@ -690,8 +307,8 @@ __global__ __launch_bounds__(64 * WM * WN, (grouped_min_blocks<OpsT, WM, WN>()))
 // moves blocks straight from global memory into LDS (16 bytes per lane,
 // global_load_lds_dwordx4: no registers and no VALU on the way).  The split
 // is the staging kernels' (round to nearest even, lo = rne(x - hi)) and the
-// tile's products and accumulation order are those of OpsBF16x3W, so the
-// result is bitwise that of the wide-wave kernel.
+// tile's products and accumulation order are those of the 4M kernels' 256 x
+// 128 tile, so the result is bitwise that tile's.
 //
 // LDS: two stages of four unpadded planes (256 rows x 64 bytes each); the
 // four 16-byte slots of a row are permuted by row (slot = chunk ^ ((row >> 2)
@@ -712,9 +329,7 @@ __device__ __forceinline__ int64_t ps_index(int64_t row, int64_t kc, int64_t kp)
   return row * 2 * kp + 32 * (kc >> 4) + (kc & 15);
 }
 
-__device__ __forceinline__ void ps_split(float x, float y, uint32_t& hi, uint32_t& lo) {
-  Stage<4, 2, 2, true, 2>::split2(x, y, hi, lo);
-}
+__device__ __forceinline__ void ps_split(float x, float y, uint32_t& hi, uint32_t& lo) { bf16_split2(x, y, hi, lo); }
 
 // One thread per complex element of the padded planes; 16 consecutive
 // threads cover one 128-byte block (their loads 128 contiguous bytes of
@@ -810,9 +425,8 @@ struct PsFrag {
   s8v ah[2], al[2], bh[4], bl[4];
 };
 
-// Fragments of sub-step s (16 real k) for wave (wm, wn), as OpsBF16x3W
-// reads them: lane (h, r) takes 8 consecutive k of row r (A) or real column
-// r (B').
+// Fragments of sub-step s (16 real k) for wave (wm, wn): lane (h, r) takes 8
+// consecutive k of row r (A) or real column r (B').
 __device__ __forceinline__ void ps_read(const char* stage, int wm, int wn, int h, int l32, int s, PsFrag& f) {
   const int ch = 2 * s + h;
 #pragma unroll
@@ -831,7 +445,7 @@ __device__ __forceinline__ void ps_read(const char* stage, int wm, int wn, int h
   }
 }
 
-// OpsBF16x3W's products in its order: per block, a_hi b_lo, a_lo b_hi, a_hi b_hi
+// Per block a_hi b_lo, a_lo b_hi, a_hi b_hi, into one accumulator.
 __device__ __forceinline__ void ps_mfma(f16v (&acc)[2][4], const PsFrag& f) {
 #pragma unroll
   for (int j = 0; j < 4; ++j)
@@ -909,8 +523,7 @@ __global__ __launch_bounds__(512, 1) void cgemm_bf16x3_presplit(GemmDesc d, cons
   const uint32_t* gA = Ap + tc.row0 * 2 * kp;
   const uint32_t* gB = Bp + 2 * tc.col0 * 2 * kp;
   const int64_t nk = kp / BKC;
-  OpsBF16x3W<4, 2, 2> ops;
-  ops.init();
+  f16v acc[2][4] = {};
   PsFrag f0, f1;
   ps_issue(lds, 0, 0, gA, gB, kp, wave, lane);
   if (nk > 1) {
@@ -923,11 +536,11 @@ __global__ __launch_bounds__(512, 1) void cgemm_bf16x3_presplit(GemmDesc d, cons
   ps_read(lds, wm, wn, h, l32, 0, f0);
   if (nk > 1) {
     for (int64_t kt = 0; kt + 2 < nk; ++kt)
-      ps_stage<true, true>(ops.acc, f0, f1, lds, kt, gA, gB, kp, wave, lane, wm, wn, h, l32);
-    ps_stage<false, true>(ops.acc, f0, f1, lds, nk - 2, gA, gB, kp, wave, lane, wm, wn, h, l32);
+      ps_stage<true, true>(acc, f0, f1, lds, kt, gA, gB, kp, wave, lane, wm, wn, h, l32);
+    ps_stage<false, true>(acc, f0, f1, lds, nk - 2, gA, gB, kp, wave, lane, wm, wn, h, l32);
   }
-  ps_stage<false, false>(ops.acc, f0, f1, lds, nk - 1, gA, gB, kp, wave, lane, wm, wn, h, l32);
-  ops.store(d, PERM, tc, wm, wn, lane);
+  ps_stage<false, false>(acc, f0, f1, lds, nk - 1, gA, gB, kp, wave, lane, wm, wn, h, l32);
+  store_4m<2>(d, PERM, tc, wm, wn, lane, [&](int i, int j, int v) { return acc[i][j][v]; });
 }
 
 // LDS above 64 KiB for the pre-split kernel, once per device.
@@ -950,7 +563,7 @@ hipError_t ensure_lds_presplit() {
 // LDS above 64 KiB must be allowed per kernel, once per device (done for
 // every instance when a context is created, so that no first launch inside
 // a graph capture has to do it).
-template <template <int, int, int> class OpsT, int WM, int WN, int VW, bool PERM>
+template <int WM, int WN, int VW, bool PERM>
 hipError_t ensure_lds(size_t lds) {
   static std::atomic<uint64_t> attr_set{0};
   if (lds <= 65536) return hipSuccess;
@@ -959,28 +572,28 @@ hipError_t ensure_lds(size_t lds) {
   if (ge != hipSuccess) return ge;
   const uint64_t bit = uint64_t{1} << (dev & 63);
   if (attr_set.load(std::memory_order_acquire) & bit) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(cgemm_mfma<OpsT, WM, WN, VW, PERM>),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(cgemm_mfma<WM, WN, VW, PERM>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e == hipSuccess) attr_set.fetch_or(bit, std::memory_order_acq_rel);
   return e;
 }
 
-template <template <int, int, int> class OpsT, int WM, int WN, int VW, bool PERM>
+template <int WM, int WN, int VW, bool PERM>
 hipError_t launch_one(const GemmDesc& d, size_t lds, hipStream_t s) {
-  using S = Shape<WM, WN, OpsT<WM, WN, VW>::kPW>;
+  using S = Shape<WM, WN>;
   const int64_t tiles_m = (d.m + S::BM - 1) / S::BM;
   const int64_t tiles_n = (d.n + S::BNC - 1) / S::BNC;
   const int64_t total = tiles_m * tiles_n * d.h;
   // one workgroup per tile; the grid's work-items must fit 32 bits
   if (total * S::NT > 0xFFFFFFFFLL) return hipErrorInvalidValue;
-  const hipError_t e = ensure_lds<OpsT, WM, WN, VW, PERM>(lds);
+  const hipError_t e = ensure_lds<WM, WN, VW, PERM>(lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((cgemm_mfma<OpsT, WM, WN, VW, PERM>), dim3(static_cast<unsigned>(total)), dim3(S::NT), lds, s, d,
+  hipLaunchKernelGGL((cgemm_mfma<WM, WN, VW, PERM>), dim3(static_cast<unsigned>(total)), dim3(S::NT), lds, s, d,
                      tiles_m, tiles_n, total);
   return hipGetLastError();
 }
 
-template <template <int, int, int> class OpsT, int WM, int WN>
+template <int WM, int WN>
 hipError_t ensure_lds_grouped(size_t lds) {
   static std::atomic<uint64_t> attr_set{0};
   if (lds <= 65536) return hipSuccess;
@@ -989,142 +602,97 @@ hipError_t ensure_lds_grouped(size_t lds) {
   if (ge != hipSuccess) return ge;
   const uint64_t bit = uint64_t{1} << (dev & 63);
   if (attr_set.load(std::memory_order_acquire) & bit) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(cgemm_mfma_grouped<OpsT, WM, WN>),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(cgemm_mfma_grouped<WM, WN>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (e == hipSuccess) attr_set.fetch_or(bit, std::memory_order_acq_rel);
   return e;
 }
 
-template <template <int, int, int> class OpsT, int WM, int WN, bool GROUPED = true>
-void prepare_shape(bool) {
-  const size_t lds = OpsT<WM, WN, 2>::kLds;
-  (void)ensure_lds<OpsT, WM, WN, 2, false>(lds);
-  (void)ensure_lds<OpsT, WM, WN, 2, true>(lds);
-  if constexpr (GROUPED) (void)ensure_lds_grouped<OpsT, WM, WN>(lds);
+template <int WM, int WN>
+void prepare_shape() {
+  const size_t lds = Ops3MBF16<WM, WN, 2>::kLds;
+  (void)ensure_lds<WM, WN, 2, false>(lds);
+  (void)ensure_lds<WM, WN, 2, true>(lds);
+  (void)ensure_lds_grouped<WM, WN>(lds);
 }
 
 // Persistent grid: a multiple of 8 (one range of tiles per XCD), never more
 // than the tiles; at most 512 workgroups (two per compute unit), or 2048
 // waves for the shapes of fewer than four waves.
-template <template <int, int, int> class OpsT, int WM, int WN>
-hipError_t launch_grouped_shape(const GroupedEntry* tab, int n, int64_t total, bool, hipStream_t s) {
-  using S = Shape<WM, WN, OpsT<WM, WN, 2>::kPW>;
-  const size_t lds = OpsT<WM, WN, 2>::kLds;
-  const hipError_t e = ensure_lds_grouped<OpsT, WM, WN>(lds);
+template <int WM, int WN>
+hipError_t launch_grouped_shape(const GroupedEntry* tab, int n, int64_t total, hipStream_t s) {
+  using S = Shape<WM, WN>;
+  const size_t lds = Ops3MBF16<WM, WN, 2>::kLds;
+  const hipError_t e = ensure_lds_grouped<WM, WN>(lds);
   if (e != hipSuccess) return e;
   constexpr int64_t cap = WM * WN < 4 ? 2048 / (WM * WN) : 512;
   int64_t grid = (total + 7) / 8 * 8;
   if (grid > cap) grid = cap;
-  hipLaunchKernelGGL((cgemm_mfma_grouped<OpsT, WM, WN>), dim3(static_cast<unsigned>(grid)), dim3(S::NT), lds, s, tab,
+  hipLaunchKernelGGL((cgemm_mfma_grouped<WM, WN>), dim3(static_cast<unsigned>(grid)), dim3(S::NT), lds, s, tab,
                      n, total);
   return hipGetLastError();
 }
 
-// Grouped forms are built only where the persistent tile loop fits the
-// registers without spilling (compiler resource report for gfx950, with
-// the launch bounds above): every complex64 4M shape, 3M but (4,4), and
-// split precision's (2,2), (1,2), (2,1), (1,1).  Other grouped launches fail
-// with hipErrorInvalidValue; callers run those GEMMs one launch each.
-template <template <int, int, int> class OpsT>
-constexpr bool grouped_ok(int variant) {
-  if (variant < 0 || variant >= kGemmVariants) return false;
-  if constexpr (std::is_same_v<OpsT<2, 2, 2>, OpsBF16x3<2, 2, 2>>) return variant == 0 || variant >= 4;
-  if constexpr (std::is_same_v<OpsT<2, 2, 2>, Ops3M<2, 2, 2>>) return variant != 3;
-  if constexpr (std::is_same_v<OpsT<2, 2, 2>, Ops3MBF16<2, 2, 2>>) return variant != 3;
-  return true;
-}
+// The 3M split form has no (4,4) instance: its three accumulator sets spill
+// at sixteen waves per workgroup (compiler resource report), so a forced
+// variant 3 runs its (4,2) tile, and has no grouped form (those fail with
+// hipErrorInvalidValue; callers run such GEMMs one launch each).
+constexpr bool grouped_ok_3m(int variant) { return variant >= 0 && variant < kGemmVariants && variant != 3; }
 
-template <template <int, int, int> class OpsT>
-hipError_t launch_grouped_variant(const GroupedEntry* tab, int n, int64_t total, int variant, bool bf16,
-                                  hipStream_t s) {
-  if (!grouped_ok<OpsT>(variant)) return hipErrorInvalidValue;
+hipError_t launch_grouped_3m(const GroupedEntry* tab, int n, int64_t total, int variant, hipStream_t s) {
   switch (variant) {
-    case 0: return launch_grouped_shape<OpsT, 2, 2>(tab, n, total, bf16, s);
-    case 4: return launch_grouped_shape<OpsT, 1, 2>(tab, n, total, bf16, s);
-    case 5: return launch_grouped_shape<OpsT, 2, 1>(tab, n, total, bf16, s);
-    case 6: return launch_grouped_shape<OpsT, 1, 1>(tab, n, total, bf16, s);
-    default: break;
-  }
-  if constexpr (!std::is_same_v<OpsT<2, 2, 2>, OpsBF16x3<2, 2, 2>>) {
-    switch (variant) {
-      case 1: return launch_grouped_shape<OpsT, 4, 2>(tab, n, total, bf16, s);
-      case 2: return launch_grouped_shape<OpsT, 2, 4>(tab, n, total, bf16, s);
-      case 3:
-        if constexpr (!std::is_same_v<OpsT<2, 2, 2>, Ops3M<2, 2, 2>> && !std::is_same_v<OpsT<2, 2, 2>, Ops3MBF16<2, 2, 2>>)
-          return launch_grouped_shape<OpsT, 4, 4>(tab, n, total, bf16, s);
-        break;
-      default: break;
-    }
-  }
-  return hipErrorInvalidValue;
-}
-
-// The narrow split tile has no (4,4) instance: split precision runs that
-// tile size as 4x2 wide waves (the narrow waves' two accumulator sets would
-// spill).  Nor has the 3M split form: its three accumulator sets spill at
-// sixteen waves per workgroup (compiler resource report), so a forced
-// variant 3 runs its (4,2) tile.
-template <template <int, int, int> class OpsT>
-constexpr bool is_split() {
-  return std::is_same_v<OpsT<2, 2, 2>, OpsBF16x3<2, 2, 2>>;
-}
-template <template <int, int, int> class OpsT>
-constexpr bool is_split_3m() {
-  return std::is_same_v<OpsT<2, 2, 2>, Ops3MBF16<2, 2, 2>>;
-}
-
-template <template <int, int, int> class OpsT>
-void prepare_ops(bool bf16) {
-  prepare_shape<OpsT, 2, 2, grouped_ok<OpsT>(0)>(bf16);
-  prepare_shape<OpsT, 4, 2, grouped_ok<OpsT>(1)>(bf16);
-  prepare_shape<OpsT, 2, 4, grouped_ok<OpsT>(2)>(bf16);
-  if constexpr (!is_split<OpsT>() && !is_split_3m<OpsT>()) prepare_shape<OpsT, 4, 4, grouped_ok<OpsT>(3)>(bf16);
-  prepare_shape<OpsT, 1, 2, grouped_ok<OpsT>(4)>(bf16);
-  prepare_shape<OpsT, 2, 1, grouped_ok<OpsT>(5)>(bf16);
-  prepare_shape<OpsT, 1, 1, grouped_ok<OpsT>(6)>(bf16);
-  const size_t lds = OpsT<2, 2, 1>::kLds;  // odd-k path
-  (void)ensure_lds<OpsT, 2, 2, 1, false>(lds);
-  (void)ensure_lds<OpsT, 2, 2, 1, true>(lds);
-}
-
-template <template <int, int, int> class OpsT, int WM, int WN>
-hipError_t launch_shape(const GemmDesc& d, bool, hipStream_t s) {
-  const size_t lds = OpsT<WM, WN, 2>::kLds;
-  const bool perm = d.offM != nullptr;
-  return perm ? launch_one<OpsT, WM, WN, 2, true>(d, lds, s) : launch_one<OpsT, WM, WN, 2, false>(d, lds, s);
-}
-
-template <template <int, int, int> class OpsT>
-hipError_t launch_variant(const GemmDesc& d, int variant, bool bf16, hipStream_t s) {
-  if ((d.k | row_stride(d)) % 2 != 0) {  // odd k or row stride: 8-byte loads, default shape only
-    const size_t lds = OpsT<2, 2, 1>::kLds;
-    return d.offM ? launch_one<OpsT, 2, 2, 1, true>(d, lds, s) : launch_one<OpsT, 2, 2, 1, false>(d, lds, s);
-  }
-  // split precision: the 256 x 128 tile runs as 4x2 wide waves (16 waves of
-  // the narrow kind would spill their two accumulator sets)
-  switch (variant) {
-    case 0: return launch_shape<OpsT, 2, 2>(d, bf16, s);
-    case 1: return launch_shape<OpsT, 4, 2>(d, bf16, s);
-    case 2: return launch_shape<OpsT, 2, 4>(d, bf16, s);
-    case 3:
-      if constexpr (is_split<OpsT>()) return launch_shape<OpsBF16x3W, 4, 2>(d, true, s);
-      else if constexpr (is_split_3m<OpsT>()) return launch_shape<OpsT, 4, 2>(d, true, s);
-      else return launch_shape<OpsT, 4, 4>(d, bf16, s);
-    case 4: return launch_shape<OpsT, 1, 2>(d, bf16, s);
-    case 5: return launch_shape<OpsT, 2, 1>(d, bf16, s);
-    case 6: return launch_shape<OpsT, 1, 1>(d, bf16, s);
+    case 0: return launch_grouped_shape<2, 2>(tab, n, total, s);
+    case 1: return launch_grouped_shape<4, 2>(tab, n, total, s);
+    case 2: return launch_grouped_shape<2, 4>(tab, n, total, s);
+    case 4: return launch_grouped_shape<1, 2>(tab, n, total, s);
+    case 5: return launch_grouped_shape<2, 1>(tab, n, total, s);
+    case 6: return launch_grouped_shape<1, 1>(tab, n, total, s);
     default: return hipErrorInvalidValue;
   }
 }
 
+template <int WM, int WN>
+hipError_t launch_shape(const GemmDesc& d, hipStream_t s) {
+  const size_t lds = Ops3MBF16<WM, WN, 2>::kLds;
+  return d.offM ? launch_one<WM, WN, 2, true>(d, lds, s) : launch_one<WM, WN, 2, false>(d, lds, s);
+}
+
+hipError_t launch_split_3m(const GemmDesc& d, int variant, hipStream_t s) {
+  if ((d.k | row_stride(d)) % 2 != 0) {  // odd k or row stride: 8-byte loads, default shape only
+    const size_t lds = Ops3MBF16<2, 2, 1>::kLds;
+    return d.offM ? launch_one<2, 2, 1, true>(d, lds, s) : launch_one<2, 2, 1, false>(d, lds, s);
+  }
+  switch (variant) {
+    case 0: return launch_shape<2, 2>(d, s);
+    case 1:
+    case 3: return launch_shape<4, 2>(d, s);
+    case 2: return launch_shape<2, 4>(d, s);
+    case 4: return launch_shape<1, 2>(d, s);
+    case 5: return launch_shape<2, 1>(d, s);
+    case 6: return launch_shape<1, 1>(d, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Which kernels run a form: split precision has both; complex64 runs the 4M
+// kernels in either (8 x 1024 x 512 x 768 in float32 3M 163 complex TFLOP/s,
+// 178 at best on large shapes, against 205-230 here, and with an imaginary
+// part that is not a difference of three sums).
+bool three_m(Form form, Prec prec) { return form == Form::M3 && prec == Prec::BF16X3; }
+
 }  // namespace
 
 void prepare_gemm_kernels() {
-  prepare_gemm_c64();
-  prepare_ops<Ops3M>(false);
-  prepare_ops<OpsBF16x3>(true);
-  prepare_ops<Ops3MBF16>(true);
-  prepare_shape<OpsBF16x3W, 4, 2, false>(true);
+  prepare_gemm_4m();
+  prepare_shape<2, 2>();
+  prepare_shape<4, 2>();
+  prepare_shape<2, 4>();
+  prepare_shape<1, 2>();
+  prepare_shape<2, 1>();
+  prepare_shape<1, 1>();
+  const size_t lds = Ops3MBF16<2, 2, 1>::kLds;  // odd-k path
+  (void)ensure_lds<2, 2, 1, false>(lds);
+  (void)ensure_lds<2, 2, 1, true>(lds);
   (void)ensure_lds_presplit();
 }
 
@@ -1152,20 +720,15 @@ int64_t grouped_layout(GroupedEntry* e, int n, int variant) {
 }
 
 bool grouped_variant_ok(Form form, Prec prec, int variant) {
-  if (prec == Prec::BF16X3)
-    return form == Form::M3 ? grouped_ok<Ops3MBF16>(variant) : grouped_ok<OpsBF16x3>(variant);
-  if (form == Form::M3) return grouped_ok<Ops3M>(variant);
+  if (three_m(form, prec)) return grouped_ok_3m(variant);
   return variant >= 0 && variant < kAllVariants;
 }
 
 hipError_t launch_gemm_grouped(const GroupedEntry* dev, int n, int64_t total, int variant, Form form, Prec prec,
                                hipStream_t s) {
   if (n <= 0 || total <= 0) return hipSuccess;
-  if (prec == Prec::BF16X3)
-    return form == Form::M3 ? launch_grouped_variant<Ops3MBF16>(dev, n, total, variant, true, s)
-                            : launch_grouped_variant<OpsBF16x3>(dev, n, total, variant, true, s);
-  if (form == Form::M3) return launch_grouped_variant<Ops3M>(dev, n, total, variant, false, s);
-  return launch_gemm_c64_4m_grouped(dev, n, total, variant, s);
+  if (three_m(form, prec)) return launch_grouped_3m(dev, n, total, variant, s);
+  return launch_gemm_4m_grouped(dev, n, total, variant, prec, s);
 }
 
 hipError_t launch_gemm_presplit(const GemmDesc& d, void* planes, bool have_a, bool have_b, hipStream_t s) {
@@ -1250,11 +813,8 @@ hipError_t launch_gemm(const GemmDesc& d, GemmKernel kind, int variant, Form for
   if (d.h <= 0 || d.m <= 0 || d.n <= 0) return hipSuccess;
   if (d.k <= 0) return hipErrorInvalidValue;
   if (kind != GemmKernel::MFMA) return launch_gemm_valu(d, kind, prec, s);
-  if (prec == Prec::BF16X3)
-    return form == Form::M3 ? launch_variant<Ops3MBF16>(d, variant, true, s)
-                            : launch_variant<OpsBF16x3>(d, variant, true, s);
-  if (form == Form::M3) return launch_variant<Ops3M>(d, variant, false, s);
-  return launch_gemm_c64_4m(d, variant, s);
+  if (three_m(form, prec)) return launch_split_3m(d, variant, s);
+  return launch_gemm_4m(d, variant, prec, s);
 }
 
 }  // namespace tnc

@@ -1,7 +1,8 @@
-// complex64 GEMM in the 4M form on the bf16 matrix pipe, at float32
-// precision:  C[b,i,j] = sum_l A[b,i,l] B[b,j,l].
+// Complex GEMM in the 4M form on the bf16 matrix pipe,
+// C[b,i,j] = sum_l A[b,i,l] B[b,j,l]:  complex64 at float32 precision (three
+// bf16 parts an operand), and split precision (two).
 //
-// A float32 has 24 significant bits, a bf16 eight, so x = hi + mid + lo with
+// complex64.  A float32 has 24 significant bits, a bf16 eight, so x = hi + mid + lo with
 // hi = rne(x), mid = rne(x - hi), lo = x - hi - mid, every difference and lo
 // itself exact: the operands keep all their bits.  Of the nine products of
 // two such sums six are formed (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi;
@@ -34,6 +35,18 @@
 // 2^-102: bf16 has no bits there) is noticed while the operands are staged,
 // infinities, NaNs and values that round to a bf16 infinity make the tile's
 // own sums non-finite, which is looked at once at the end.
+//
+// complex64 in the 3M form runs here as well: 16 x 1024 x 512 x 768 312 us
+// on the FP32 pipe with three products, 243 here, at 0.3 of the error.
+//
+// Split precision (hi and lo, three products hi lo, lo hi, hi hi added to one
+// accumulator, in waves of one column block the first two to a second one)
+// is the same tile with a part less and no FP32 pass: what the operands lose
+// is the format's own.  Bound by power too, 1275 executed bf16 TFLOP/s: 64 x
+// 1024 x 256 x 1024 0.390 -> 0.369 ms against tiles whose staging the
+// compiler dealt out, 2048 x 512 x 512 x 512 6.35 -> 5.95, 6 x 1000 x 500 x
+// 776 82.5 -> 70.9 us; shapes for few tiles as for complex64 (4 x 256 x 4096
+// x 1024 as a planned pair 219 -> 150 us).
 //
 // 4M form as one real GEMM of m x 2n x 2k: a complex row of A read as 2k
 // floats, times (br, -bi, ...) for Re C and (bi, br, ...) for Im C; both real
@@ -132,19 +145,31 @@ __device__ __forceinline__ f16v mm(const s8v& a, const s8v& b, const f16v& c) {
 // The six products: parts of A and of B, hi hi last; each shares an operand
 // with the one before.
 constexpr int kPartA[6] = {0, 0, 1, 1, 2, 0}, kPartB[6] = {2, 1, 1, 0, 0, 0};
+// Split precision's three: a_hi b_lo, a_lo b_hi, a_hi b_hi.
+constexpr int kSplitA[3] = {0, 1, 0}, kSplitB[3] = {1, 0, 0};
 
-template <int WM, int WN, int PW>
+// PARTS = 3: complex64, 2: split precision.
+template <int PARTS, int WM, int WN, int PW>
 struct XTile {
+  static constexpr bool EXACT = PARTS == 3;
   static constexpr int BM = 64 * WM, BNC = 32 * WN * PW, NT = 64 * WM * WN;
   static constexpr int NJ = 2 * PW;                      // 32-column blocks of the real view per wave
   static constexpr int PA = BM * 32, PB = 2 * BNC * 32;  // bytes of one part's plane: 16 bf16 per row
-  static constexpr int STAGE = 3 * (PA + PB);
-  static constexpr size_t kLds = 2 * STAGE;
+  static constexpr int STAGE = PARTS * (PA + PB);
+  // LDS holds BUFS stages and is staged AHEAD of the products, with a barrier
+  // every AHEAD stages: two parts make half the MFMAs of three, so their
+  // stages go in pairs.
+  static constexpr int BUFS = EXACT ? 2 : 4, AHEAD = BUFS / 2;
+  static constexpr size_t kLds = BUFS * STAGE;
+  static constexpr int PRODUCTS = EXACT ? 6 : 3;
   static constexpr int AL = BM * 4 / NT, BL = BNC * 4 / NT;  // 16-byte loads per thread and stage
   static_assert(AL >= 1 && AL * NT == BM * 4 && BL >= 1 && BL * NT == BNC * 4, "staging must tile evenly");
 
   f16v acc[2][NJ];
-  f16v t[2];  // sums of one stage: of the block at hand and of the one before
+  // three parts: sums of one stage, of the block at hand and of the one
+  // before; two parts on narrow waves: the cross products' sums
+  static constexpr bool CROSS = !EXACT && PW == 1;
+  f16v t[2][CROSS ? NJ : 1];
   f4 ra[AL], rb[BL];
   const float2 *pa[AL], *pb[BL];
   uint32_t tiny;
@@ -171,7 +196,10 @@ struct XTile {
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    t[0] = t[1] = f16v{};
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < (CROSS ? NJ : 1); ++j) t[i][j] = f16v{};
     tiny = 0xFFFFFFFFu;
   }
 
@@ -194,17 +222,16 @@ struct XTile {
     p += XK;
     return v;
   }
-  // LDS rows are 32 bytes, their two 16-byte halves swapped every 8 rows
-  // (half ^ ((row >> 3) & 1)): the fragment reads of 16 lanes (16 rows, one
-  // half) and the 8-byte stores of 32 lanes (8 rows) touch every bank once.
-  // Within 16 rows of B' the even rows come first (row r at ((r & 1) << 3) |
-  // (r >> 1 & 7)), so that the rows that one store instruction writes are
-  // neighbours.
-  // Staging of a stage, in units of one 16-byte load (the first AL of A,
-  // the others of B) and eight pieces each, so that it can be dealt out
-  // between the MFMAs of the stage before.
-  static constexpr int U = AL + BL, PIECES = 8;
-  uint32_t w[2][3];  // the unit's parts: of its first and second complex value
+  // Staging of a stage, in units of one 16-byte load (the first AL of A, the
+  // others of B) and PIECES pieces each, so that it can be dealt out between
+  // MFMAs.  LDS rows are 32 bytes, their two 16-byte halves swapped every 8
+  // rows (half ^ ((row >> 3) & 1)): the fragment reads of 16 lanes (16 rows,
+  // one half) and the 8-byte stores of 32 lanes (8 rows) touch every bank
+  // once.  Within 16 rows of B' the even rows come first (row r at ((r & 1) <<
+  // 3) | (r >> 1 & 7)), so that the rows that one store instruction writes
+  // are neighbours.
+  static constexpr int U = AL + BL, PIECES = 2 * PARTS + 2;
+  uint32_t w[2][PARTS];  // the unit's parts: of its first and second complex value
 
   template <int u>
   __device__ __forceinline__ f4& staged() {
@@ -217,36 +244,34 @@ struct XTile {
   __device__ __forceinline__ void piece(char* lds, int tid) {
     const int r = tid >> 2, c = tid & 3;
     f4& v = staged<u>();
-    if constexpr (q < 6) {
-      constexpr int e = q / 3, part = q % 3;
+    if constexpr (q < 2 * PARTS) {
+      constexpr int e = q / PARTS, part = q % PARTS;
       float x = v[2 * e], y = v[2 * e + 1];
-      if constexpr (part < 2) {
+      if constexpr (part < 2) {  // (what the second of two parts leaves is not read)
         w[e][part] = take_part(x, y);
         v[2 * e] = x;
         v[2 * e + 1] = y;
       } else {
-        w[e][2] = last_part(x, y, tiny);
+        w[e][part] = last_part(x, y, tiny);
       }
-      return;
-    }
-    if constexpr (u < AL) {
-      if (q == 7) return;
+    } else if constexpr (u < AL) {
+      if (q % 2 == 1) return;
       char* p = lds + r * 32 + ((8 * c) ^ (((r >> 3) & 1) << 4)) + u * (NT / 4) * 32;
 #pragma unroll
-      for (int t = 0; t < 3; ++t) *reinterpret_cast<uint2*>(p + t * PA) = make_uint2(w[0][t], w[1][t]);
-      return;
-    }
-    char* p = lds + 3 * PA + (((2 * r) & ~15) | (r & 7)) * 32 + (u - AL) * (NT / 4) * 64;
-    if (q == 6) {
-      constexpr uint32_t NEG_IM = 0x80000000u;
-#pragma unroll
-      for (int t = 0; t < 3; ++t)
-        *reinterpret_cast<uint2*>(p + t * PB + 8 * c) = make_uint2(w[0][t] ^ NEG_IM, w[1][t] ^ NEG_IM);
+      for (int t = 0; t < PARTS; ++t) *reinterpret_cast<uint2*>(p + t * PA) = make_uint2(w[0][t], w[1][t]);
     } else {
-      auto swap = [](uint32_t x) { return (x >> 16) | (x << 16); };
+      char* p = lds + PARTS * PA + (((2 * r) & ~15) | (r & 7)) * 32 + (u - AL) * (NT / 4) * 64;
+      if constexpr (q % 2 == 0) {
+        constexpr uint32_t NEG_IM = 0x80000000u;
 #pragma unroll
-      for (int t = 0; t < 3; ++t)
-        *reinterpret_cast<uint2*>(p + t * PB + 256 + ((8 * c) ^ 16)) = make_uint2(swap(w[0][t]), swap(w[1][t]));
+        for (int t = 0; t < PARTS; ++t)
+          *reinterpret_cast<uint2*>(p + t * PB + 8 * c) = make_uint2(w[0][t] ^ NEG_IM, w[1][t] ^ NEG_IM);
+      } else {
+        auto swap = [](uint32_t x) { return (x >> 16) | (x << 16); };
+#pragma unroll
+        for (int t = 0; t < PARTS; ++t)
+          *reinterpret_cast<uint2*>(p + t * PB + 256 + ((8 * c) ^ 16)) = make_uint2(swap(w[0][t]), swap(w[1][t]));
+      }
     }
   }
   template <bool CHECK, int u>
@@ -268,45 +293,49 @@ struct XTile {
   }
 
   // One stage: the products of `cur`; with NEXT the staged registers are
-  // split into `nxt` and loaded again (whole stages).  Each 32 x 32 block's
-  // six products of the stage are summed from zero and then added to its
-  // accumulator by the VALU.
+  // split into `nxt` and loaded again (whole stages).  Three parts: each 32 x
+  // 32 block's six products of the stage are summed from zero and then added
+  // to its accumulator by the VALU.
   template <bool NEXT>
   __device__ __forceinline__ void step(const char* cur, char* nxt, int tid, int wm, int wn, int lane) {
     const int h = lane >> 5, r = lane & 31;
     const char* a = cur + (wm * 64 + r) * 32 + ((h ^ ((r >> 3) & 1)) << 4);
-    const char* b = cur + 3 * PA + (wn * 64 * PW + ((r & 16) | ((r & 1) << 3) | ((r >> 1) & 7))) * 32 +
+    const char* b = cur + PARTS * PA + (wn * 64 * PW + ((r & 16) | ((r & 1) << 3) | ((r >> 1) & 7))) * 32 +
                     ((h ^ (r & 1)) << 4);
-    constexpr int SLOTS = 12 * NJ, Q = U * PIECES;
-    s8v fa[2][3], fb[2][3];
+    constexpr int SLOTS = 2 * PRODUCTS * NJ, Q = U * PIECES;
+    s8v fa[2][PARTS], fb[2][PARTS];
     auto read_a = [&](int i, int q) { fa[i][q] = *reinterpret_cast<const s8v*>(a + q * PA + i * 1024); };
     auto read_b = [&](int j, int q) { fb[j & 1][q] = *reinterpret_cast<const s8v*>(b + q * PB + j * 1024); };
-    read_a(0, 0);
-    read_b(0, 2);
-    read_b(0, 1);
-    read_a(0, 1);
-    read_b(0, 0);
-    read_a(0, 2);
+    each<PARTS>([&](auto q) {
+      read_a(0, q);
+      read_b(0, PARTS - 1 - q);
+    });
     __builtin_amdgcn_sched_barrier(0);
     each<SLOTS>([&](auto slot) {
-      constexpr int s = slot, c = s / 6, k6 = s % 6, i = c & 1, j = c >> 1;
-      if constexpr (k6 == 0) t[i] = f16v{};
-      t[i] = mm(fa[i][kPartA[k6]], fb[j & 1][kPartB[k6]], t[i]);
-      if constexpr (c == 0 && k6 < 3) read_a(1, k6);
-      if constexpr (i == 1 && j + 1 < NJ) {  // the next block's, once this one's part is done with
-        if constexpr (k6 == 0) read_b(j + 1, 0);
-        if constexpr (k6 == 1) read_b(j + 1, 2);
-        if constexpr (k6 == 3) read_b(j + 1, 1);
+      constexpr int s = slot, c = s / PRODUCTS, kp = s % PRODUCTS, i = c & 1, j = c >> 1;
+      if constexpr (EXACT) {
+        f16v& sum = t[i][0];
+        if constexpr (kp == 0) sum = f16v{};
+        sum = mm(fa[i][kPartA[kp]], fb[j & 1][kPartB[kp]], sum);
+      } else {
+        f16v& sum = CROSS && kp < 2 ? t[i][CROSS ? j : 0] : acc[i][j];
+        sum = mm(fa[i][kSplitA[kp]], fb[j & 1][kSplitB[kp]], sum);
       }
-      if constexpr (k6 >= 2) {  // four of the sums of the block before
+      if constexpr (c == 0 && kp < PARTS) read_a(1, kp);
+      if constexpr (i == 1 && j + 1 < NJ) {  // the next block's, once this one's part is done with
+        if constexpr (kp == 0) read_b(j + 1, 0);
+        if constexpr (kp == 1) read_b(j + 1, PARTS - 1);
+        if constexpr (EXACT && kp == 3) read_b(j + 1, 1);
+      }
+      if constexpr (EXACT && kp >= 2) {  // four of the sums of the block before
         f16v& d = acc[i ^ 1][c == 0 ? NJ - 1 : (c - 1) >> 1];
-        each<4>([&](auto v) { d[4 * (k6 - 2) + v] += t[i ^ 1][4 * (k6 - 2) + v]; });
+        each<4>([&](auto v) { d[4 * (kp - 2) + v] += t[i ^ 1][0][4 * (kp - 2) + v]; });
       }
       if constexpr (NEXT)
         each<(s + 1) * Q / SLOTS - s * Q / SLOTS>([&](auto n) {
           constexpr int q = s * Q / SLOTS + n;
           piece<q / PIECES, q % PIECES>(nxt, tid);
-          if constexpr (q % PIECES == 7) load_unit<false, q / PIECES>(0, tid);
+          if constexpr (q % PIECES == PIECES - 1) load_unit<false, q / PIECES>(0, tid);
         });
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -327,26 +356,28 @@ struct XTile {
     const float2* B = d.B + uniform(ob);
     init(A, B, d, tc, tid);
     const int64_t k = d.k, nk = (k + XK - 1) / XK, full = k / XK;
-    load(k, tid);
-    stage(lds, tid);
-    if (nk > 1) load(k - XK, tid);
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q)
+      if (q < nk) {
+        load(k - q * XK, tid);
+        stage(lds + q * STAGE, tid);
+      }
+    if (AHEAD < nk) load(k - AHEAD * XK, tid);
     __syncthreads();
+    auto buf = [&](int64_t st) { return lds + (st & (BUFS - 1)) * STAGE; };
     int64_t kt = 0;
-    for (; kt + 2 < full; ++kt) {
-      char* cur = lds + (kt & 1) * STAGE;
-      char* nxt = lds + ((kt & 1) ^ 1) * STAGE;
-      step<true>(cur, nxt, tid, wm, wn, lane);
+    for (; kt + 2 * AHEAD < full; kt += AHEAD) {
+      each<AHEAD>([&](auto q) { step<true>(buf(kt + q), buf(kt + q + AHEAD), tid, wm, wn, lane); });
       __syncthreads();
     }
     for (; kt < nk; ++kt) {
-      char* cur = lds + (kt & 1) * STAGE;
-      char* nxt = lds + ((kt & 1) ^ 1) * STAGE;
-      if (kt + 1 < nk) stage(nxt, tid);
-      if (kt + 2 < nk) load(k - (kt + 2) * XK, tid);
-      step<false>(cur, nxt, tid, wm, wn, lane);
+      if (kt + AHEAD < nk) stage(buf(kt + AHEAD), tid);
+      if (kt + AHEAD + 1 < nk) load(k - (kt + AHEAD + 1) * XK, tid);
+      step<false>(buf(kt), nullptr, tid, wm, wn, lane);
       __syncthreads();
     }
-    acc[1][NJ - 1] += t[1];
+    if constexpr (!EXACT) return true;
+    acc[1][NJ - 1] += t[1][0];
     float s = 0.f;  // NaN if any sum is not finite
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -357,40 +388,30 @@ struct XTile {
     return !__syncthreads_or(tiny < 0x00FFFFFFu || !(s == 0.f));
   }
 
+  __device__ __forceinline__ float value(int i, int j, int v) const {
+    if constexpr (CROSS)
+      return acc[i][j][v] + t[i][j][v];
+    else
+      return acc[i][j][v];
+  }
+
   __device__ __forceinline__ void store(const GemmDesc& d, bool perm, const TileCoord& tc, int wm, int wn,
                                         int lane) const {
-    if (perm) {
-      store_perm_pairs<PW>(d, tc, wm, wn, lane, [&](int i, int j, int v) { return acc[i][j][v]; });
-      return;
-    }
-    const int h = lane >> 5, l32 = lane & 31;
-    float* C = reinterpret_cast<float*>(d.C + tc.b * d.m * d.n) + (l32 & 1);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int64_t col = (tc.col0 * 2 + wn * 64 * PW + j * 32 + l32) >> 1;
-        if (col >= d.n) continue;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t row = tc.row0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-          if (row < d.m) C[2 * (row * d.n + col)] = acc[i][j][v];
-        }
-      }
+    store_4m<PW>(d, perm, tc, wm, wn, lane, [&](int i, int j, int v) { return value(i, j, v); });
   }
 };
 
-template <int WM, int WN, int PW, bool PERM>
-__global__ __launch_bounds__(64 * WM * WN, 2) void cgemm_c64(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
+template <int PARTS, int WM, int WN, int PW, bool PERM>
+__global__ __launch_bounds__(64 * WM * WN, 2) void cgemm_4m(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
                                                             int64_t total) {
-  using T = XTile<WM, WN, PW>;
+  using T = XTile<PARTS, WM, WN, PW>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const TileCoord tc = uniform(map_tile_shared<T::BM, T::BNC>(tiles_m, tiles_n, total));
   T t;
-  if (t.run(d, tc, lds, tid, wm, wn, lane))
+  if (t.run(d, tc, lds, tid, wm, wn, lane))  // (always, with two parts)
     t.store(d, PERM, tc, wm, wn, lane);
   else
     T::fp32_tile(d, tc, wm, wn, lane);
@@ -399,10 +420,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void cgemm_c64(GemmDesc d, int64_t
 // Persistent grouped form: see GroupedEntry.  Tiles are dealt to the 8 XCDs
 // in contiguous ranges (tiles of one entry stay on few XCDs, whose L2 they
 // share) and each workgroup of an XCD takes every nb-th tile of its range.
-template <int WM, int WN, int PW>
-__global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void cgemm_c64_grouped(
+template <int PARTS, int WM, int WN, int PW>
+__global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void cgemm_4m_grouped(
     const GroupedEntry* __restrict__ tab, int n, int64_t total) {
-  using T = XTile<WM, WN, PW>;
+  using T = XTile<PARTS, WM, WN, PW>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int64_t per = (total + 7) >> 3;  // tiles per XCD
   const int64_t xcd = blockIdx.x & 7, nb = gridDim.x >> 3;
@@ -439,7 +460,7 @@ __global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void cgemm_c64_
 // so it loses where tiles are many.  256 x 256 x 256 26.6 -> 7.0 us, 1024 x
 // 128 x 128 16.5 -> 5.5, 16 x 256 x 256 25.8 -> 6.7 (launches back to back, 4.6
 // of it the launch).
-template <int W, int BI, int BJ>
+template <int PARTS, int W, int BI, int BJ>
 struct XDirect {
   static constexpr int BM = 32 * BI, BNC = 16 * BJ, NT = 64 * W;
   static constexpr int REGS = 16 * BI * BJ;                  // sums per lane
@@ -465,18 +486,18 @@ struct XDirect {
     }
   }
 
-  __device__ __forceinline__ static void split(const f4 (&v)[2], s8v (&part)[3], uint32_t& tiny) {
+  __device__ __forceinline__ static void split(const f4 (&v)[2], s8v (&part)[PARTS], uint32_t& tiny) {
     uint32_t w[3][4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float a = v[e >> 1][2 * (e & 1)], b = v[e >> 1][2 * (e & 1) + 1];
       w[0][e] = take_part(a, b);
       w[1][e] = take_part(a, b);
-      w[2][e] = last_part(a, b, tiny);
+      if constexpr (PARTS == 3) w[2][e] = last_part(a, b, tiny);
     }
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int q = 0; q < 3; ++q) part[q] = __builtin_bit_cast(s8v, (u4){w[q][0], w[q][1], w[q][2], w[q][3]});
+    for (int q = 0; q < PARTS; ++q) part[q] = __builtin_bit_cast(s8v, (u4){w[q][0], w[q][1], w[q][2], w[q][3]});
   }
 
   template <bool CHECK>
@@ -517,7 +538,7 @@ struct XDirect {
     const int64_t nk = (k + XK - 1) / XK;
     if (wave < nk) load_stage(wave);
     for (int64_t st = wave; st < nk; st += W) {
-      s8v fa[BI][3], fb[BJ][3];
+      s8v fa[BI][PARTS], fb[BJ][PARTS];
 #pragma unroll
       for (int i = 0; i < BI; ++i) split(x[i], fa[i], tiny);
 #pragma unroll
@@ -535,11 +556,13 @@ struct XDirect {
       if (st + W < nk) load_stage(st + W);
       f16v c[BI][BJ] = {};
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
+      for (int q = 0; q < (PARTS == 3 ? 6 : 3); ++q)
 #pragma unroll
         for (int j = 0; j < BJ; ++j)
 #pragma unroll
-          for (int i = 0; i < BI; ++i) c[i][j] = mm(fa[i][kPartA[q]], fb[j][kPartB[q]], c[i][j]);
+          for (int i = 0; i < BI; ++i)
+            c[i][j] = PARTS == 3 ? mm(fa[i][kPartA[q]], fb[j][kPartB[q]], c[i][j])
+                                 : mm(fa[i][kSplitA[q]], fb[j][kSplitB[q]], c[i][j]);
 #pragma unroll
       for (int i = 0; i < BI; ++i)
 #pragma unroll
@@ -557,7 +580,7 @@ struct XDirect {
           mine[(16 * (i * BJ + j) + v) * 64] = acc[i][j][v];
         }
     // (the vote is a barrier: every wave's sums are in LDS behind it)
-    if (__syncthreads_or(tiny < 0x00FFFFFFu || !(s == 0.f))) {
+    if (__syncthreads_or(PARTS == 3 && (tiny < 0x00FFFFFFu || !(s == 0.f)))) {
       if (wave < BI * BJ) fp32_block(d, tc.b, tc.row0 + 32 * (wave / BJ), tc.col0 + 16 * (wave % BJ), lane);
       return;
     }
@@ -584,10 +607,10 @@ struct XDirect {
   }
 };
 
-template <int W, int BI, int BJ>
-__global__ __launch_bounds__(64 * W) void cgemm_c64_direct(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
+template <int PARTS, int W, int BI, int BJ>
+__global__ __launch_bounds__(64 * W) void cgemm_4m_direct(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
                                                            int64_t total) {
-  using T = XDirect<W, BI, BJ>;
+  using T = XDirect<PARTS, W, BI, BJ>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   const TileCoord tc = uniform(map_tile_shared<T::BM, T::BNC>(tiles_m, tiles_n, total));
@@ -596,9 +619,9 @@ __global__ __launch_bounds__(64 * W) void cgemm_c64_direct(GemmDesc d, int64_t t
 }
 
 // one workgroup per tile of the launch's entries
-template <int W, int BI, int BJ>
-__global__ __launch_bounds__(64 * W) void cgemm_c64_direct_grouped(const GroupedEntry* __restrict__ tab, int n) {
-  using T = XDirect<W, BI, BJ>;
+template <int PARTS, int W, int BI, int BJ>
+__global__ __launch_bounds__(64 * W) void cgemm_4m_direct_grouped(const GroupedEntry* __restrict__ tab, int n) {
+  using T = XDirect<PARTS, W, BI, BJ>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   int e = 0;
@@ -623,100 +646,104 @@ hipError_t allow_lds(F* kernel, size_t lds, std::atomic<uint64_t>& done) {
   return e;
 }
 
-template <int WM, int WN, int PW, bool PERM>
+template <int PARTS, int WM, int WN, int PW, bool PERM>
 hipError_t ready_one() {
   static std::atomic<uint64_t> done{0};
-  return allow_lds(cgemm_c64<WM, WN, PW, PERM>, XTile<WM, WN, PW>::kLds, done);
+  return allow_lds(cgemm_4m<PARTS, WM, WN, PW, PERM>, XTile<PARTS, WM, WN, PW>::kLds, done);
 }
-template <int WM, int WN, int PW>
+template <int PARTS, int WM, int WN, int PW>
 hipError_t ready_grouped() {
   static std::atomic<uint64_t> done{0};
-  return allow_lds(cgemm_c64_grouped<WM, WN, PW>, XTile<WM, WN, PW>::kLds, done);
+  return allow_lds(cgemm_4m_grouped<PARTS, WM, WN, PW>, XTile<PARTS, WM, WN, PW>::kLds, done);
 }
 
-template <int WM, int WN, int PW, bool PERM>
+template <int PARTS, int WM, int WN, int PW, bool PERM>
 hipError_t launch_one(const GemmDesc& d, hipStream_t s) {
-  using T = XTile<WM, WN, PW>;
+  using T = XTile<PARTS, WM, WN, PW>;
   const int64_t tiles_m = (d.m + T::BM - 1) / T::BM;
   const int64_t tiles_n = (d.n + T::BNC - 1) / T::BNC;
   const int64_t total = tiles_m * tiles_n * d.h;
   // one workgroup per tile; the grid's work-items must fit 32 bits
   if (total * T::NT > 0xFFFFFFFFLL) return hipErrorInvalidValue;
-  const hipError_t e = ready_one<WM, WN, PW, PERM>();
+  const hipError_t e = ready_one<PARTS, WM, WN, PW, PERM>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((cgemm_c64<WM, WN, PW, PERM>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s, d,
+  hipLaunchKernelGGL((cgemm_4m<PARTS, WM, WN, PW, PERM>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s, d,
                      tiles_m, tiles_n, total);
   return hipGetLastError();
 }
-template <int WM, int WN, int PW>
+template <int PARTS, int WM, int WN, int PW>
 hipError_t launch_shape(const GemmDesc& d, hipStream_t s) {
-  return d.offM ? launch_one<WM, WN, PW, true>(d, s) : launch_one<WM, WN, PW, false>(d, s);
+  return d.offM ? launch_one<PARTS, WM, WN, PW, true>(d, s) : launch_one<PARTS, WM, WN, PW, false>(d, s);
 }
 
 // Persistent grid: a multiple of 8 (one range of tiles per XCD), never more
 // than the tiles; at most 512 workgroups (two per compute unit), or 2048
 // waves for the shapes of fewer than four waves.
-template <int WM, int WN, int PW>
+template <int PARTS, int WM, int WN, int PW>
 hipError_t launch_grouped_shape(const GroupedEntry* tab, int n, int64_t total, hipStream_t s) {
-  using T = XTile<WM, WN, PW>;
-  const hipError_t e = ready_grouped<WM, WN, PW>();
+  using T = XTile<PARTS, WM, WN, PW>;
+  const hipError_t e = ready_grouped<PARTS, WM, WN, PW>();
   if (e != hipSuccess) return e;
   constexpr int64_t cap = WM * WN < 4 ? 2048 / (WM * WN) : 512;
   int64_t grid = (total + 7) / 8 * 8;
   if (grid > cap) grid = cap;
-  hipLaunchKernelGGL((cgemm_c64_grouped<WM, WN, PW>), dim3(static_cast<unsigned>(grid)), dim3(T::NT), T::kLds, s, tab, n,
+  hipLaunchKernelGGL((cgemm_4m_grouped<PARTS, WM, WN, PW>), dim3(static_cast<unsigned>(grid)), dim3(T::NT), T::kLds, s, tab, n,
                      total);
   return hipGetLastError();
 }
 
-template <int W, int BI, int BJ>
+template <int PARTS, int W, int BI, int BJ>
 hipError_t ready_direct() {
   static std::atomic<uint64_t> done{0}, done_grouped{0};
-  const size_t lds = XDirect<W, BI, BJ>::kLds;
-  const hipError_t e = allow_lds(cgemm_c64_direct<W, BI, BJ>, lds, done);
-  return e != hipSuccess ? e : allow_lds(cgemm_c64_direct_grouped<W, BI, BJ>, lds, done_grouped);
+  const size_t lds = XDirect<PARTS, W, BI, BJ>::kLds;
+  const hipError_t e = allow_lds(cgemm_4m_direct<PARTS, W, BI, BJ>, lds, done);
+  return e != hipSuccess ? e : allow_lds(cgemm_4m_direct_grouped<PARTS, W, BI, BJ>, lds, done_grouped);
 }
-template <int W, int BI, int BJ>
+template <int PARTS, int W, int BI, int BJ>
 hipError_t launch_direct(const GemmDesc& d, hipStream_t s) {
-  using T = XDirect<W, BI, BJ>;
+  using T = XDirect<PARTS, W, BI, BJ>;
   const int64_t tiles_m = (d.m + T::BM - 1) / T::BM, tiles_n = (d.n + T::BNC - 1) / T::BNC;
   const int64_t total = tiles_m * tiles_n * d.h;
   if (total * T::NT > 0xFFFFFFFFLL) return hipErrorInvalidValue;
-  const hipError_t e = ready_direct<W, BI, BJ>();
+  const hipError_t e = ready_direct<PARTS, W, BI, BJ>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((cgemm_c64_direct<W, BI, BJ>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s, d,
+  hipLaunchKernelGGL((cgemm_4m_direct<PARTS, W, BI, BJ>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s, d,
                      tiles_m, tiles_n, total);
   return hipGetLastError();
 }
 
-template <int W, int BI, int BJ>
+template <int PARTS, int W, int BI, int BJ>
 hipError_t launch_direct_grouped(const GroupedEntry* tab, int n, int64_t total, hipStream_t s) {
-  using T = XDirect<W, BI, BJ>;
+  using T = XDirect<PARTS, W, BI, BJ>;
   if (total * T::NT > 0xFFFFFFFFLL) return hipErrorInvalidValue;
-  const hipError_t e = ready_direct<W, BI, BJ>();
+  const hipError_t e = ready_direct<PARTS, W, BI, BJ>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((cgemm_c64_direct_grouped<W, BI, BJ>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s,
+  hipLaunchKernelGGL((cgemm_4m_direct_grouped<PARTS, W, BI, BJ>), dim3(static_cast<unsigned>(total)), dim3(T::NT), T::kLds, s,
                      tab, n);
   return hipGetLastError();
 }
 
-template <int WM, int WN, int PW>
+template <int PARTS, int WM, int WN, int PW>
 void prepare_shape() {
-  (void)ready_one<WM, WN, PW, false>();
-  (void)ready_one<WM, WN, PW, true>();
-  (void)ready_grouped<WM, WN, PW>();
+  (void)ready_one<PARTS, WM, WN, PW, false>();
+  (void)ready_one<PARTS, WM, WN, PW, true>();
+  (void)ready_grouped<PARTS, WM, WN, PW>();
 }
 
-}  // namespace
 
-void prepare_gemm_c64() {
-  prepare_shape<4, 1, 2>();
-  prepare_shape<2, 2, 2>();
-  prepare_shape<4, 2, 2>();
-  prepare_shape<2, 4, 1>();
-  (void)ready_direct<8, 1, 1>();
-  (void)ready_direct<8, 1, 2>();
-  (void)ready_direct<8, 2, 2>();
+template <int PARTS>
+void prepare_tiles() {
+  prepare_shape<PARTS, 2, 2, 1>();
+  prepare_shape<PARTS, 4, 1, 2>();
+  prepare_shape<PARTS, 2, 2, 2>();
+  prepare_shape<PARTS, 4, 2, 2>();
+  prepare_shape<PARTS, 1, 2, 1>();
+  prepare_shape<PARTS, 2, 1, 1>();
+  prepare_shape<PARTS, 1, 1, 1>();
+  prepare_shape<PARTS, 2, 4, 1>();
+  (void)ready_direct<PARTS, 8, 1, 1>();
+  (void)ready_direct<PARTS, 8, 1, 2>();
+  (void)ready_direct<PARTS, 8, 2, 2>();
 }
 
 // The 128 x 128 tile runs as four wide waves (each A fragment feeds four
@@ -724,41 +751,66 @@ void prepare_gemm_c64() {
 // has no more tiles than compute units: a CU then has two waves per SIMD
 // from its one workgroup instead of one (6 x 1000 x 500 x 777, 192 tiles:
 // 0.141 -> 0.125 ms; 8192 x 8192 x 4096, 4096 tiles: 10.3 -> 9.8 ms the
-// other way).  An element's sums do not depend on which of them ran.
-hipError_t launch_gemm_c64_4m(const GemmDesc& d, int variant, hipStream_t s) {
+// other way).  In complex64 an element's sums do not depend on which of them
+// ran; in split precision they do (CROSS), and it always runs the narrow.
+template <int PARTS>
+bool narrow_128(int64_t tiles) {
+  return PARTS == 2 || tiles <= 256;
+}
+
+template <int PARTS>
+hipError_t launch_tiles(const GemmDesc& d, int variant, hipStream_t s) {
   switch (variant) {
-    case 0: return launch_shape<2, 2, 1>(d, s);
-    case 1: return launch_shape<4, 1, 2>(d, s);
+    case 0: return launch_shape<PARTS, 2, 2, 1>(d, s);
+    case 1: return launch_shape<PARTS, 4, 1, 2>(d, s);
     case 2:
-      if (d.h * ((d.m + 127) / 128) * ((d.n + 127) / 128) <= 256) return launch_shape<2, 4, 1>(d, s);
-      return launch_shape<2, 2, 2>(d, s);
-    case 3: return launch_shape<4, 2, 2>(d, s);
-    case 4: return launch_shape<1, 2, 1>(d, s);
-    case 5: return launch_shape<2, 1, 1>(d, s);
-    case 6: return launch_shape<1, 1, 1>(d, s);
-    case kDirect32x16: return launch_direct<8, 1, 1>(d, s);
-    case kDirect32x32: return launch_direct<8, 1, 2>(d, s);
-    case kDirect64x32: return launch_direct<8, 2, 2>(d, s);
+      if (narrow_128<PARTS>(d.h * ((d.m + 127) / 128) * ((d.n + 127) / 128))) return launch_shape<PARTS, 2, 4, 1>(d, s);
+      return launch_shape<PARTS, 2, 2, 2>(d, s);
+    case 3: return launch_shape<PARTS, 4, 2, 2>(d, s);
+    case 4: return launch_shape<PARTS, 1, 2, 1>(d, s);
+    case 5: return launch_shape<PARTS, 2, 1, 1>(d, s);
+    case 6: return launch_shape<PARTS, 1, 1, 1>(d, s);
+    case kDirect32x16: return launch_direct<PARTS, 8, 1, 1>(d, s);
+    case kDirect32x32: return launch_direct<PARTS, 8, 1, 2>(d, s);
+    case kDirect64x32: return launch_direct<PARTS, 8, 2, 2>(d, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_gemm_c64_4m_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, hipStream_t s) {
+template <int PARTS>
+hipError_t launch_tiles_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, hipStream_t s) {
   switch (variant) {
-    case 0: return launch_grouped_shape<2, 2, 1>(tab, n, total, s);
-    case 1: return launch_grouped_shape<4, 1, 2>(tab, n, total, s);
+    case 0: return launch_grouped_shape<PARTS, 2, 2, 1>(tab, n, total, s);
+    case 1: return launch_grouped_shape<PARTS, 4, 1, 2>(tab, n, total, s);
     case 2:
-      if (total <= 256) return launch_grouped_shape<2, 4, 1>(tab, n, total, s);
-      return launch_grouped_shape<2, 2, 2>(tab, n, total, s);
-    case 3: return launch_grouped_shape<4, 2, 2>(tab, n, total, s);
-    case 4: return launch_grouped_shape<1, 2, 1>(tab, n, total, s);
-    case 5: return launch_grouped_shape<2, 1, 1>(tab, n, total, s);
-    case 6: return launch_grouped_shape<1, 1, 1>(tab, n, total, s);
-    case kDirect32x16: return launch_direct_grouped<8, 1, 1>(tab, n, total, s);
-    case kDirect32x32: return launch_direct_grouped<8, 1, 2>(tab, n, total, s);
-    case kDirect64x32: return launch_direct_grouped<8, 2, 2>(tab, n, total, s);
+      if (narrow_128<PARTS>(total)) return launch_grouped_shape<PARTS, 2, 4, 1>(tab, n, total, s);
+      return launch_grouped_shape<PARTS, 2, 2, 2>(tab, n, total, s);
+    case 3: return launch_grouped_shape<PARTS, 4, 2, 2>(tab, n, total, s);
+    case 4: return launch_grouped_shape<PARTS, 1, 2, 1>(tab, n, total, s);
+    case 5: return launch_grouped_shape<PARTS, 2, 1, 1>(tab, n, total, s);
+    case 6: return launch_grouped_shape<PARTS, 1, 1, 1>(tab, n, total, s);
+    case kDirect32x16: return launch_direct_grouped<PARTS, 8, 1, 1>(tab, n, total, s);
+    case kDirect32x32: return launch_direct_grouped<PARTS, 8, 1, 2>(tab, n, total, s);
+    case kDirect64x32: return launch_direct_grouped<PARTS, 8, 2, 2>(tab, n, total, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+}  // namespace
+
+void prepare_gemm_4m() {
+  prepare_tiles<3>();
+  prepare_tiles<2>();
+}
+
+hipError_t launch_gemm_4m(const GemmDesc& d, int variant, Prec prec, hipStream_t s) {
+  return prec == Prec::BF16X3 ? launch_tiles<2>(d, variant, s) : launch_tiles<3>(d, variant, s);
+}
+
+hipError_t launch_gemm_4m_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, Prec prec,
+                                  hipStream_t s) {
+  return prec == Prec::BF16X3 ? launch_tiles_grouped<2>(tab, n, total, variant, s)
+                              : launch_tiles_grouped<3>(tab, n, total, variant, s);
 }
 
 }  // namespace tnc

@@ -187,7 +187,7 @@ struct GatherDesc {
 // MFMA tile variants: variant v uses workgroups of WM x WN wave64, each
 // wave owning 64 x 32 complex of C (gemm_variant_tile gives the block tile).
 constexpr int kGemmVariants = 7;
-// Beside them the complex64 4M form has three shapes for launches with few
+// Beside them the 4M kernels have three shapes for launches with few
 // tiles, whose waves share out K instead of the tile (named by their complex
 // tile; chosen by default_variant and the autotuner, never forced).
 constexpr int kDirect32x16 = 7, kDirect32x32 = 8, kDirect64x32 = 9, kAllVariants = 10;
@@ -201,10 +201,9 @@ hipError_t launch_gemm(const GemmDesc& d, GemmKernel kind, int variant, Form for
 // one persistent launch whose workgroups loop over the tiles of all of them.
 // Every tile is computed exactly as the single-GEMM kernel of that variant
 // computes it, so each result is bitwise the same as a launch of its own.
-// Entries need even k and row stride (16-byte operand loads).  Grouped
-// forms exist only where the persistent tile loop fits the registers
-// without spilling (grouped_variant_ok: every 4M variant, 3M but 3, split
-// precision's 0 and 4-6); other launches fail with hipErrorInvalidValue.
+// Entries need even k and row stride.  Every shape of the 4M kernels has a
+// grouped form, of split precision's 3M form every one but 3
+// (grouped_variant_ok); other launches fail with hipErrorInvalidValue.
 struct GroupedEntry {
   GemmDesc d;
   int64_t tiles_m, tiles_n;   // tile grid of one batch entry
@@ -218,10 +217,10 @@ int64_t grouped_layout(GroupedEntry* e, int n, int variant);
 bool grouped_variant_ok(Form form, Prec prec, int variant);
 hipError_t launch_gemm_grouped(const GroupedEntry* dev, int n, int64_t total, int variant, Form form, Prec prec,
                                hipStream_t s);
-// The complex64 4M form (called by launch_gemm and its siblings).
-hipError_t launch_gemm_c64_4m(const GemmDesc& d, int variant, hipStream_t s);
-hipError_t launch_gemm_c64_4m_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, hipStream_t s);
-void prepare_gemm_c64();
+// The 4M form (called by launch_gemm and its siblings).
+hipError_t launch_gemm_4m(const GemmDesc& d, int variant, Prec prec, hipStream_t s);
+hipError_t launch_gemm_4m_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, Prec prec, hipStream_t s);
+void prepare_gemm_4m();
 hipError_t launch_gemm_valu(const GemmDesc& d, GemmKernel kind, Prec prec, hipStream_t s);
 // Split-bf16x3 on operands split once into bf16 planes (large steps of one
 // batch entry, h == 1, no operand tables): the launch splits A and B into
