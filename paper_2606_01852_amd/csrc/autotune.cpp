@@ -243,6 +243,7 @@ void assign_variants(const Plan& plan, ChunkPlan& cp, bool tune) {
     else
       sp.variant = default_variant(plan.prec, plan.form, d.h, d.m, d.n);
   }
+  summarize_steps(cp);
 }
 
 }  // namespace tnc

@@ -210,6 +210,15 @@ struct LevelPlan {
   int64_t off_gather = -1, off_gather_prefix = -1, gather_total = 0;
 };
 
+// What a run contributes to a lockstep job: its bytes of the job's tables,
+// the number of sub-tables (each aligned to 256 bytes), and the launches
+// the run issues on its own (eager; the measure of how launch-bound it is).
+struct LockstepInfo {
+  size_t bytes_per_run = 0;
+  int64_t parts = 0;
+  int64_t launches = 0;
+};
+
 struct ChunkPlan {
   int j = 0;                       // number of trailing sliced labels batched
   bool grouped = false;            // execute level by level
@@ -238,6 +247,11 @@ struct ChunkPlan {
   double flops = 0, bytes = 0, transpose_bytes = 0;
   int64_t max_tensor = 0;
   int n_permutes = 0, n_perm_stores = 0;
+  // what a submission needs of the steps, collected where their variants are
+  // assigned (a walk over the 317 steps of a 20-qubit circuit, cold for every
+  // request's plan, took longer than the rest of its submission)
+  LockstepInfo lockstep;                     // of one such chunk
+  std::string step_key;                      // kind, variant and split of every step
 };
 
 struct StepTimer {
@@ -345,14 +359,7 @@ struct LockstepRun {
   RunArgs a;
 };
 std::string structure_key(Plan& plan, int64_t first, int64_t count);
-// What a run contributes to a lockstep job: its bytes of the job's tables,
-// the number of sub-tables (each aligned to 256 bytes), and the launches
-// the run issues on its own (eager; the measure of how launch-bound it is).
-struct LockstepInfo {
-  size_t bytes_per_run = 0;
-  int64_t parts = 0;
-  int64_t launches = 0;
-};
+void summarize_steps(ChunkPlan& cp);  // fills ChunkPlan::lockstep and step_key
 LockstepInfo lockstep_info(Plan& plan, int64_t first, int64_t count);
 size_t lockstep_table_bytes(const LockstepInfo& t, int n_runs);
 void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_tables, size_t cap,

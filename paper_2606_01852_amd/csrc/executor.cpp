@@ -640,11 +640,12 @@ void run_plan(Plan& plan, const RunArgs& a) {
 // Several runs of plans with one structure (the same path, shapes, chunking
 // and tile variants, see structure_key) over slice ranges with the same
 // chunk sequence, executed together on one stream: chunk by chunk and level
-// by level, every run's leaf preparations and small GEMMs are launched as
-// in a run of its own, and every MFMA step goes out as one grouped launch
-// over the runs' GEMMs of that step.  Each output element is computed by the
-// same tile code in the same order as alone, so every run's result is
-// bitwise its result alone.
+// by level, with one launch over the runs for every level's small GEMMs and
+// leaf gathers, every step that has a launch of its own (and its split-K
+// epilogue) and the final reduction; tiled leaf permutes, separate transposes
+// and steps without a grouped form are launched per run.  Each output
+// element is computed by the same code in the same order as alone, so every
+// run's result is bitwise its result alone.
 
 std::string structure_key(Plan& plan, int64_t first, int64_t count) {
   std::string k;
@@ -669,6 +670,7 @@ std::string structure_key(Plan& plan, int64_t first, int64_t count) {
       for (int l : plan.sliced) put(l);
       plan.key_prefix = k;
     }
+    k.reserve(plan.key_prefix.size() + 16 * plan.pairs.size() + 256);
     k = plan.key_prefix;
   }
   put(plan.prec);
@@ -685,12 +687,7 @@ std::string structure_key(Plan& plan, int64_t first, int64_t count) {
     put(c.first);
     if (seen[c.first]) continue;
     seen[c.first] = 1;
-    const ChunkPlan& cp = plan.chunk(c.first);
-    for (const StepPlan& sp : cp.steps) {
-      put(static_cast<int64_t>(sp.kind));
-      put(sp.variant);
-      put(sp.split);
-    }
+    k += plan.chunk(c.first).step_key;
   }
   return k;
 }
@@ -702,44 +699,59 @@ size_t table_align(size_t x) { return (x + kTableAlign - 1) / kTableAlign * kTab
 
 }  // namespace
 
+void summarize_steps(ChunkPlan& cp) {
+  cp.step_key.clear();
+  auto put = [&](int32_t v) { cp.step_key.append(reinterpret_cast<const char*>(&v), sizeof v); };
+  for (const StepPlan& sp : cp.steps) {
+    put(static_cast<int32_t>(sp.kind));
+    put(sp.variant);
+    put(sp.split);
+  }
+  LockstepInfo t;
+  // launches of this chunk in a run of its own (enqueue_chunk's order)
+  auto step_launches = [&](const StepPlan& sp) { return 1 + (sp.split > 1 || sp.trans ? 1 : 0); };
+  t.launches = 1 + (cp.n_base_slots ? 1 : 0);  // reduction, chunk bases
+  if (cp.steps.empty() && !cp.leaf[0].direct) ++t.launches;
+  if (cp.grouped) {
+    for (const LevelPlan& lv : cp.levels) {
+      t.launches += (lv.group_leaves.empty() ? 0 : 1) + (lv.group_steps.empty() || lv.chained ? 0 : 1);
+      t.launches += static_cast<int64_t>(lv.single_leaves.size());
+      for (int s : lv.single_steps) t.launches += step_launches(cp.steps[s]);
+    }
+  } else {
+    for (const StepPlan& sp : cp.steps) t.launches += static_cast<int64_t>(sp.preps.size()) + step_launches(sp);
+  }
+  auto part = [&](size_t bytes) {
+    t.bytes_per_run += bytes;
+    t.parts += 1;
+  };
+  auto step_parts = [&](const StepPlan& sp) {
+    part(sp.kind == GemmKernel::MFMA ? sizeof(GroupedEntry) : sizeof(GemmDesc));
+    if (sp.split > 1) part(sizeof(SplitkRun));
+  };
+  part(sizeof(ReduceRun));
+  if (cp.grouped) {
+    for (const LevelPlan& lv : cp.levels) {  // per run: one GroupRun per grouped launch
+      if (!lv.group_steps.empty() && !lv.chained) part(sizeof(GroupRun));
+      if (!lv.group_leaves.empty()) part(sizeof(GroupRun));
+      for (int s : lv.single_steps) step_parts(cp.steps[s]);
+    }
+  } else {
+    for (const StepPlan& sp : cp.steps) step_parts(sp);
+  }
+  cp.lockstep = t;
+}
+
 LockstepInfo lockstep_info(Plan& plan, int64_t first, int64_t count) {
   LockstepInfo t;
-  const auto chunks = decompose(plan, first, count);
   std::vector<char> seen(plan.chunks.size(), 0);
-  for (auto& c : chunks) {
-    const ChunkPlan& cp = plan.chunk(c.first);
-    // launches of this chunk in a run of its own (enqueue_chunk's order)
-    auto step_launches = [&](const StepPlan& sp) { return 1 + (sp.split > 1 || sp.trans ? 1 : 0); };
-    int64_t nl = 1 + (cp.n_base_slots ? 1 : 0);  // reduction, chunk bases
-    if (cp.steps.empty() && !cp.leaf[0].direct) ++nl;
-    if (cp.grouped) {
-      for (const LevelPlan& lv : cp.levels) {
-        nl += (lv.group_leaves.empty() ? 0 : 1) + (lv.group_steps.empty() || lv.chained ? 0 : 1);
-        nl += static_cast<int64_t>(lv.single_leaves.size());
-        for (int s : lv.single_steps) nl += step_launches(cp.steps[s]);
-      }
-    } else {
-      for (const StepPlan& sp : cp.steps) nl += static_cast<int64_t>(sp.preps.size()) + step_launches(sp);
-    }
-    t.launches += nl;
+  for (auto& c : decompose(plan, first, count)) {
+    const LockstepInfo& q = plan.chunk(c.first).lockstep;
+    t.launches += q.launches;
     if (seen[c.first]) continue;
     seen[c.first] = 1;
-    for (const StepPlan& sp : cp.steps)
-      if (sp.kind == GemmKernel::MFMA) {
-        t.bytes_per_run += sizeof(GroupedEntry);
-        t.parts += 1;
-      }
-    if (!cp.grouped) continue;
-    for (const LevelPlan& lv : cp.levels) {  // per run: one GroupRun per grouped launch
-      if (!lv.group_steps.empty() && !lv.chained) {
-        t.bytes_per_run += sizeof(GroupRun);
-        t.parts += 1;
-      }
-      if (!lv.group_leaves.empty()) {
-        t.bytes_per_run += sizeof(GroupRun);
-        t.parts += 1;
-      }
-    }
+    t.bytes_per_run += q.bytes_per_run;
+    t.parts += q.parts;
   }
   return t;
 }
@@ -770,9 +782,10 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
       ops.emplace_back(new ChunkOps{*runs[r].plan, *runs[r].plan->chunks[j], runs[r].a, rb[r].cur_dev, stream, none});
     return ops;
   };
-  // Tables of the job, built once on the host and uploaded once: per MFMA
-  // step the K runs' GEMMs (grouped launch), per tree level one GroupRun
-  // per run for its small GEMMs and one for its plain gathers.  Tables
+  // Tables of the job, built once on the host and uploaded once: per step
+  // with a launch of its own the K runs' GEMMs and split-K epilogues, per
+  // tree level one GroupRun per run for its small GEMMs and one for its plain
+  // gathers, per chunk plan the K roots.  Tables
   // serve every chunk of a chunk plan, so leaf bases are read from each
   // run's "current chunk" slot, refreshed before the chunk's first launch.
   char* host = static_cast<char*>(host_tables);
@@ -789,7 +802,13 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
     int n_gemm = 0, n_gath = 0;  // runs in them (0: no such launch)
     int64_t gemm_blocks = 0, gath_total = 0;
   };
-  std::map<std::pair<int, int>, std::pair<size_t, int64_t>> grouped;  // (j, step) -> (offset, tiles)
+  struct StepTabs {
+    size_t gemm = 0, epilogue = 0;  // offsets of the GroupedEntry or GemmDesc table, of the SplitkRun table
+    int64_t tiles = 0;              // MFMA: tiles of the launch
+    bool split = false;
+  };
+  std::map<std::pair<int, int>, StepTabs> grouped;                    // (j, step)
+  std::map<int, size_t> roots;                                        // j -> offset of the ReduceRun table
   std::map<std::pair<int, int>, LevelTabs> levtabs;                   // (j, level)
   std::vector<char> built(p0.chunks.size(), 0);
   for (size_t c = 0; c < rb[0].chunks.size(); ++c) {
@@ -798,24 +817,54 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
     built[j] = 1;
     const ChunkPlan& cp0 = *p0.chunks[j];
     auto ops = ops_of(c);
+    std::vector<char> in_level(cp0.steps.size(), 0);  // run by a level's launch
+    if (cp0.grouped)
+      for (const LevelPlan& lv : cp0.levels)
+        for (int s : lv.group_steps) in_level[s] = 1;
     for (int s = 0; s < static_cast<int>(cp0.steps.size()); ++s) {
-      if (cp0.steps[s].kind != GemmKernel::MFMA || ops[0]->presplit(cp0.steps[s])) continue;
-      const int v = ops[0]->variant(cp0.steps[s]);
-      if (!grouped_variant_ok(form, prec, v)) continue;  // no grouped form: per-request launches
+      const StepPlan& sp0 = cp0.steps[s];
+      if (in_level[s] || ops[0]->presplit(sp0)) continue;
+      const int v = ops[0]->variant(sp0);
+      const bool mfma = sp0.kind == GemmKernel::MFMA;
+      if (mfma && !grouped_variant_ok(form, prec, v)) continue;  // no grouped form: per-request launches
       bool ok = true;
       for (int r = 0; ok && r < K; ++r) {
         const StepPlan& sp = ops[r]->cp.steps[s];
-        ok = sp.kind == GemmKernel::MFMA && ops[r]->variant(sp) == v;
+        ok = sp.kind == sp0.kind && (!mfma || ops[r]->variant(sp) == v);
       }
       if (!ok) continue;
-      const size_t off = take(K * sizeof(GroupedEntry));
-      auto* e = reinterpret_cast<GroupedEntry*>(host + off);
-      for (int r = 0; r < K; ++r) {
-        std::memset(&e[r], 0, sizeof(GroupedEntry));
-        e[r].d = ops[r]->desc(s);
+      StepTabs t;
+      if (mfma) {
+        t.gemm = take(K * sizeof(GroupedEntry));
+        auto* e = reinterpret_cast<GroupedEntry*>(host + t.gemm);
+        for (int r = 0; r < K; ++r) {
+          std::memset(&e[r], 0, sizeof(GroupedEntry));
+          e[r].d = ops[r]->desc(s);
+        }
+        t.tiles = grouped_layout(e, K, v);
+        if (t.tiles <= 0) continue;
+      } else {
+        t.gemm = take(K * sizeof(GemmDesc));
+        auto* e = reinterpret_cast<GemmDesc*>(host + t.gemm);
+        for (int r = 0; r < K; ++r) e[r] = ops[r]->desc(s);
       }
-      const int64_t total = grouped_layout(e, K, v);
-      if (total > 0) grouped[{j, s}] = {off, total};
+      if (sp0.split > 1 && !sp0.trans) {
+        t.split = true;
+        t.epilogue = take(K * sizeof(SplitkRun));
+        auto* e = reinterpret_cast<SplitkRun*>(host + t.epilogue);
+        for (int r = 0; r < K; ++r) {
+          const StepPlan& sp = ops[r]->cp.steps[s];
+          e[r] = {ops[r]->desc(s).C, ops[r]->ptr(sp.C), sp.dev_offM, sp.dev_offN};
+        }
+      }
+      grouped[{j, s}] = t;
+    }
+    bool reducing = true;
+    for (int r = 0; r < K; ++r) reducing = reducing && !runs[r].a.direct_out;
+    if (reducing) {
+      roots[j] = take(K * sizeof(ReduceRun));
+      auto* e = reinterpret_cast<ReduceRun*>(host + roots[j]);
+      for (int r = 0; r < K; ++r) e[r] = {ops[r]->ptr(ops[r]->cp.root_id), runs[r].a.acc};
     }
     if (!cp0.grouped) continue;
     // per level, the runs' own device tables (materialized with each plan)
@@ -872,11 +921,22 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
         for (auto& op : ops) op->step(s);
         return;
       }
-      const int v = ops[0]->variant(cp0.steps[s]);
-      check_hip(launch_gemm_grouped(reinterpret_cast<const GroupedEntry*>(dev + it->second.first), K,
-                                    it->second.second, v, form, prec, stream),
-                "grouped GEMM launch");
-      for (auto& op : ops) op->finish(s);
+      const StepPlan& sp = cp0.steps[s];
+      const StepTabs& t = it->second;
+      if (sp.kind == GemmKernel::MFMA)
+        check_hip(launch_gemm_grouped(reinterpret_cast<const GroupedEntry*>(dev + t.gemm), K, t.tiles,
+                                      ops[0]->variant(sp), form, prec, stream),
+                  "grouped GEMM launch");
+      else
+        check_hip(launch_gemm_valu_runs(ops[0]->desc(s), reinterpret_cast<const GemmDesc*>(dev + t.gemm), K, sp.kind, prec,
+                                        stream),
+                  "grouped step launch");
+      if (t.split)
+        check_hip(launch_splitk_reduce_runs(reinterpret_cast<const SplitkRun*>(dev + t.epilogue), K, sp.h, sp.lm, sp.ln,
+                                            sp.split, stream),
+                  "grouped split-K epilogues");
+      else
+        for (auto& op : ops) op->finish(s);
     };
     const int ns = static_cast<int>(cp0.steps.size());
     if (ns == 0)
@@ -907,7 +967,15 @@ void run_lockstep(std::vector<LockstepRun>& runs, void* host_tables, void* dev_t
         gemm(s);
       }
     }
-    for (int r = 0; r < K; ++r) ops[r]->reduce(runs[r].a.fresh_acc && c == 0);
+    bool all_fresh = true, none_fresh = true;
+    for (int r = 0; r < K; ++r) (runs[r].a.fresh_acc && c == 0 ? none_fresh : all_fresh) = false;
+    auto root = roots.find(j);
+    if (root != roots.end() && (all_fresh || none_fresh))
+      check_hip(launch_reduce_fp64_runs(reinterpret_cast<const ReduceRun*>(dev + root->second), K, cp0.hs, cp0.R, all_fresh,
+                                        stream),
+                "grouped reductions");
+    else
+      for (int r = 0; r < K; ++r) ops[r]->reduce(runs[r].a.fresh_acc && c == 0);
   }
 }
 

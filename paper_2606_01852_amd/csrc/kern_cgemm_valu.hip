@@ -17,7 +17,7 @@ namespace tnc {
 namespace {
 
 template <bool SPLIT>
-__global__ __launch_bounds__(256) void cgemm_small(GemmDesc d) {
+__device__ __forceinline__ void small_body(const GemmDesc& d) {
   const int64_t mn = d.m * d.n;
   const int64_t total = d.h * mn;
   for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < total;
@@ -58,7 +58,7 @@ struct DotAcc {
 };
 
 template <bool SPLIT>
-__global__ __launch_bounds__(256) void cgemm_dot(GemmDesc d) {
+__device__ __forceinline__ void dot_body(const GemmDesc& d) {
   const int lane = threadIdx.x & 63;
   const int64_t mn = d.m * d.n;
   const int64_t total = d.h * mn;
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void cgemm_dot(GemmDesc d) {
 // wave per output, k = 4096 took 7.4 us for 16 outputs on four CUs, now
 // 3.9).  The four waves' sums are added in order.
 template <bool SPLIT>
-__global__ __launch_bounds__(256) void cgemm_dot_few(GemmDesc d) {
+__device__ __forceinline__ void dot_few_body(const GemmDesc& d) {
   __shared__ float2 part[4];
   const int tid = threadIdx.x;
   const int64_t mn = d.m * d.n, out = blockIdx.x;
@@ -154,10 +154,38 @@ __global__ __launch_bounds__(256) void cgemm_dot_few(GemmDesc d) {
   }
 }
 
-__global__ __launch_bounds__(256) void splitk_reduce(const float2* __restrict__ P, float2* __restrict__ C,
-                                                     int64_t h, int64_t m, int64_t n, int64_t S,
-                                                     const int64_t* __restrict__ offM,
-                                                     const int64_t* __restrict__ offN) {
+// One launch for the step, or for the same step of several runs (grid row y
+// is run y, its descriptor in the table): eight requests of a fused job that
+// end in a small step each, a reduction and a copy took 24 launches there,
+// 13 us apart while the workers contend for the runtime.
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void cgemm_small(GemmDesc d) {
+  small_body<SPLIT>(d);
+}
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void cgemm_small_runs(const GemmDesc* __restrict__ runs) {
+  small_body<SPLIT>(runs[blockIdx.y]);
+}
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void cgemm_dot(GemmDesc d) {
+  dot_body<SPLIT>(d);
+}
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void cgemm_dot_runs(const GemmDesc* __restrict__ runs) {
+  dot_body<SPLIT>(runs[blockIdx.y]);
+}
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void cgemm_dot_few(GemmDesc d) {
+  dot_few_body<SPLIT>(d);
+}
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void cgemm_dot_few_runs(const GemmDesc* __restrict__ runs) {
+  dot_few_body<SPLIT>(runs[blockIdx.y]);
+}
+
+__device__ __forceinline__ void splitk_body(const float2* __restrict__ P, float2* __restrict__ C, int64_t h, int64_t m,
+                                            int64_t n, int64_t S, const int64_t* __restrict__ offM,
+                                            const int64_t* __restrict__ offN) {
   const int64_t mn = m * n;
   const int64_t total = h * mn;
   for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < total;
@@ -196,6 +224,56 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float2* __restrict__ 
   }
 }
 
+__global__ __launch_bounds__(256) void splitk_reduce(const float2* __restrict__ P, float2* __restrict__ C,
+                                                     int64_t h, int64_t m, int64_t n, int64_t S,
+                                                     const int64_t* __restrict__ offM,
+                                                     const int64_t* __restrict__ offN) {
+  splitk_body(P, C, h, m, n, S, offM, offN);
+}
+__global__ __launch_bounds__(256) void splitk_reduce_runs(const SplitkRun* __restrict__ runs, int64_t h, int64_t m,
+                                                          int64_t n, int64_t S) {
+  const SplitkRun q = runs[blockIdx.y];
+  splitk_body(q.P, q.C, h, m, n, S, q.offM, q.offN);
+}
+
+int64_t elements_grid(int64_t total) {
+  const int64_t grid = (total + 255) / 256;
+  return grid > 1048576 ? 1048576 : grid;
+}
+
+template <bool SPLIT>
+hipError_t launch_valu(const GemmDesc& d, const GemmDesc* runs, int n_runs, GemmKernel kind, hipStream_t s) {
+  const int64_t total = d.h * d.m * d.n;
+  const bool few = total <= kDotFewOutputs;
+  const int64_t gx = kind == GemmKernel::SMALL ? elements_grid(total) : few ? total : (total + 3) / 4;
+  if (gx > 0x7FFFFFLL) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(n_runs));
+  if (kind == GemmKernel::SMALL) {
+    if (runs)
+      hipLaunchKernelGGL(cgemm_small_runs<SPLIT>, grid, dim3(256), 0, s, runs);
+    else
+      hipLaunchKernelGGL(cgemm_small<SPLIT>, grid, dim3(256), 0, s, d);
+  } else if (few) {
+    if (runs)
+      hipLaunchKernelGGL(cgemm_dot_few_runs<SPLIT>, grid, dim3(256), 0, s, runs);
+    else
+      hipLaunchKernelGGL(cgemm_dot_few<SPLIT>, grid, dim3(256), 0, s, d);
+  } else {
+    if (runs)
+      hipLaunchKernelGGL(cgemm_dot_runs<SPLIT>, grid, dim3(256), 0, s, runs);
+    else
+      hipLaunchKernelGGL(cgemm_dot<SPLIT>, grid, dim3(256), 0, s, d);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_valu(const GemmDesc& d, const GemmDesc* runs, int n_runs, GemmKernel kind, Prec prec, hipStream_t s) {
+  if (d.h <= 0 || d.m <= 0 || d.n <= 0) return hipSuccess;
+  if (d.k <= 0 || n_runs < 1 || n_runs > 65535 || (kind != GemmKernel::SMALL && kind != GemmKernel::DOT))
+    return hipErrorInvalidValue;
+  return prec == Prec::BF16X3 ? launch_valu<true>(d, runs, n_runs, kind, s) : launch_valu<false>(d, runs, n_runs, kind, s);
+}
+
 }  // namespace
 
 hipError_t launch_splitk_reduce(const float2* P, float2* C, int64_t h, int64_t m, int64_t n, int64_t S,
@@ -203,43 +281,28 @@ hipError_t launch_splitk_reduce(const float2* P, float2* C, int64_t h, int64_t m
   const int64_t total = h * m * n;
   if (total <= 0) return hipSuccess;
   if (S <= 0) return hipErrorInvalidValue;
-  int64_t grid = (total + 255) / 256;
-  if (grid > 1048576) grid = 1048576;
-  hipLaunchKernelGGL(splitk_reduce, dim3(grid), dim3(256), 0, s, P, C, h, m, n, S, offM, offN);
+  hipLaunchKernelGGL(splitk_reduce, dim3(static_cast<unsigned>(elements_grid(total))), dim3(256), 0, s, P, C, h, m, n, S,
+                     offM, offN);
+  return hipGetLastError();
+}
+
+hipError_t launch_splitk_reduce_runs(const SplitkRun* runs, int n_runs, int64_t h, int64_t m, int64_t n, int64_t S,
+                                     hipStream_t s) {
+  const int64_t total = h * m * n;
+  if (total <= 0) return hipSuccess;
+  if (S <= 0 || n_runs < 1 || n_runs > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(splitk_reduce_runs, dim3(static_cast<unsigned>(elements_grid(total)), static_cast<unsigned>(n_runs)),
+                     dim3(256), 0, s, runs, h, m, n, S);
   return hipGetLastError();
 }
 
 hipError_t launch_gemm_valu(const GemmDesc& d, GemmKernel kind, Prec prec, hipStream_t s) {
-  if (d.h <= 0 || d.m <= 0 || d.n <= 0) return hipSuccess;
-  if (d.k <= 0) return hipErrorInvalidValue;
-  if (kind == GemmKernel::DOT) {
-    const int64_t total = d.h * d.m * d.n;
-    const int64_t grid = (total + 3) / 4;
-    if (grid > 0x7FFFFFLL) return hipErrorInvalidValue;
-    if (total <= kDotFewOutputs) {
-      if (prec == Prec::BF16X3)
-        hipLaunchKernelGGL(cgemm_dot_few<true>, dim3(total), dim3(256), 0, s, d);
-      else
-        hipLaunchKernelGGL(cgemm_dot_few<false>, dim3(total), dim3(256), 0, s, d);
-      return hipGetLastError();
-    }
-    if (prec == Prec::BF16X3)
-      hipLaunchKernelGGL(cgemm_dot<true>, dim3(grid), dim3(256), 0, s, d);
-    else
-      hipLaunchKernelGGL(cgemm_dot<false>, dim3(grid), dim3(256), 0, s, d);
-    return hipGetLastError();
-  }
-  if (kind == GemmKernel::SMALL) {
-    const int64_t total = d.h * d.m * d.n;
-    int64_t grid = (total + 255) / 256;
-    if (grid > 1048576) grid = 1048576;
-    if (prec == Prec::BF16X3)
-      hipLaunchKernelGGL(cgemm_small<true>, dim3(grid), dim3(256), 0, s, d);
-    else
-      hipLaunchKernelGGL(cgemm_small<false>, dim3(grid), dim3(256), 0, s, d);
-    return hipGetLastError();
-  }
-  return hipErrorInvalidValue;
+  return launch_valu(d, nullptr, 1, kind, prec, s);
+}
+
+hipError_t launch_gemm_valu_runs(const GemmDesc& shape, const GemmDesc* runs, int n_runs, GemmKernel kind, Prec prec,
+                                 hipStream_t s) {
+  return runs ? launch_valu(shape, runs, n_runs, kind, prec, s) : hipErrorInvalidValue;
 }
 
 }  // namespace tnc

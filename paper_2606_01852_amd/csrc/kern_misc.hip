@@ -13,8 +13,8 @@ namespace {
 
 // One workgroup per output element: thread t adds s = t, t + 256, ... in
 // order, then a fixed LDS tree combines the 256 partial sums.
-__global__ __launch_bounds__(256) void reduce_fp64_block(const float2* root, double2* acc, int64_t hs,
-                                                          int64_t R, int overwrite) {
+__device__ __forceinline__ void reduce_block_body(const float2* root, double2* acc, int64_t hs, int64_t R,
+                                                  int overwrite) {
   __shared__ double sr[256], si[256];
   const int64_t i = blockIdx.x;
   double xr = 0.0, xi = 0.0;
@@ -42,8 +42,8 @@ __global__ __launch_bounds__(256) void reduce_fp64_block(const float2* root, dou
 }
 
 // One thread per output element, s in order.
-__global__ __launch_bounds__(256) void reduce_fp64_thread(const float2* root, double2* acc, int64_t hs,
-                                                           int64_t R, int overwrite) {
+__device__ __forceinline__ void reduce_thread_body(const float2* root, double2* acc, int64_t hs, int64_t R,
+                                                   int overwrite) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < R;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     double xr = 0.0, xi = 0.0;
@@ -57,6 +57,24 @@ __global__ __launch_bounds__(256) void reduce_fp64_thread(const float2* root, do
     a.y += xi;
     acc[i] = a;
   }
+}
+
+// One root, or the roots of several runs (grid row y is run y).
+__global__ __launch_bounds__(256) void reduce_fp64_block(const float2* root, double2* acc, int64_t hs, int64_t R,
+                                                         int overwrite) {
+  reduce_block_body(root, acc, hs, R, overwrite);
+}
+__global__ __launch_bounds__(256) void reduce_fp64_thread(const float2* root, double2* acc, int64_t hs, int64_t R,
+                                                          int overwrite) {
+  reduce_thread_body(root, acc, hs, R, overwrite);
+}
+__global__ __launch_bounds__(256) void reduce_fp64_block_runs(const ReduceRun* __restrict__ runs, int64_t hs, int64_t R,
+                                                              int overwrite) {
+  reduce_block_body(runs[blockIdx.y].root, runs[blockIdx.y].acc, hs, R, overwrite);
+}
+__global__ __launch_bounds__(256) void reduce_fp64_thread_runs(const ReduceRun* __restrict__ runs, int64_t hs, int64_t R,
+                                                               int overwrite) {
+  reduce_thread_body(runs[blockIdx.y].root, runs[blockIdx.y].acc, hs, R, overwrite);
 }
 
 __global__ __launch_bounds__(256) void norm2_kernel(const double2* acc, int64_t R, double* out) {
@@ -122,6 +140,20 @@ hipError_t launch_reduce_fp64(const float2* root, double2* acc, int64_t hs, int6
     hipLaunchKernelGGL(reduce_fp64_block, dim3(static_cast<unsigned>(R)), dim3(256), 0, s, root, acc, hs, R, ow);
   else
     hipLaunchKernelGGL(reduce_fp64_thread, dim3(grid_for(R)), dim3(256), 0, s, root, acc, hs, R, ow);
+  return hipGetLastError();
+}
+
+hipError_t launch_reduce_fp64_runs(const ReduceRun* runs, int n_runs, int64_t hs, int64_t R, bool overwrite,
+                                   hipStream_t s) {
+  if (R <= 0 || hs <= 0) return hipSuccess;
+  if (n_runs < 1 || n_runs > 65535) return hipErrorInvalidValue;
+  const int ow = overwrite ? 1 : 0;
+  const unsigned n = static_cast<unsigned>(n_runs);
+  if (hs >= 64 && R <= 65536)
+    hipLaunchKernelGGL(reduce_fp64_block_runs, dim3(static_cast<unsigned>(R), n), dim3(256), 0, s, runs, hs, R, ow);
+  else
+    hipLaunchKernelGGL(reduce_fp64_thread_runs, dim3(static_cast<unsigned>(grid_for(R)), n), dim3(256), 0, s, runs, hs, R,
+                       ow);
   return hipGetLastError();
 }
 

@@ -222,6 +222,11 @@ hipError_t launch_gemm_4m(const GemmDesc& d, int variant, Prec prec, hipStream_t
 hipError_t launch_gemm_4m_grouped(const GroupedEntry* tab, int n, int64_t total, int variant, Prec prec, hipStream_t s);
 void prepare_gemm_4m();
 hipError_t launch_gemm_valu(const GemmDesc& d, GemmKernel kind, Prec prec, hipStream_t s);
+// The same VALU step of n_runs runs of one structure (a fused serving job) in
+// one launch: `runs` is their descriptors on the device, all of the shape of
+// `shape`; each run's result is bitwise that of its own launch.
+hipError_t launch_gemm_valu_runs(const GemmDesc& shape, const GemmDesc* runs, int n_runs, GemmKernel kind, Prec prec,
+                                 hipStream_t s);
 // Split-bf16x3 on operands split once into bf16 planes (large steps of one
 // batch entry, h == 1, no operand tables): the launch splits A and B into
 // `planes` (presplit_plane_bytes(m, n, k) bytes of device memory, 256-byte
@@ -272,6 +277,15 @@ hipError_t launch_gemm_presplit_3m(const GemmDesc& d, void* buf, bool have_a, bo
 // p ascending, stored at b * m * n + (offM ? offM[i] + offN[j] : i * n + j).
 hipError_t launch_splitk_reduce(const float2* P, float2* C, int64_t h, int64_t m, int64_t n, int64_t S,
                                 const int64_t* offM, const int64_t* offN, hipStream_t s);
+// The epilogues of one step of several runs in one launch.
+struct SplitkRun {
+  const float2* P;
+  float2* C;
+  const int64_t* offM;
+  const int64_t* offN;
+};
+hipError_t launch_splitk_reduce_runs(const SplitkRun* runs, int n_runs, int64_t h, int64_t m, int64_t n, int64_t S,
+                                     hipStream_t s);
 // Grouped launches (one per tree level).  Operand pointers flagged rel_*
 // hold arena offsets, relocated against the arena base at run time, so the
 // tables stay valid for any arena.
@@ -364,6 +378,13 @@ hipError_t launch_gather(const GatherDesc& d, hipStream_t s);
 // (the same bits as adding it to a zeroed accumulator).
 hipError_t launch_reduce_fp64(const float2* root, double2* acc, int64_t hs, int64_t R, bool overwrite,
                               hipStream_t s);
+// The roots of several runs in one launch.
+struct ReduceRun {
+  const float2* root;
+  double2* acc;
+};
+hipError_t launch_reduce_fp64_runs(const ReduceRun* runs, int n_runs, int64_t hs, int64_t R, bool overwrite,
+                                   hipStream_t s);
 // out = sum_i |acc[i]|^2 in FP64 (one value written to *out, device pointer).
 hipError_t launch_norm2(const double2* acc, int64_t R, double* out, hipStream_t s);
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t s);

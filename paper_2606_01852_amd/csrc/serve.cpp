@@ -119,6 +119,7 @@ struct Request {
   std::string key;                   // structure key (fusable light request), or empty
   LockstepInfo tables;               // its share of a fused job's tables
   int64_t table_off = -1, table_bytes = 0;  // a fused job's table (first request of the job)
+  int64_t result_off = -1;                  // in it, where the job's results lie side by side; -1: each in its own run's memory
   Clock::time_point t_submit, t_done;
   bool done = false;
   tnc_status status = TNC_OK;
@@ -265,6 +266,7 @@ struct Server {
       // after the lock and the notifications (a last reference tears the
       // plan down, with device synchronizations)
       std::vector<std::shared_ptr<Plan>> finished;
+      bool waiting = false;
       {
         std::lock_guard<std::mutex> g(mu);
         Request& r = *job[0];
@@ -284,6 +286,7 @@ struct Server {
           // network here, before any waiter returns
           for (auto& q : job) q->batcher.reset();
         }
+        waiting = !queue.empty();  // what this job held may admit any of them
         const Clock::time_point now = Clock::now();
         for (auto& q : job) {
           q->t_done = now;
@@ -294,7 +297,7 @@ struct Server {
           q->plan = nullptr;
         }
       }
-      cv_work.notify_all();
+      if (waiting) cv_work.notify_all();
       cv_done.notify_all();
     }
   }
@@ -318,6 +321,14 @@ struct Server {
     }
     if (job.size() == 1) return;
     r0.table_bytes = static_cast<int64_t>(lockstep_table_bytes(r0.tables, static_cast<int>(job.size())));
+    // small results side by side behind the table, so that one copy fetches
+    // them all (a copy of its own costs a request as much as a launch)
+    const int64_t results = static_cast<int64_t>(job.size()) * r0.plan->chunks[0]->R * 16;
+    r0.result_off = -1;
+    if (results <= kPackedResults) {
+      r0.result_off = align_up(r0.table_bytes);
+      r0.table_bytes = r0.result_off + results;
+    }
     r0.table_off = arena.alloc(r0.table_bytes);
     if (r0.table_off >= 0) return;
     // no room for the table: the others go back to the front of the queue
@@ -354,6 +365,7 @@ struct Server {
     return bufs[slot];
   }
 
+  static constexpr int64_t kPackedResults = 1 << 20;
   static constexpr const char* kHostOnly = "host-only context: the request was admitted but nothing runs";
 
   // Run `plan` over all its slices in the request's arena interval; the FP64
@@ -444,6 +456,8 @@ struct Server {
       const int K = static_cast<int>(job.size());
       std::vector<LockstepRun> runs(K);
       size_t res_total = 0;
+      Request& r0 = *job[0];
+      char* packed = r0.result_off >= 0 ? ctx.arena + r0.table_off + r0.result_off : nullptr;
       for (int q = 0; q < K; ++q) {
         Request& r = *job[q];
         runs[q].plan = r.plan;
@@ -452,17 +466,19 @@ struct Server {
         a.count = r.count;
         a.arena = ctx.arena + r.arena_off;
         a.arena_bytes = static_cast<size_t>(r.work_bytes);
-        a.acc = reinterpret_cast<double2*>(ctx.arena + r.arena_off + r.acc_off);
+        a.acc = reinterpret_cast<double2*>(packed ? packed + res_total : ctx.arena + r.arena_off + r.acc_off);
         a.stream = stream;
         a.fresh_acc = true;
         res_total += static_cast<size_t>(r.plan->chunks[0]->R) * 16;
       }
-      Request& r0 = *job[0];
       void* host_tab = staging(pinned_tab, pinned_tab_bytes, slot, static_cast<size_t>(r0.table_bytes));
-      run_lockstep(runs, host_tab, ctx.arena + r0.table_off, static_cast<size_t>(r0.table_bytes), stream);
+      run_lockstep(runs, host_tab, ctx.arena + r0.table_off,
+                   static_cast<size_t>(packed ? r0.result_off : r0.table_bytes), stream);
       char* host = static_cast<char*>(staging(pinned, pinned_bytes, slot, res_total));
       size_t off = 0;
-      for (int q = 0; q < K; ++q) {
+      if (packed)
+        check_hip(hipMemcpyAsync(host, packed, res_total, hipMemcpyDeviceToHost, stream), "result copy");
+      for (int q = 0; q < K && !packed; ++q) {
         const size_t b = static_cast<size_t>(job[q]->plan->chunks[0]->R) * 16;
         check_hip(hipMemcpyAsync(host + off, runs[q].a.acc, b, hipMemcpyDeviceToHost, stream), "result copy");
         off += b;
@@ -648,7 +664,7 @@ tnc_status tnc_submit(tnc_ctx ctx, tnc_plan plan, int64_t first_slice, int64_t n
       s->queue.push_back(r);
       s->reqs[r->id] = r;
     }
-    s->cv_work.notify_all();
+    s->cv_work.notify_one();  // one request gives one worker work: all of them woken, each submission costs their contention
     *id = r->id;
   TNC_CATCH
 }
@@ -786,7 +802,7 @@ tnc_status tnc_submit_row(tnc_ctx ctx, tnc_batcher bh, const void* const* row_da
         wake = true;
       }
     }
-    if (wake) s->cv_work.notify_all();
+    if (wake) s->cv_work.notify_one();
     *id = r->id;
   TNC_CATCH
 }
