@@ -242,6 +242,8 @@ struct ChunkPlan {
   DeviceBuf leaf_cache;                      // permuted copies of the cached leaves
   int64_t cache_bytes = 0;
   int n_cached = 0;
+  std::vector<int> cache_gathers;            // cached leaves that one gather launch fills (their tables' offsets follow)
+  int64_t off_cache_gather = -1, off_cache_prefix = -1, cache_gather_total = 0;
   std::vector<uint64_t> cache_version;       // leaf versions the cache holds (empty: not filled)
   std::vector<uint8_t> host_blob;
   double flops = 0, bytes = 0, transpose_bytes = 0;

@@ -85,6 +85,14 @@ void materialize(const Net& net, ChunkPlan& cp, hipStream_t stream) {
       L.off_gather_prefix = put(blob, std::vector<int64_t>(L.group_leaves.size()));
     }
   }
+  cp.cache_gathers.clear();
+  for (int t = 0; t < net.n_tensors; ++t)
+    if (cp.leaf[t].cached && !cp.leaf[t].perm.tiled && cp.leaf[t].perm.plain.rank <= kGroupRank)
+      cp.cache_gathers.push_back(t);
+  if (!cp.cache_gathers.empty()) {
+    cp.off_cache_gather = put(blob, std::vector<GroupGather>(cp.cache_gathers.size()));
+    cp.off_cache_prefix = put(blob, std::vector<int64_t>(cp.cache_gathers.size()));
+  }
   if (!blob.empty()) cp.blob.alloc(blob.size());
   if (cp.cache_bytes) cp.leaf_cache.alloc(static_cast<size_t>(cp.cache_bytes));
   char* base = static_cast<char*>(cp.blob.ptr);
@@ -133,6 +141,30 @@ void materialize(const Net& net, ChunkPlan& cp, hipStream_t stream) {
     g.vec = vec ? 1 : 0;
     return g;
   };
+  // the table of one gather launch, into the arena or into the leaf cache
+  auto gathers = [&](const std::vector<int>& leaves, int64_t off, int64_t off_prefix, bool cache) {
+    GroupGather* tab = reinterpret_cast<GroupGather*>(blob.data() + off);
+    int64_t* pre = reinterpret_cast<int64_t*>(blob.data() + off_prefix);
+    int64_t acc = 0;
+    for (size_t q = 0; q < leaves.size(); ++q) {
+      const int t = leaves[q];
+      const LeafPrep& lp = cp.leaf[t];
+      GroupGather g;
+      std::memset(&g, 0, sizeof(g));
+      g.in = static_cast<const float2*>(net.leaf[t].ptr);
+      g.out_off = cache ? lp.cache_off : cp.buf_off[cp.tensor_buf[t]];
+      g.rank = lp.perm.plain.rank;
+      g.base_slot = cache ? -1 : lp.base_slot;
+      for (int r = 0; r < g.rank; ++r) {
+        g.ext[r] = lp.perm.plain.ext[r];
+        g.in_stride[r] = lp.perm.plain.in_stride[r];
+      }
+      tab[q] = g;
+      pre[q] = acc;
+      acc += cp.numel[t];
+    }
+    return acc;
+  };
   for (size_t li = 0; li < cp.levels.size(); ++li) {
     LevelPlan& L = cp.levels[li];
     if (L.chain) {
@@ -171,30 +203,10 @@ void materialize(const Net& net, ChunkPlan& cp, hipStream_t stream) {
         for (int64_t x = 0; x < tab[q].total; x += L.gemm_per) *blk++ = {static_cast<int32_t>(q), 0, x};
       }
     }
-    if (!L.group_leaves.empty()) {
-      GroupGather* tab = reinterpret_cast<GroupGather*>(blob.data() + L.off_gather);
-      int64_t* pre = reinterpret_cast<int64_t*>(blob.data() + L.off_gather_prefix);
-      int64_t acc = 0;
-      for (size_t q = 0; q < L.group_leaves.size(); ++q) {
-        const int t = L.group_leaves[q];
-        const LeafPrep& lp = cp.leaf[t];
-        GroupGather g;
-        std::memset(&g, 0, sizeof(g));
-        g.in = static_cast<const float2*>(net.leaf[t].ptr);
-        g.out_off = cp.buf_off[cp.tensor_buf[t]];
-        g.rank = lp.perm.plain.rank;
-        g.base_slot = lp.base_slot;
-        for (int r = 0; r < g.rank; ++r) {
-          g.ext[r] = lp.perm.plain.ext[r];
-          g.in_stride[r] = lp.perm.plain.in_stride[r];
-        }
-        tab[q] = g;
-        pre[q] = acc;
-        acc += cp.numel[t];
-      }
-      L.gather_total = acc;
-    }
+    if (!L.group_leaves.empty()) L.gather_total = gathers(L.group_leaves, L.off_gather, L.off_gather_prefix, false);
   }
+  if (!cp.cache_gathers.empty())
+    cp.cache_gather_total = gathers(cp.cache_gathers, cp.off_cache_gather, cp.off_cache_prefix, true);
   if (!blob.empty()) {
     // upload on the caller's stream and wait for it alone: other requests
     // keep running, and nobody sees the tables before they are complete
@@ -277,8 +289,18 @@ void refresh_leaf_cache(const Net& net, ChunkPlan& cp, hipStream_t stream) {
     if (cp.leaf[t].cached && cp.cache_version[t] != net.version[t]) stale = true;
   if (!stale) return;
   if (stream != net.ctx->stream) check_hip(hipStreamSynchronize(net.ctx->stream), "leaf cache");
+  // one launch for all plain gathers (a launch each, the 73 leaves of a
+  // 12-qubit circuit were most of a new plan's first run)
+  const char* blob = static_cast<const char*>(cp.blob.ptr);
+  if (!cp.cache_gathers.empty())
+    check_hip(launch_group_gather(reinterpret_cast<const GroupGather*>(blob + cp.off_cache_gather),
+                                  reinterpret_cast<const int64_t*>(blob + cp.off_cache_prefix),
+                                  static_cast<int>(cp.cache_gathers.size()), cp.cache_gather_total,
+                                  static_cast<char*>(cp.leaf_cache.ptr), nullptr, stream),
+              "leaf cache");
   for (int t = 0; t < net.n_tensors; ++t)
-    if (cp.leaf[t].cached) check_hip(launch_leaf_prep(net, cp, t, cached_leaf(cp, t), nullptr, stream), "leaf cache");
+    if (cp.leaf[t].cached && (cp.leaf[t].perm.tiled || cp.leaf[t].perm.plain.rank > kGroupRank))
+      check_hip(launch_leaf_prep(net, cp, t, cached_leaf(cp, t), nullptr, stream), "leaf cache");
   check_hip(hipStreamSynchronize(stream), "leaf cache");
   cp.cache_version = net.version;
 }
