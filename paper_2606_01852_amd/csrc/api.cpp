@@ -682,10 +682,23 @@ PermuteJob plan_permute(int32_t rank, const int64_t* extents, const int32_t* per
   return j;
 }
 
+// Whether a stand-alone permute runs as a plain gather.  The table areas are
+// shared by calls, in stream order: a graph that had captured one would share
+// it with calls made outside its stream's order, so a tiled permutation is
+// refused under capture (and one that need not be tiled is not tiled there).
+bool runs_plain(const PermuteJob& j, hipStream_t s) {
+  if (!j.shape.tiled) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  check_hip(hipStreamIsCapturing(s, &st), "capture status");
+  if (st == hipStreamCaptureStatusNone) return false;
+  if (!j.shape.optional) fail(TNC_E_DEVICE, "a tiled permutation cannot be captured");
+  return true;
+}
+
 // Enqueue a planned permutation: its tables into `tables` (shape.bytes() of
 // device memory), then the permutation that reads them.
-void enqueue_permute(const PermuteJob& j, const void* in, void* out, char* tables, hipStream_t s) {
-  if (!j.shape.tiled) {
+void enqueue_permute(const PermuteJob& j, bool plain, const void* in, void* out, char* tables, hipStream_t s) {
+  if (plain) {
     GatherDesc g = j.plain;
     g.in = static_cast<const float2*>(in);
     g.out = static_cast<float2*>(out);
@@ -710,14 +723,6 @@ void enqueue_permute(const PermuteJob& j, const void* in, void* out, char* table
   check_hip(launch_permute(d, s), "permute launch");
 }
 
-// The table areas are shared by calls, in stream order: a graph that had
-// captured one would share it with calls made outside its stream's order.
-void refuse_capture(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  check_hip(hipStreamIsCapturing(s, &st), "capture status");
-  if (st != hipStreamCaptureStatusNone) fail(TNC_E_DEVICE, "a tiled permutation cannot be captured");
-}
-
 }  // namespace
 
 extern "C" {
@@ -729,8 +734,8 @@ tnc_status tnc_permute(tnc_ctx ctx, const void* in, void* out, int32_t rank, con
   const PermuteJob j = plan_permute(rank, extents, perm);
   Ctx& c = *ctx->c;
   set_device(c);
-  if (j.shape.tiled) {
-    refuse_capture(c.stream);
+  const bool plain = runs_plain(j, c.stream);
+  if (!plain) {
     // every call on the context's stream writes its tables here before the
     // launch that reads them, so calls need not wait for each other; only a
     // larger area does (the first: 1 MiB, a 2^30-element permutation's tables
@@ -740,7 +745,7 @@ tnc_status tnc_permute(tnc_ctx ctx, const void* in, void* out, int32_t rank, con
       c.scratch.alloc(std::max(j.shape.bytes(), kStaticPermuteTableBytes));
     }
   }
-  enqueue_permute(j, in, out, static_cast<char*>(c.scratch.ptr), c.stream);
+  enqueue_permute(j, plain, in, out, static_cast<char*>(c.scratch.ptr), c.stream);
   TNC_CATCH
 }
 
@@ -754,16 +759,16 @@ tnc_status tnc_permute_noalloc(tnc_ctx ctx, const void* in, void* out, int32_t r
                           " bytes, above the fixed table area of " + std::to_string(kStaticPermuteTableBytes));
   Ctx& c = *ctx->c;
   set_device(c);
-  if (!j.shape.tiled) {
-    enqueue_permute(j, in, out, nullptr, c.stream);
+  const bool plain = runs_plain(j, c.stream);
+  if (plain) {
+    enqueue_permute(j, plain, in, out, nullptr, c.stream);
     return TNC_OK;
   }
-  refuse_capture(c.stream);
   StaticTables* t = nullptr;
   check_hip(static_table_area(c.device, &t), "table area address");
   std::lock_guard<std::mutex> g(t->mu);
   check_hip(hipStreamWaitEvent(c.stream, t->last_use, 0), "table area");
-  enqueue_permute(j, in, out, t->ptr, c.stream);
+  enqueue_permute(j, false, in, out, t->ptr, c.stream);
   check_hip(hipEventRecord(t->last_use, c.stream), "table area");
   TNC_CATCH
 }

@@ -116,6 +116,7 @@ struct PermuteDesc {
 struct PermuteShape {
   static constexpr int kTileDims = 12;  // T <= 4096, extents >= 2
   int32_t tiled = 0;                    // 0: no useful tile, plain gather only
+  int32_t optional = 0;                 // the plain gather may take a tiled shape's place
   int32_t pairs = 0;                    // PermuteDesc::pairs
   int32_t T = 0, slots = 0;
   int32_t n_tile = 0, n_outer = 0, split = 0;  // outer dims [split, n_outer) make the lo table
