@@ -695,14 +695,19 @@ bool runs_plain(const PermuteJob& j, hipStream_t s) {
   return true;
 }
 
-// Enqueue a planned permutation: its tables into `tables` (shape.bytes() of
-// device memory), then the permutation that reads them.
+// Enqueue a planned permutation: where it needs tables they go into `tables`
+// (shape.bytes() of device memory), then the permutation that reads them.
 void enqueue_permute(const PermuteJob& j, bool plain, const void* in, void* out, char* tables, hipStream_t s) {
   if (plain) {
     GatherDesc g = j.plain;
     g.in = static_cast<const float2*>(in);
     g.out = static_cast<float2*>(out);
     check_hip(launch_gather(g, s), "permute launch");
+    return;
+  }
+  if (permute_direct(j.shape)) {
+    check_hip(launch_permute_direct(j.shape, static_cast<const float2*>(in), static_cast<float2*>(out), s),
+              "permute launch");
     return;
   }
   check_hip(launch_permute_tables(j.shape, tables, s), "permute tables");
@@ -735,7 +740,7 @@ tnc_status tnc_permute(tnc_ctx ctx, const void* in, void* out, int32_t rank, con
   Ctx& c = *ctx->c;
   set_device(c);
   const bool plain = runs_plain(j, c.stream);
-  if (!plain) {
+  if (!plain && !permute_direct(j.shape)) {
     // every call on the context's stream writes its tables here before the
     // launch that reads them, so calls need not wait for each other; only a
     // larger area does (the first: 1 MiB, a 2^30-element permutation's tables
@@ -760,7 +765,7 @@ tnc_status tnc_permute_noalloc(tnc_ctx ctx, const void* in, void* out, int32_t r
   Ctx& c = *ctx->c;
   set_device(c);
   const bool plain = runs_plain(j, c.stream);
-  if (plain) {
+  if (plain || permute_direct(j.shape)) {
     enqueue_permute(j, plain, in, out, nullptr, c.stream);
     return TNC_OK;
   }

@@ -191,6 +191,100 @@ __global__ __launch_bounds__(kPermThreads) void permute_pairs(PermuteDesc d) {
   }
 }
 
+// A stand-alone permutation without tables: a workgroup works out the offsets
+// of its tile from the digits (kernel arguments, so scalar loads; a division
+// is one multiplication), then moves tiles as the kernels above do.
+template <int NT, int EPT, bool PAIRS>
+__global__ __launch_bounds__(NT) void permute_digits(PermuteShape p, const f2v* __restrict__ in, f2v* __restrict__ out) {
+  extern __shared__ f2v lds[];
+  constexpr int W = PAIRS ? 2 : 1;  // elements per load and store
+  typedef std::conditional_t<PAIRS, f4v, f2v> V;
+  const uint32_t t = threadIdx.x;
+  int32_t ri[EPT], wo[EPT], ws[EPT], ws1[EPT];
+  uint32_t x[EPT], y[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    x[e] = y[e] = (e * NT + t) * W;
+    ri[e] = wo[e] = ws[e] = 0;
+  }
+  const int32_t wpos0 = p.wpos[0];
+  for (int d = 0; d < p.n_tile; ++d) {
+    const uint32_t re = p.rext[d], rm = p.rmul[d], we = p.wext[d], wm = p.wmul[d];
+    const int32_t rs = p.rin[d], os = p.wout[d], ps = p.wpos[d];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const uint32_t qr = __umulhi(x[e], rm), qw = __umulhi(y[e], wm);
+      ri[e] += static_cast<int32_t>(x[e] - qr * re) * rs;
+      const int32_t dig = static_cast<int32_t>(y[e] - qw * we);
+      wo[e] += dig * os;
+      ws[e] += dig * ps;
+      x[e] = qr;
+      y[e] = qw;
+    }
+  }
+  bool ok[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    ok[e] = (e * NT + t) * W < static_cast<uint32_t>(p.T);
+    ws1[e] = PermuteShape::pad(ws[e] + wpos0);
+    ws[e] = PermuteShape::pad(ws[e]);
+  }
+  auto outer = [&](uint32_t tile, int64_t& io, int64_t& oo) {
+    io = oo = 0;
+    for (int d = p.n_outer - 1; d >= 0; --d) {
+      const uint32_t q = __umulhi(tile, p.omul[d]);
+      const int64_t dig = tile - q * p.oext[d];
+      io += dig * p.oin[d];
+      oo += dig * p.oout[d];
+      tile = q;
+    }
+  };
+  const uint32_t n_tiles = static_cast<uint32_t>(p.n_tiles);
+  uint32_t tile = blockIdx.x;
+  if (tile >= n_tiles) return;
+  V v[EPT];
+  int64_t io, oo, next_oo = 0;
+  auto load = [&](int64_t o) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      if (ok[e]) v[e] = __builtin_nontemporal_load(reinterpret_cast<const V*>(in + o + ri[e]));
+  };
+  outer(tile, io, oo);
+  load(io);
+  for (; tile < n_tiles; tile += gridDim.x) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      if (ok[e]) {
+        const int32_t s = (e * NT + t) * W;
+        if constexpr (PAIRS) {
+          lds[PermuteShape::pad(s)] = v[e].xy;
+          lds[PermuteShape::pad(s + 1)] = v[e].zw;
+        } else {
+          lds[PermuteShape::pad(s)] = v[e];
+        }
+      }
+    __syncthreads();
+    if (tile + gridDim.x < n_tiles) {
+      outer(tile + gridDim.x, io, next_oo);
+      load(io);
+    }
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      if (ok[e]) {
+        V w;
+        if constexpr (PAIRS) {
+          const f2v a = lds[ws[e]], b = lds[ws1[e]];
+          w = f4v{a.x, a.y, b.x, b.y};
+        } else {
+          w = lds[ws[e]];
+        }
+        __builtin_nontemporal_store(w, reinterpret_cast<V*>(out + oo + wo[e]));
+      }
+    oo = next_oo;
+    __syncthreads();
+  }
+}
+
 // The index tables of a stand-alone permute: one entry per thread (a tile
 // element's four, or a lo or hi pair), a few microseconds at most.  Built
 // here because the alternative, tables from the host, costs the call a wait
@@ -230,6 +324,21 @@ __global__ __launch_bounds__(256) void gather_plain(GatherDesc d) {
 
 }  // namespace
 
+// Workgroups of a launch: many short-lived ones of about 8192 elements (64
+// KiB) each: a few tiles per workgroup, so each loads its next tile while it
+// stores the current one.  Measured: 131072 workgroups best among 8192 .. one
+// per tile on pair30's 2^30-element operand (4096-element tiles); 1024-
+// element tiles of 2^28 elements 0.94 -> 0.85 ms at 32768 instead of
+// 131072, pair_batch's 64 operand permutes 0.164 -> 0.125 ms.  At least
+// 1024 workgroups (or one per tile) so that small tensors stay spread
+// over the chip.
+static int64_t workgroups(int64_t n_tiles, int64_t T) {
+  int64_t grid = n_tiles * T / 8192;
+  if (grid < 1024) grid = 1024;
+  if (grid > n_tiles) grid = n_tiles;
+  return grid > 131072 ? 131072 : grid;
+}
+
 hipError_t launch_permute(const PermuteDesc& d, hipStream_t s) {
   if (d.n_tiles <= 0) return hipSuccess;
   // 16 elements per thread for every tile of up to 4096 elements: measured
@@ -239,18 +348,7 @@ hipError_t launch_permute(const PermuteDesc& d, hipStream_t s) {
   while (ept * kPermThreads < d.T) ept *= 2;
   if (d.n_tiles >= 1024 && ept < 16) ept = 16;
   const size_t lds = static_cast<size_t>(d.slots) * sizeof(float2);
-  // many short-lived workgroups of about 8192 elements (64 KiB) each: a
-  // few tiles per workgroup, so each loads its next tile while it stores
-  // the current one.  Measured: 131072 workgroups best among 8192 .. one
-  // per tile on pair30's 2^30-element operand (4096-element tiles); 1024-
-  // element tiles of 2^28 elements 0.94 -> 0.85 ms at 32768 instead of
-  // 131072, pair_batch's 64 operand permutes 0.164 -> 0.125 ms.  At least
-  // 1024 workgroups (or one per tile) so that small tensors stay spread
-  // over the chip.
-  int64_t grid = d.n_tiles * d.T / 8192;
-  if (grid < 1024) grid = 1024;
-  if (grid > d.n_tiles) grid = d.n_tiles;
-  if (grid > 131072) grid = 131072;
+  const int64_t grid = workgroups(d.n_tiles, d.T);
   // 16-byte pairs where the tables allow them and the base keeps them
   // aligned (standalone repeats of pair30's 2^30-element permutation:
   // 5.77 -> 5.92 TB/s; pair_batch's 64 operand permutes: 0.198 -> 0.165
@@ -292,6 +390,32 @@ hipError_t launch_permute(const PermuteDesc& d, hipStream_t s) {
   if (d.planes == 2) return launch(std::integral_constant<int, 2>{});
   if (d.planes == 3) return launch(std::integral_constant<int, 3>{});
   return launch(std::integral_constant<int, 0>{});
+}
+
+// As far as the digits' divisions are exact, which is as far as it was faster
+// everywhere (us per call with tables, without: 2^12 elements 7.1, 3.7; 2^18
+// 11.0, 5.5; 6^9 44.6, 31.3; 2^23 37.5, 31.5; 2^26 203, 199).
+bool permute_direct(const PermuteShape& p) { return p.tiled && p.n_tiles <= 65536; }
+
+hipError_t launch_permute_direct(const PermuteShape& p, const float2* in, float2* out, hipStream_t s) {
+  if (!permute_direct(p) || p.T > 4096) return hipErrorInvalidValue;
+  // (a pair's second element is the next in the write order's first mode)
+  const bool pairs = p.pairs && p.wext[0] % 2 == 0 && (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 16 == 0;
+  const size_t lds = static_cast<size_t>(p.slots) * sizeof(float2);
+  const dim3 grid(static_cast<unsigned>(workgroups(p.n_tiles, p.T)));
+  const f2v* i = reinterpret_cast<const f2v*>(in);
+  f2v* o = reinterpret_cast<f2v*>(out);
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, s, p, i, o);
+    return hipGetLastError();
+  };
+  if (pairs)
+    return p.T <= 1024   ? launch(permute_digits<256, 2, true>, 256)
+           : p.T <= 2048 ? launch(permute_digits<256, 4, true>, 256)
+                         : launch(permute_digits<512, 4, true>, 512);
+  return p.T <= 1024   ? launch(permute_digits<256, 4, false>, 256)
+         : p.T <= 2048 ? launch(permute_digits<512, 4, false>, 512)
+                       : launch(permute_digits<512, 8, false>, 512);
 }
 
 hipError_t launch_permute_tables(const PermuteShape& p, char* tables, hipStream_t s) {

@@ -127,6 +127,10 @@ struct PermuteShape {
   int32_t rin[kTileDims], wout[kTileDims], wpos[kTileDims];
   uint32_t oext[64];            // outer dims in output order
   int64_t oin[64], oout[64];
+  // x / ext is (x * mul) >> 32 with mul = ceil(2^32 / ext) while x * ext <
+  // 2^32: any tile element, and any tile of up to 2^16
+  uint32_t rmul[kTileDims], wmul[kTileDims], omul[64];
+  static uint32_t reciprocal(uint32_t ext) { return static_cast<uint32_t>(((uint64_t{1} << 32) + ext - 1) / ext); }
   static __host__ __device__ int32_t pad(int64_t x) { return static_cast<int32_t>(x + (x >> 5)); }
   __host__ __device__ void read_entry(uint32_t x, int32_t& in, int32_t& slot) const {
     slot = pad(x);
@@ -170,6 +174,10 @@ struct PermuteShape {
   size_t bytes() const { return tiled ? offset(6) : 0; }
 };
 hipError_t launch_permute_tables(const PermuteShape& p, char* tables, hipStream_t s);
+// The permutation in one launch, its offsets worked out by every workgroup
+// from the digits; for shapes that permute_direct allows.
+bool permute_direct(const PermuteShape& p);
+hipError_t launch_permute_direct(const PermuteShape& p, const float2* in, float2* out, hipStream_t s);
 
 // Plain gather: out[w] = in[base + sum_d digit_d(w) * in_stride[d]] over
 // row-major output dims (any shape; used for small tensors).

@@ -260,6 +260,8 @@ static PermuteShape tile_shape(const std::vector<int64_t>& ext0, const std::vect
     P.wext[q] = static_cast<uint32_t>(ext[e]);
     P.wout[q] = static_cast<int32_t>(ost[e]);
     P.wpos[q] = static_cast<int32_t>(rstride[e]);
+    P.rmul[q] = PermuteShape::reciprocal(P.rext[q]);
+    P.wmul[q] = PermuteShape::reciprocal(P.wext[q]);
   }
   // outer dims (not in the tile), output order; split into lo (inner) and hi
   std::vector<int> outer;
@@ -292,6 +294,7 @@ static PermuteShape tile_shape(const std::vector<int64_t>& ext0, const std::vect
   P.pairs = pairs ? 1 : 0;
   for (int q = 0; q < P.n_outer; ++q) {
     P.oext[q] = static_cast<uint32_t>(ext[outer[q]]);
+    P.omul[q] = PermuteShape::reciprocal(P.oext[q]);
     P.oin[q] = st[outer[q]];
     P.oout[q] = ost[outer[q]];
   }
