@@ -41,7 +41,7 @@ bool runs_4m(int prec, int form) { return prec == TNC_PREC_C64 || form == TNC_GE
 // Ranking of the variants by measured per-tile throughput on large shapes.
 const std::vector<int>& ranking(tnc_prec prec, tnc_cgemm form) {
   static const std::vector<int> r4m = {3, 2, 0, 1, 4, 5, 6, kDirect64x32, kDirect32x32, kDirect32x16};
-  static const std::vector<int> r3m = {0, 2, 4, 1, 5, 6};
+  static const std::vector<int> r3m = {2, 0, 1, 4, 5, 6};
   return runs_4m(prec, form) ? r4m : r3m;
 }
 
@@ -57,6 +57,19 @@ std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m,
 
 }  // namespace
 
+// Split 3M: 128 x 128 where it has two tiles per CU and little padding (16 x
+// 1024 x 512 x 768 159 us on 128 x 64, 142 so; 200 x 90 x 100 x 300, which has
+// 200 tiles, 35.6, 38.4), else 128 x 64 unless it pads a quarter away that a
+// small tile with enough workgroups does not.  (64 x 64, the choice below
+// 1024 tiles before: 16 x 1024 x 256 x 1024 as a pair 212 us, now 143.)
+static int default_variant_3m(int64_t h, int64_t m, int64_t n) {
+  if (tiles_for(2, h, m, n) >= 512 && padding_waste(2, m, n) <= 0.125) return 2;
+  if (padding_waste(0, m, n) > 0.25)
+    for (int v : {4, 5, 6})
+      if (tiles_for(v, h, m, n) >= 1024 && padding_waste(v, m, n) <= 0.125) return v;
+  return 0;
+}
+
 // 4M kernels.  With few tiles the shapes that share K out: the largest of
 // them that still has no more than one workgroup per CU (us per launch,
 // 128 x 64 tile before and the chosen shape: 256 x 256 x 256 26.6, 7.0;
@@ -67,15 +80,16 @@ std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m,
 // workgroups fill 256 CUs, and how well one CU's waves hide each other's
 // latency (fewer than two per SIMD do not: 2 x 4096 x 256 x 128 runs 20.5 us
 // on 256 workgroups of four waves, 28.0 on 512 of two, 24.8 on 128 of eight).
-static int default_variant_4m(tnc_prec prec, int64_t h, int64_t m, int64_t n) {
+int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n) {
+  if (!runs_4m(prec, form)) return default_variant_3m(h, m, n);
   const int64_t few = tiles_for(kDirect32x16, h, m, n);
   if (few <= 256) return kDirect32x16;
   if (few <= 512) return kDirect32x32;
   if (few <= 1024) return kDirect64x32;
   // (8192 x 8192 x 4096 in complex64, 64 x 1024 x 256 x 1024 in split precision)
   static const double c64[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};
-  static const double bf16x3[kGemmVariants] = {0.83, 0.87, 0.875, 1.0, 0.70, 0.52, 0.495};
-  const double* rate = prec == TNC_PREC_BF16X3 ? bf16x3 : c64;
+  static const double split[kGemmVariants] = {0.83, 0.87, 0.875, 1.0, 0.70, 0.52, 0.495};
+  const double* rate = prec == TNC_PREC_BF16X3 ? split : c64;
   static const int waves[kGemmVariants] = {4, 4, 8, 8, 2, 2, 1};
   int best = 4;
   double top = 0.0;
@@ -90,15 +104,6 @@ static int default_variant_4m(tnc_prec prec, int64_t h, int64_t m, int64_t n) {
     }
   }
   return best;
-}
-
-int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n) {
-  if (runs_4m(prec, form)) return default_variant_4m(prec, h, m, n);
-  // the best-ranked shape that still gives every CU a few tiles and wastes
-  // little on padding; small problems fall through to the small shapes
-  for (int v : ranking(prec, form))
-    if (tiles_for(v, h, m, n) >= 4 * 256 && padding_waste(v, m, n) <= 0.125) return v;
-  return 4;
 }
 
 std::string TuneKey::str() const {
