@@ -286,7 +286,7 @@ struct Server {
           // network here, before any waiter returns
           for (auto& q : job) q->batcher.reset();
         }
-        waiting = !queue.empty();  // what this job held may admit any of them
+        waiting = stop || !queue.empty();  // what this job held may admit any of them
         const Clock::time_point now = Clock::now();
         for (auto& q : job) {
           q->t_done = now;
