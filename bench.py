@@ -38,16 +38,18 @@ sys.path.insert(0, ROOT)
 PEAK_FP32_MFMA = 157.3   # TFLOP/s, MI355X dense FP32 matrix
 PEAK_HBM_TBS = 8.0       # TB/s, MI355X HBM3E
 PEAK_BF16_MFMA = 2516.6  # TFLOP/s, MI355X dense bf16 matrix
+PEAK_C64 = PEAK_BF16_MFMA / 6    # complex64: six bf16 products per real product (an exact three-way split)
+PEAK_SPLIT = PEAK_BF16_MFMA / 3  # split precision: three
 PEAK_HBM = 8000.0        # GB/s
 
-# Memory-side traffic per launch of the dominant kernel (4M GEMM, 4x4-wave
-# tiles, the 2^30-output contraction), from rocprofv3 --pmc FETCH_SIZE
-# (371,296,253 KiB, x2.0) and WRITE_SIZE (8,388,609 KiB, x1.0); the factors
-# are what the same counters read for a 4 GiB device copy.  FETCH_SIZE counts
-# every L2 miss (served by the memory-side cache or HBM): with k = 2^14 the
-# A/B panels of the tiles running at once are re-read per K stage.  Set to
+# Memory-side traffic per launch of the dominant kernel (complex64 4M GEMM,
+# 256 x 128 complex tiles, the 2^30-output contraction), from rocprofv3 --pmc
+# FETCH_SIZE (573,869,720 KiB, x2.0) and WRITE_SIZE (8,388,608 KiB, x1.0); the
+# factors are what the same counters read for a 4 GiB device copy.  FETCH_SIZE
+# counts every L2 miss (served by the memory-side cache or HBM): with k = 2^14
+# the A/B panels of the tiles running at once are re-read per K stage.  Set to
 # None when the kernel changes.
-GEMM_TRAFFIC_BYTES = 769.0e9
+GEMM_TRAFFIC_BYTES = 1184.0e9
 
 
 def path_roofline_s(tnc, plan, n_runs: int = 1, leaf_permutes: bool = True, split: bool = False,
@@ -56,15 +58,15 @@ def path_roofline_s(tnc, plan, n_runs: int = 1, leaf_permutes: bool = True, spli
     device batch at max(its algorithmic bytes 8 (hA m k + hB n k + h m n) /
     8 TB/s, its MFMA work / the precision's peak), plus the leaf permutes at
     16 bytes per element / 8 TB/s; times the number of batches run.  MFMA
-    work: 8 h m n k FLOP (6 h m n k executed in the 3M form) at 157.3
-    TFLOP/s, or at 2516.6 / 3 for split precision (three bf16 products per
-    real product)."""
+    work: 8 h m n k FLOP (6 h m n k executed in split precision's 3M form;
+    complex64 runs 4M in either) at the bf16 peak over the bf16 products per
+    real product: 2516.6 / 6 TFLOP/s, / 3 for split precision."""
     info = tnc.tnc_plan_get_info(plan.handle)
-    peak = (PEAK_BF16_MFMA / 3 if split else PEAK_FP32_MFMA) * 1e12
+    peak = (PEAK_SPLIT if split else PEAK_C64) * 1e12
     t = 0.0
     for s in range(info.n_steps):
         st = tnc.tnc_plan_get_batch_step(plan.handle, s)
-        fl = (6.0 if three_m else 8.0) * st.h * st.m * st.n * st.k
+        fl = (6.0 if three_m and split else 8.0) * st.h * st.m * st.n * st.k
         by = 8.0 * (st.hA * st.m * st.k + st.hB * st.n * st.k + st.h * st.m * st.n)
         t += max(by / (PEAK_HBM_TBS * 1e12), fl / peak)
     if leaf_permutes:
@@ -557,10 +559,10 @@ def dominant_step(tnc, plan, split: bool = False, three_m: bool = False):
     """The step with the most profiled kernel time (profiling on, a run just
     done): its algorithmic bytes 8 (hA m k + hB n k + h m n) and FLOPs
     8 h m n k per batch, what bounds it at MI355X peaks (HBM 8 TB/s; MFMA:
-    FP32 157.3 TFLOP/s, or bf16 2516.6 / 3 for split precision, three bf16
-    products per real product) and the achieved fraction of that bound; for
-    the 3M form also the fraction in executed MFMA work (6 of the 8 FLOPs
-    per complex MAC)."""
+    bf16 2516.6 TFLOP/s over the bf16 products per real product, six in
+    complex64 and three in split precision) and the achieved fraction of that
+    bound; for split precision's 3M form also the fraction in executed MFMA
+    work (6 of the 8 FLOPs per complex MAC)."""
     info = tnc.tnc_plan_get_info(plan.handle)
     best = None
     for s in range(info.n_steps):
@@ -574,7 +576,7 @@ def dominant_step(tnc, plan, split: bool = False, three_m: bool = False):
     per = ms / cnt * 1e-3
     fl = 8.0 * st.h * st.m * st.n * st.k
     by = 8.0 * (st.hA * st.m * st.k + st.hB * st.n * st.k + st.h * st.m * st.n)
-    peak_mfma = PEAK_BF16_MFMA / 3 if split else PEAK_FP32_MFMA
+    peak_mfma = PEAK_SPLIT if split else PEAK_C64
     mfma = fl / (peak_mfma * 1e12) >= by / (PEAK_HBM_TBS * 1e12)
     achieved = fl / per / 1e12 if mfma else by / per / 1e9
     peak = peak_mfma if mfma else PEAK_HBM
@@ -582,7 +584,7 @@ def dominant_step(tnc, plan, split: bool = False, three_m: bool = False):
            "ms_per_launch": round(per * 1e3, 4), "launches": cnt, "bound": "mfma" if mfma else "hbm",
            "achieved": round(achieved, 3), "peak": round(peak, 1), "unit": "TFLOP/s" if mfma else "GB/s",
            "frac": round(achieved / peak, 4)}
-    if mfma and three_m:
+    if mfma and three_m and split:
         rec["frac_executed"] = round(achieved * 6 / 8 / peak, 4)
     return rec
 
@@ -1018,7 +1020,7 @@ def main():
     bperm_ms, bperm_n = tnc.tnc_plan_get_profile(plan_b.handle, -1)
     gemm_avg_s = gemm_ms / max(gemm_n, 1) / 1e3
     achieved = plan_a.info.flops_per_slice / gemm_avg_s / 1e12
-    peak = PEAK_BF16_MFMA / 3 if prec == tnc.PREC_BF16X3 else PEAK_FP32_MFMA
+    peak = PEAK_SPLIT if prec == tnc.PREC_BF16X3 else PEAK_C64
     value = flops_step * args.steps / dt / 1e12
     perm_bytes = plan_a.info.transpose_bytes
     perm_gbs = perm_bytes / (perm_ms / max(perm_n, 1) * 2 / 1e3) / 1e9 if perm_n else None
@@ -1051,7 +1053,7 @@ def main():
                      "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "traffic": GEMM_TRAFFIC_BYTES},
         "measured_ceilings": {"fp32_mfma_tflops": round(hw.flops_per_s / 1e12, 2),
                               "copy_gbs": round(hw.hbm_bytes_per_s / 1e9, 1),
-                              "gemm_frac_of_measured_mfma": round(achieved / (hw.flops_per_s / 1e12), 4),
+                              "gemm_over_measured_fp32_mfma": round(achieved / (hw.flops_per_s / 1e12), 4),
                               "permute_frac_of_measured_copy": round(perm_gbs / (hw.hbm_bytes_per_s / 1e9), 4)
                               if perm_gbs else None},
         "kernels": {"gemm_ms": round(gemm_avg_s * 1e3, 3),
@@ -1072,9 +1074,9 @@ def main():
     if not args.no_forms and args.form == "4M" and args.prec == "c64":
         # the same step in the other GEMM forms (same inputs, same arena)
         res["other_forms"] = {}
-        for name, fprec, fform, fpeak in (("3M", tnc.PREC_C64, tnc.GEMM_3M, PEAK_FP32_MFMA),
-                                          ("bf16x3", tnc.PREC_BF16X3, tnc.GEMM_4M, PEAK_BF16_MFMA / 3),
-                                          ("bf16x3_3M", tnc.PREC_BF16X3, tnc.GEMM_3M, PEAK_BF16_MFMA / 3)):
+        for name, fprec, fform, fpeak in (("3M", tnc.PREC_C64, tnc.GEMM_3M, PEAK_C64),
+                                          ("bf16x3", tnc.PREC_BF16X3, tnc.GEMM_4M, PEAK_SPLIT),
+                                          ("bf16x3_3M", tnc.PREC_BF16X3, tnc.GEMM_3M, PEAK_SPLIT)):
             pa = tnc.Plan(tn_a, path_a.pairs, (), fprec, fform)
             pb = tnc.Plan(tn_b, path_b.pairs, (), fprec, fform)
             tnc.tnc_plan_autotune(pa.handle)
@@ -1095,15 +1097,15 @@ def main():
             g_ms, g_n = tnc.tnc_plan_get_profile(pa.handle, 0)
             g_s = g_ms / max(g_n, 1) / 1e3
             gt = plan_a.info.flops_per_slice / g_s / 1e12
-            # executed MFMA work against its own peak: the 3M forms execute
-            # 6 of the 8 FLOPs per complex MAC, split-bf16x3 three bf16
-            # products per real product (peak / 3 in the 8-FLOP convention)
-            executed = gt * (6 / 8 if fform == tnc.GEMM_3M else 1.0) / fpeak
+            # executed MFMA work against its own peak: split precision's 3M
+            # form executes 6 of the 8 FLOPs per complex MAC; complex64
+            # computes 4M under either name
+            executed = gt * (6 / 8 if fform == tnc.GEMM_3M and fprec == tnc.PREC_BF16X3 else 1.0) / fpeak
             res["other_forms"][name] = {
                 "tflops": round(flops_step / fdt / 1e12, 3), "ms_per_step": round(fdt * 1e3, 3),
                 "gemm_tflops": round(gt, 3), "gemm_frac_of_executed_mfma_peak": round(executed, 4),
-                # the 8-FLOP complex convention against the form's precision
-                # peak (FP32 MFMA, or bf16 MFMA / 3 for split precision)
+                # the 8-FLOP complex convention against the precision's peak
+                # (bf16 MFMA / 6, or / 3 for split precision)
                 "gemm_frac_of_peak_8flop": round(gt / fpeak, 4),
                 "variant": tnc.tnc_plan_get_step(pa.handle, 0).variant,
                 "presplit": bool(tnc.tnc_plan_get_step(pa.handle, 0).presplit)}
