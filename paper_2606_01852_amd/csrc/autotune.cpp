@@ -57,13 +57,19 @@ std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m,
 
 }  // namespace
 
-// Split 3M: 128 x 128 where it has two tiles per CU and little padding (16 x
-// 1024 x 512 x 768 159 us on 128 x 64, 142 so; 200 x 90 x 100 x 300, which has
-// 200 tiles, 35.6, 38.4), else 128 x 64 unless it pads a quarter away that a
-// small tile with enough workgroups does not.  (64 x 64, the choice below
-// 1024 tiles before: 16 x 1024 x 256 x 1024 as a pair 212 us, now 143.)
+// Split 3M: 128 x 128 where it has two tiles per CU, little padding and fills
+// its last round about as well as 128 x 64, which is 7 % slower per product
+// (16 x 1024 x 512 x 768 159 us on 128 x 64, 142 so; 200 x 90 x 100 x 300, which
+// has 200 tiles, 35.6, 38.4; 13 x 356 x 1918 x 2194, 585 tiles in three rounds,
+// 606, 637), else 128 x 64 unless it pads a quarter away that a small tile with
+// enough workgroups does not.  (64 x 64, the choice below 1024 tiles before:
+// 16 x 1024 x 256 x 1024 as a pair 212 us, now 143.)
 static int default_variant_3m(int64_t h, int64_t m, int64_t n) {
-  if (tiles_for(2, h, m, n) >= 512 && padding_waste(2, m, n) <= 0.125) return 2;
+  auto full = [&](int v) {  // the share of the rounds that is work
+    const int64_t t = tiles_for(v, h, m, n), q = (t + 255) / 256;
+    return (1.0 - padding_waste(v, m, n)) * static_cast<double>(t) / (256.0 * q);
+  };
+  if (tiles_for(2, h, m, n) >= 512 && padding_waste(2, m, n) <= 0.125 && full(2) > 0.935 * full(0)) return 2;
   if (padding_waste(0, m, n) > 0.25)
     for (int v : {4, 5, 6})
       if (tiles_for(v, h, m, n) >= 1024 && padding_waste(v, m, n) <= 0.125) return v;
