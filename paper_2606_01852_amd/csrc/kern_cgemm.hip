@@ -445,19 +445,25 @@ __device__ __forceinline__ void ps_read(const char* stage, int wm, int wn, int h
   }
 }
 
-// Per block a_hi b_lo, a_lo b_hi, a_hi b_hi, into one accumulator.
+// Per block a_hi b_lo, a_lo b_hi, a_hi b_hi, into one accumulator.  The two
+// blocks of a column take turns so that five of six neighbours share an
+// operand, which the chip's power budget feels (block by block two of six: 16384
+// x 8192 x 8192 20.45 -> 20.29 ms, in the 3M form 15.78 -> 15.65).
 __device__ __forceinline__ void ps_mfma(f16v (&acc)[2][4], const PsFrag& f) {
+  auto mm = [&](int i, int j, const s8v& a, const s8v& b) {
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b),
+                                                        acc[i][j], 0, 0, 0);
+  };
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, f.ah[i]),
-                                                          __builtin_bit_cast(bf8, f.bl[j]), acc[i][j], 0, 0, 0);
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, f.al[i]),
-                                                          __builtin_bit_cast(bf8, f.bh[j]), acc[i][j], 0, 0, 0);
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, f.ah[i]),
-                                                          __builtin_bit_cast(bf8, f.bh[j]), acc[i][j], 0, 0, 0);
-    }
+  for (int j = 0; j < 4; ++j) {
+    const int p = j & 1, q = p ^ 1;
+    mm(p, j, f.ah[p], f.bl[j]);
+    mm(q, j, f.ah[q], f.bl[j]);
+    mm(q, j, f.al[q], f.bh[j]);
+    mm(p, j, f.al[p], f.bh[j]);
+    mm(p, j, f.ah[p], f.bh[j]);
+    mm(q, j, f.ah[q], f.bh[j]);
+  }
 }
 
 // Stage kk's blocks of the tile into LDS buffer `buf`: 64 wave-loads of 1
