@@ -76,11 +76,14 @@ static int default_variant_3m(int64_t h, int64_t m, int64_t n) {
   return 0;
 }
 
-// 4M kernels.  With few tiles the shapes that share K out: the largest of
-// them that still has no more than one workgroup per CU (us per launch,
+// 4M kernels.  With few tiles the shapes that share K out (us per launch,
 // 128 x 64 tile before and the chosen shape: 256 x 256 x 256 26.6, 7.0;
 // 512 x 512 x 512 47, 14.6; 8 x 1024 x 64 x 128 17.3, 10.7; from 2048
-// 32 x 16 tiles on the tiles win: 1024 x 1024 x 64 12.5, 13.4).  Else the
+// 32 x 16 tiles on the tiles win: 1024 x 1024 x 64 12.5, 13.4), the one with
+// the least rounds, weighed by what a round takes (1 x 1000 x 500 x 200: 1024
+// tiles of 32 x 16, two to a CU, 15.9; 512 of 32 x 32 15.7; 256 of 64 x 32
+// 12.4; where 64 x 32 pads into a second round, 3 x 138 x 1067 x 79: 12.1, 11.9,
+// 15.2).  Else the
 // tile with the largest product of what it reaches on large shapes (relative
 // to 256 x 128), the share of it that is not padding, how evenly its
 // workgroups fill 256 CUs, and how well one CU's waves hide each other's
@@ -90,8 +93,11 @@ int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t
   if (!runs_4m(prec, form)) return default_variant_3m(h, m, n);
   const int64_t few = tiles_for(kDirect32x16, h, m, n);
   if (few <= 256) return kDirect32x16;
-  if (few <= 512) return kDirect32x32;
-  if (few <= 1024) return kDirect64x32;
+  if (few <= 1024) {
+    auto rounds = [&](int v, int64_t at_once) { return static_cast<double>((tiles_for(v, h, m, n) + at_once - 1) / at_once); };
+    const double t7 = 1.2 * rounds(kDirect32x16, 512), t8 = rounds(kDirect32x32, 256), t9 = 1.4 * rounds(kDirect64x32, 256);
+    return t9 <= t8 && t9 <= t7 ? kDirect64x32 : t8 <= t7 ? kDirect32x32 : kDirect32x16;
+  }
   // (8192 x 8192 x 4096 in complex64, 64 x 1024 x 256 x 1024 in split precision)
   static const double c64[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};
   static const double split[kGemmVariants] = {0.83, 0.87, 0.875, 1.0, 0.70, 0.52, 0.495};
