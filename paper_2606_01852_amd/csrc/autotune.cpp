@@ -108,7 +108,7 @@ int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t
   for (int v : {3, 2, 0, 1, 4, 5, 6}) {
     const int64_t t = tiles_for(v, h, m, n), q = (t + 255) / 256;
     const int64_t w = q * waves[v];
-    const double hide = w >= 8 ? 1.0 : w >= 4 ? 0.58 : w >= 2 ? 0.35 : 0.2;
+    const double hide = w >= 8 ? 1.0 : w >= 4 ? 0.58 : w >= 2 ? 0.32 : 0.2;
     const double e = rate[v] * (1.0 - padding_waste(v, m, n)) * (static_cast<double>(t) / (256.0 * q)) * hide;
     if (e > 1.01 * top) {
       top = e;
