@@ -676,13 +676,15 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
       const int64_t t0 = sp.h * ((sp.lm + 127) / 128) * ((sp.ln + 63) / 64);
       // parts of at least 128 complex; a long K on few tiles is a long serial
       // loop on few CUs, whatever the step's size.  Where the 4M kernels
-      // share K out inside their workgroups (default_variant: up to 512
-      // tiles of 32 x 16 here), the epilogue's launch costs more below 512
-      // than the cut gains (256 x 256 x 256 in two parts 6.3 + 4.7 us, whole
-      // 7.0; 4096 x 256 x 256, which has 2048: 20.5 + 6.9 and 32 stages in
-      // sequence)
+      // share K out inside their workgroups (default_variant: up to 1024 tiles
+      // of 32 x 16), the epilogue's launch costs more below 512 than the cut
+      // gains (256 x 256 x 256 in two parts 6.3 + 4.7 us, whole 7.0; 4 x 512 x
+      // 256 x 256 as a pair 24.3, whole 14.8); in split precision, whose
+      // stages are shorter, up to 2048 (4096 x 256 x 256 25.1, whole 18.4; in
+      // complex64 that is 26 to 30 either way, with the store's order)
       const bool shared = (plan.prec == TNC_PREC_C64 || plan.form == TNC_GEMM_4M) &&
-                          sp.h * ((sp.lm + 31) / 32) * ((sp.ln + 15) / 16) <= 512;
+                          sp.h * ((sp.lm + 31) / 32) * ((sp.ln + 15) / 16) <=
+                              (plan.prec == TNC_PREC_C64 ? 1024 : 2048);
       if (t0 < 512 && sp.k >= (shared ? 512 : 256))
         while (t0 * S * 2 <= 2048 && sp.k / (S * 2) >= 128 && sp.k % (16 * S * 2) == 0) S *= 2;
     } else if (sp.kind == GemmKernel::DOT) {
