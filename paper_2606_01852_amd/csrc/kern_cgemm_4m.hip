@@ -466,6 +466,7 @@ struct XDirect {
   static constexpr int REGS = 16 * BI * BJ;                  // sums per lane
   static constexpr size_t kLds = size_t{W} * REGS * 64 * 4;  // one wave's sums after the other's
   static constexpr int N = REGS / W;                         // of them, added up and stored by one wave
+  static_assert(W <= 8, "sums below 2^124 add up to a finite one");
   static_assert(N >= 1 && N <= 16 && 16 % N == 0, "a wave stores part of one block");
 
   f4 x[BI][2], y[BJ][2];  // this lane's four complex values of its rows of A and columns of B
@@ -527,7 +528,7 @@ struct XDirect {
       pb[j] = d.B + uniform(ob) + (col < d.n ? col : d.n - 1) * ld;
     }
     uint32_t tiny = 0xFFFFFFFFu;
-    f16v acc[BI][BJ] = {};
+    f16v acc[BI][BJ];
     auto load_stage = [&](int64_t st) {
       const int64_t l = st * XK + 4 * h;
       if ((st + 1) * XK <= k)
@@ -536,53 +537,76 @@ struct XDirect {
         load<true>(pa, pb, l, k);
     };
     const int64_t nk = (k + XK - 1) / XK;
-    if (wave < nk) load_stage(wave);
-    for (int64_t st = wave; st < nk; st += W) {
-      s8v fa[BI][PARTS], fb[BJ][PARTS];
-#pragma unroll
-      for (int i = 0; i < BI; ++i) split(x[i], fa[i], tiny);
-#pragma unroll
-      for (int j = 0; j < BJ; ++j) {
-        f4 z[2];  // B': (br, -bi) for even real columns, (bi, br) for odd ones
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          z[e].x = odd ? y[j][e].y : y[j][e].x;
-          z[e].y = odd ? y[j][e].x : -y[j][e].y;
-          z[e].z = odd ? y[j][e].w : y[j][e].z;
-          z[e].w = odd ? y[j][e].z : -y[j][e].w;
-        }
-        split(z, fb[j], tiny);
-      }
-      if (st + W < nk) load_stage(st + W);
-      f16v c[BI][BJ] = {};
-#pragma unroll
-      for (int q = 0; q < (PARTS == 3 ? 6 : 3); ++q)
-#pragma unroll
-        for (int j = 0; j < BJ; ++j)
-#pragma unroll
-          for (int i = 0; i < BI; ++i)
-            c[i][j] = PARTS == 3 ? mm(fa[i][kPartA[q]], fb[j][kPartB[q]], c[i][j])
-                                 : mm(fa[i][kSplitA[q]], fb[j][kSplitB[q]], c[i][j]);
+    // the sum of the stages first, first + stride, ...
+    auto add_up = [&](int64_t first, auto stride) {
 #pragma unroll
       for (int i = 0; i < BI; ++i)
 #pragma unroll
-        for (int j = 0; j < BJ; ++j) acc[i][j] += c[i][j];
-    }
-    float s = 0.f;  // NaN if any sum is not finite
-    float* mine = reinterpret_cast<float*>(lds) + wave * REGS * 64 + lane;
+        for (int j = 0; j < BJ; ++j) acc[i][j] = f16v{};
+      if (first < nk) load_stage(first);
+      for (int64_t st = first; st < nk; st += stride) {
+        s8v fa[BI][PARTS], fb[BJ][PARTS];
 #pragma unroll
-    for (int i = 0; i < BI; ++i)
+        for (int i = 0; i < BI; ++i) split(x[i], fa[i], tiny);
 #pragma unroll
-      for (int j = 0; j < BJ; ++j)
+        for (int j = 0; j < BJ; ++j) {
+          f4 z[2];  // B': (br, -bi) for even real columns, (bi, br) for odd ones
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          s = fmaf(acc[i][j][v], 0.f, s);
-          mine[(16 * (i * BJ + j) + v) * 64] = acc[i][j][v];
+          for (int e = 0; e < 2; ++e) {
+            z[e].x = odd ? y[j][e].y : y[j][e].x;
+            z[e].y = odd ? y[j][e].x : -y[j][e].y;
+            z[e].z = odd ? y[j][e].w : y[j][e].z;
+            z[e].w = odd ? y[j][e].z : -y[j][e].w;
+          }
+          split(z, fb[j], tiny);
         }
+        if (st + stride < nk) load_stage(st + stride);
+        f16v c[BI][BJ] = {};
+#pragma unroll
+        for (int q = 0; q < (PARTS == 3 ? 6 : 3); ++q)
+#pragma unroll
+          for (int j = 0; j < BJ; ++j)
+#pragma unroll
+            for (int i = 0; i < BI; ++i)
+              c[i][j] = PARTS == 3 ? mm(fa[i][kPartA[q]], fb[j][kPartB[q]], c[i][j])
+                                   : mm(fa[i][kSplitA[q]], fb[j][kSplitB[q]], c[i][j]);
+#pragma unroll
+        for (int i = 0; i < BI; ++i)
+#pragma unroll
+          for (int j = 0; j < BJ; ++j) acc[i][j] += c[i][j];
+      }
+    };
+    // the wave's sums to LDS; true if one of them is 2^124 or above: not
+    // finite, or so large that the waves' sums, which follow K's order only
+    // inside a wave, might not add up to one that is
+    auto put = [&]() {
+      uint32_t top[4] = {0, 0, 0, 0};  // twice the bits of the largest (a NaN's are above any other)
+      float* mine = reinterpret_cast<float*>(lds) + wave * REGS * 64 + lane;
+#pragma unroll
+      for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int j = 0; j < BJ; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const uint32_t t = __float_as_uint(acc[i][j][v]) << 1;
+            top[v & 3] = top[v & 3] < t ? t : top[v & 3];
+            mine[(16 * (i * BJ + j) + v) * 64] = acc[i][j][v];
+          }
+#pragma unroll
+      for (int q = 1; q < 4; ++q) top[0] = top[0] < top[q] ? top[q] : top[0];
+      return top[0] >= (uint32_t{127 + 124} << 24);
+    };
+    add_up(wave, std::integral_constant<int, W>{});
     // (the vote is a barrier: every wave's sums are in LDS behind it)
-    if (__syncthreads_or(PARTS == 3 && (tiny < 0x00FFFFFFu || !(s == 0.f)))) {
-      if (wave < BI * BJ) fp32_block(d, tc.b, tc.row0 + 32 * (wave / BJ), tc.col0 + 16 * (wave % BJ), lane);
-      return;
+    const bool large = put();
+    if (__syncthreads_or(large || (PARTS == 3 && tiny < 0x00FFFFFFu))) {
+      if constexpr (PARTS == 3) {
+        if (wave < BI * BJ) fp32_block(d, tc.b, tc.row0 + 32 * (wave / BJ), tc.col0 + 16 * (wave % BJ), lane);
+        return;
+      }
+      add_up(wave ? nk : 0, std::integral_constant<int, 1>{});  // all of K in order, in one wave
+      (void)put();
+      __syncthreads();
     }
     const float* part = reinterpret_cast<const float*>(lds) + wave * N * 64 + lane;
     const int ij = wave * N / 16, v0 = wave * N & 15;

@@ -1,0 +1,59 @@
+"""GPU: 4M GEMMs over float32's whole range, on the tiles and on the shapes for
+few tiles.
+
+A sum whose partial sums in order stay finite is finite, however the kernel
+shares K out.
+"""
+import numpy as np
+import pytest
+
+from tests.gpu_util import from_dev, to_dev
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2606_01852_amd import tnc  # noqa: E402
+
+# by default: the shapes for few tiles (32 x 16, 32 x 32, 64 x 32 complex),
+# then tiles; k ends inside a stage of 8 in some
+FEW = [(1, 64, 32, 128), (10, 128, 128, 133), (20, 128, 128, 128)]
+TILED = [(v, (3, 300, 161, 137)) for v in range(7)]
+CALLS = [(-1, s) for s in FEW] + TILED
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = tnc.Context(0, arena_bytes=64 << 20)
+    yield c
+    c.close()
+
+
+def gemm(ctx, A, B, variant, prec=tnc.PREC_C64):
+    (h, m, k), n = A.shape, B.shape[1]
+    Ad, Bd = to_dev(torch, A), to_dev(torch, B)
+    Cd = torch.full((h, m, n, 2), float("nan"), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    tnc.tnc_ctx_set_gemm_variant(ctx.handle, variant)
+    try:
+        tnc.tnc_batched_cgemm(ctx.handle, h, m, n, k, Ad.data_ptr(), m * k, Bd.data_ptr(), n * k, Cd.data_ptr(),
+                              prec, tnc.GEMM_4M)
+        ctx.sync()
+    finally:
+        tnc.tnc_ctx_set_gemm_variant(ctx.handle, -1)
+    return from_dev(Cd).reshape(h, m, n, 2)
+
+
+@pytest.mark.parametrize("prec", [tnc.PREC_C64, tnc.PREC_BF16X3], ids=["c64", "bf16x3"])
+@pytest.mark.parametrize("variant, shape", CALLS, ids=str)
+def test_partial_sums_stay_finite(ctx, variant, shape, prec):
+    """+a +a . -a -a +a +a . +a -a -a over sixteen stages of eight k, a = 2^126:
+    in order never above 3 a, but a sum over the stages 0, 8, 1, 9 alone is
+    4 a, which no float32 holds."""
+    h, m, n, _ = shape
+    A, B = np.zeros((h, m, 128), np.complex64), np.ones((h, n, 128), np.complex64)
+    for stage, sign in ((0, 1), (1, 1), (6, -1), (7, -1), (8, 1), (9, 1), (12, 1), (14, -1), (15, -1)):
+        A[:, :, 8 * stage] = sign * 2.0 ** 63
+    B *= np.float32(2.0 ** 63)
+    print(variant, shape, flush=True)
+    got = gemm(ctx, A, B, variant, prec)
+    assert np.all(got[..., 0] == np.float32(2.0 ** 126)) and not np.any(got[..., 1])
