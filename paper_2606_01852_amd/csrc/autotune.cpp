@@ -89,7 +89,11 @@ static int default_variant_3m(int64_t h, int64_t m, int64_t n) {
 // workgroups fill 256 CUs, and how well one CU's waves hide each other's
 // latency (fewer than two per SIMD do not: 2 x 4096 x 256 x 128 runs 20.5 us
 // on 256 workgroups of four waves, 28.0 on 512 of two, 24.8 on 128 of eight).
-int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n) {
+// Split precision's 256 x 128 tile (3) has one sum for all three products
+// where the others keep the cross products apart (error against 64 bits at
+// k = 1024, 4096, 16384: 1.005, 1.02 and 1.08 times theirs), so nobody gets it
+// unasked except planned steps that give every CU four tiles of it.
+int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n, bool planned) {
   if (!runs_4m(prec, form)) return default_variant_3m(h, m, n);
   const int64_t few = tiles_for(kDirect32x16, h, m, n);
   if (few <= 256) return kDirect32x16;
@@ -100,13 +104,14 @@ int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t
   }
   // (8192 x 8192 x 4096 in complex64, 64 x 1024 x 256 x 1024 in split precision)
   static const double c64[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};
-  static const double split[kGemmVariants] = {0.83, 0.87, 0.875, 1.0, 0.70, 0.52, 0.495};
+  static const double split[kGemmVariants] = {0.83, 0.86, 0.875, 1.0, 0.70, 0.52, 0.495};
   const double* rate = prec == TNC_PREC_BF16X3 ? split : c64;
   static const int waves[kGemmVariants] = {4, 4, 8, 8, 2, 2, 1};
   int best = 4;
   double top = 0.0;
   for (int v : {3, 2, 0, 1, 4, 5, 6}) {
     const int64_t t = tiles_for(v, h, m, n), q = (t + 255) / 256;
+    if (v == 3 && prec == TNC_PREC_BF16X3 && !(planned && t >= 1024 && padding_waste(v, m, n) <= 0.125)) continue;
     const int64_t w = q * waves[v];
     const double hide = w >= 8 ? 1.0 : w >= 4 ? 0.58 : w >= 2 ? 0.32 : 0.2;
     const double e = rate[v] * (1.0 - padding_waste(v, m, n)) * (static_cast<double>(t) / (256.0 * q)) * hide;
@@ -258,7 +263,7 @@ void assign_variants(const Plan& plan, ChunkPlan& cp, bool tune) {
     if (tune && !c.host_only)
       sp.variant = tune_shape(c, key, d.k, perm);
     else
-      sp.variant = default_variant(plan.prec, plan.form, d.h, d.m, d.n);
+      sp.variant = default_variant(plan.prec, plan.form, d.h, d.m, d.n, true);
   }
   summarize_steps(cp);
 }

@@ -39,8 +39,8 @@
 // complex64 in the 3M form runs here as well: 16 x 1024 x 512 x 768 312 us
 // on the FP32 pipe with three products, 243 here, at 0.3 of the error.
 //
-// Split precision (hi and lo, three products hi lo, lo hi, hi hi added to one
-// accumulator, in waves of one column block the first two to a second one)
+// Split precision (hi and lo, three products hi lo, lo hi, hi hi, the first two
+// added to an accumulator of their own, in the 256 x 128 tile all to one)
 // is the same tile with a part less and no FP32 pass: what the operands lose
 // is the format's own.  Bound by power too, 1275 executed bf16 TFLOP/s: 64 x
 // 1024 x 256 x 1024 0.390 -> 0.369 ms against tiles whose staging the
@@ -167,8 +167,11 @@ struct XTile {
 
   f16v acc[2][NJ];
   // three parts: sums of one stage, of the block at hand and of the one
-  // before; two parts on narrow waves: the cross products' sums
-  static constexpr bool CROSS = !EXACT && PW == 1;
+  // before; two parts: the cross products' sums, except in the 256 x 128 tile,
+  // whose eight wide waves have no registers for them (256 x 64 has four, one
+  // per SIMD)
+  static constexpr bool CROSS = !EXACT && !(PW == 2 && WM * WN > 4);
+  static constexpr int WAVES = CROSS && PW == 2 ? 1 : 2;  // per SIMD, at least
   f16v t[2][CROSS ? NJ : 1];
   f4 ra[AL], rb[BL];
   const float2 *pa[AL], *pb[BL];
@@ -402,8 +405,8 @@ struct XTile {
 };
 
 template <int PARTS, int WM, int WN, int PW, bool PERM>
-__global__ __launch_bounds__(64 * WM * WN, 2) void cgemm_4m(GemmDesc d, int64_t tiles_m, int64_t tiles_n,
-                                                            int64_t total) {
+__global__ __launch_bounds__(64 * WM * WN, (XTile<PARTS, WM, WN, PW>::WAVES)) void cgemm_4m(GemmDesc d, int64_t tiles_m,
+                                                                                   int64_t tiles_n, int64_t total) {
   using T = XTile<PARTS, WM, WN, PW>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
@@ -421,7 +424,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void cgemm_4m(GemmDesc d, int64_t 
 // in contiguous ranges (tiles of one entry stay on few XCDs, whose L2 they
 // share) and each workgroup of an XCD takes every nb-th tile of its range.
 template <int PARTS, int WM, int WN, int PW>
-__global__ __launch_bounds__(64 * WM * WN, WM * WN == 4 ? 2 : 1) void cgemm_4m_grouped(
+__global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4 ? XTile<PARTS, WM, WN, PW>::WAVES : 1)) void cgemm_4m_grouped(
     const GroupedEntry* __restrict__ tab, int n, int64_t total) {
   using T = XTile<PARTS, WM, WN, PW>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -759,7 +762,7 @@ template <int PARTS>
 void prepare_tiles() {
   prepare_shape<PARTS, 2, 2, 1>();
   prepare_shape<PARTS, 4, 1, 2>();
-  prepare_shape<PARTS, 2, 2, 2>();
+  if constexpr (PARTS == 3) prepare_shape<PARTS, 2, 2, 2>();
   prepare_shape<PARTS, 4, 2, 2>();
   prepare_shape<PARTS, 1, 2, 1>();
   prepare_shape<PARTS, 2, 1, 1>();
@@ -770,17 +773,14 @@ void prepare_tiles() {
   (void)ready_direct<PARTS, 8, 2, 2>();
 }
 
-// The 128 x 128 tile runs as four wide waves (each A fragment feeds four
-// column blocks: fewer LDS reads), or as eight narrow ones where a launch
+// complex64's 128 x 128 tile runs as four wide waves (each A fragment feeds
+// four column blocks: fewer LDS reads), or as eight narrow ones where a launch
 // has no more tiles than compute units: a CU then has two waves per SIMD
 // from its one workgroup instead of one (6 x 1000 x 500 x 777, 192 tiles:
 // 0.141 -> 0.125 ms; 8192 x 8192 x 4096, 4096 tiles: 10.3 -> 9.8 ms the
-// other way).  In complex64 an element's sums do not depend on which of them
-// ran; in split precision they do (CROSS), and it always runs the narrow.
-template <int PARTS>
-bool narrow_128(int64_t tiles) {
-  return PARTS == 2 || tiles <= 256;
-}
+// other way); an element's sums do not depend on which of them ran.  Split
+// precision's always runs as eight, which have registers for the cross sums.
+bool wide_128(int64_t tiles) { return tiles > 256; }
 
 template <int PARTS>
 hipError_t launch_tiles(const GemmDesc& d, int variant, hipStream_t s) {
@@ -788,8 +788,9 @@ hipError_t launch_tiles(const GemmDesc& d, int variant, hipStream_t s) {
     case 0: return launch_shape<PARTS, 2, 2, 1>(d, s);
     case 1: return launch_shape<PARTS, 4, 1, 2>(d, s);
     case 2:
-      if (narrow_128<PARTS>(d.h * ((d.m + 127) / 128) * ((d.n + 127) / 128))) return launch_shape<PARTS, 2, 4, 1>(d, s);
-      return launch_shape<PARTS, 2, 2, 2>(d, s);
+      if constexpr (PARTS == 3)
+        if (wide_128(d.h * ((d.m + 127) / 128) * ((d.n + 127) / 128))) return launch_shape<PARTS, 2, 2, 2>(d, s);
+      return launch_shape<PARTS, 2, 4, 1>(d, s);
     case 3: return launch_shape<PARTS, 4, 2, 2>(d, s);
     case 4: return launch_shape<PARTS, 1, 2, 1>(d, s);
     case 5: return launch_shape<PARTS, 2, 1, 1>(d, s);
@@ -807,8 +808,9 @@ hipError_t launch_tiles_grouped(const GroupedEntry* tab, int n, int64_t total, i
     case 0: return launch_grouped_shape<PARTS, 2, 2, 1>(tab, n, total, s);
     case 1: return launch_grouped_shape<PARTS, 4, 1, 2>(tab, n, total, s);
     case 2:
-      if (narrow_128<PARTS>(total)) return launch_grouped_shape<PARTS, 2, 4, 1>(tab, n, total, s);
-      return launch_grouped_shape<PARTS, 2, 2, 2>(tab, n, total, s);
+      if constexpr (PARTS == 3)
+        if (wide_128(total)) return launch_grouped_shape<PARTS, 2, 2, 2>(tab, n, total, s);
+      return launch_grouped_shape<PARTS, 2, 4, 1>(tab, n, total, s);
     case 3: return launch_grouped_shape<PARTS, 4, 2, 2>(tab, n, total, s);
     case 4: return launch_grouped_shape<PARTS, 1, 2, 1>(tab, n, total, s);
     case 5: return launch_grouped_shape<PARTS, 2, 1, 1>(tab, n, total, s);

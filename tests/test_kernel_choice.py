@@ -1,0 +1,38 @@
+"""Which kernel and tile a planned step gets (host-only plans)."""
+import numpy as np
+import pytest
+
+from paper_2606_01852_amd import tnc
+
+MFMA, SMALL = 0, 1
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = tnc.Context(-1, arena_bytes=64 << 30)
+    yield c
+    c.close()
+
+
+def step(ctx, h, m, n, k, prec, form):
+    """The one step of a batch of h products [m, k] x [k, n]."""
+    net = tnc.Network(ctx, [(0, 1, 3), (0, 2, 3)], np.array([h, m, n, k], dtype=np.int64), (0, 1, 2), None)
+    plan = tnc.Plan(net, [(0, 1)], (), prec, form)
+    s = tnc.tnc_plan_get_step(plan.handle, 0)
+    plan.close()
+    net.close()
+    return s
+
+
+@pytest.mark.parametrize("h, m, n, k", [(2, 2048, 2048, 512), (8, 1024, 1024, 256), (3, 2560, 1280, 300), (64, 500, 120, 777),
+                                        (40, 256, 128, 2000), (9, 1500, 2048, 700), (64, 1024, 512, 64), (2, 4096, 8192, 64)])
+def test_split_precision_keeps_two_sums_unless_it_had_one(ctx, h, m, n, k):
+    """The 256 x 128 tile (3), whose products share one sum, only where 1024
+    of it with little padding cover the step."""
+    s = step(ctx, h, m, n, k, tnc.PREC_BF16X3, tnc.GEMM_4M)
+    assert s.kernel == MFMA
+    rows, cols = (s.n, s.m) if s.swapped else (s.m, s.n)
+    tiles = s.h * -(-rows // 256) * -(-cols // 128)
+    full = rows * cols * s.h / (tiles * 256 * 128)
+    if s.variant == 3:
+        assert tiles >= 1024 and full >= 0.875
