@@ -857,13 +857,13 @@ tnc_status tnc_batched_cgemm(tnc_ctx ctx, int64_t h, int64_t m, int64_t n, int64
       d.bshift[0] = sh;
     }
   }
-  const GemmKernel kind = choose_gemm_kernel(h, m, n, k);
+  const Prec p = prec == TNC_PREC_BF16X3 ? Prec::BF16X3 : Prec::C64;
+  const Form f = form == TNC_GEMM_3M ? Form::M3 : Form::M4;
+  const GemmKernel kind = choose_gemm_kernel(h, m, n, k, shares_k(p, f));
   const int variant = c.gemm_variant >= 0
                           ? c.gemm_variant
                           : default_variant(static_cast<tnc_prec>(prec), static_cast<tnc_cgemm>(form), h, m, n, false);
-  check_hip(launch_gemm(d, kind, variant, form == TNC_GEMM_3M ? Form::M3 : Form::M4,
-                        prec == TNC_PREC_BF16X3 ? Prec::BF16X3 : Prec::C64, c.stream),
-            "gemm launch");
+  check_hip(launch_gemm(d, kind, variant, f, p, c.stream), "gemm launch");
   TNC_CATCH
 }
 

@@ -56,11 +56,13 @@ enum class GemmKernel : int { MFMA = 0, SMALL = 1, DOT = 2 };
 // stand-alone GEMM entry point).
 //  * MFMA for shapes that fill its 64 x 32 wave tiles, and for skinny shapes
 //    (m >= 16, n >= 8) with enough work (2^22 complex MACs, or 2^18 with a
-//    long K) that running MFMA on padded tiles still beats one thread per
-//    output;
+//    long K that the kernels share out, see share_k) that running MFMA on
+//    padded tiles still beats one thread per output;
 //  * DOT (one wave64 per output) for long reductions with few outputs;
 //  * SMALL (one thread per output) for the rest: tiny steps.
-inline GemmKernel choose_gemm_kernel(int64_t h, int64_t m, int64_t n, int64_t k) {
+// share_k: the 4M kernels are at hand, which have shapes whose waves share K
+// out (4M form, and complex64 in either).
+inline GemmKernel choose_gemm_kernel(int64_t h, int64_t m, int64_t n, int64_t k, bool share_k) {
   const int64_t tiles = ((m + 127) / 128) * ((n + 63) / 64) * h;
   const int64_t work = h * m * n * k;  // complex MACs
   if (k >= 16 && tiles < (int64_t{1} << 24)) {
@@ -70,12 +72,16 @@ inline GemmKernel choose_gemm_kernel(int64_t h, int64_t m, int64_t n, int64_t k)
     if (m >= 64 && n >= 32 && (work >= (int64_t{1} << 22) || k > 128)) return GemmKernel::MFMA;
     if (m >= 16 && n >= 8 && work >= (int64_t{1} << 22)) return GemmKernel::MFMA;
     // a long serial K on few outputs (16 x 256 x 256: 20.7 us one thread per
-    // output, 6.7 us on MFMA with K shared out)
-    if (m >= 16 && n >= 16 && k >= 128 && work >= (int64_t{1} << 18)) return GemmKernel::MFMA;
+    // output, 6.7 us on MFMA with K shared out; split precision's 3M tiles go
+    // through K alone and round more than one thread per output: 1.4 times
+    // the error)
+    if (share_k && m >= 16 && n >= 16 && k >= 128 && work >= (int64_t{1} << 18)) return GemmKernel::MFMA;
   }
   if (k >= 256 && m * n <= 64 && (h * m * n + 3) / 4 < 0x7FFFFF) return GemmKernel::DOT;
   return GemmKernel::SMALL;
 }
+
+inline bool shares_k(Prec prec, Form form) { return prec == Prec::C64 || form == Form::M4; }
 
 // Tiled gather-permute of complex64: out (contiguous) gets, for every tile
 // t < n_tiles and element e < T of the tile,

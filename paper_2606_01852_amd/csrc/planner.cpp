@@ -523,6 +523,8 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
     if (!cp->leaf[t].direct && !cp->leaf[t].cached && ns > 0) cp->steps[cp->leaf[t].step].preps.push_back(t);
 
   // steps: sizes, batch strides, kernel, output offsets
+  const bool share_k = shares_k(plan.prec == TNC_PREC_BF16X3 ? Prec::BF16X3 : Prec::C64,
+                                plan.form == TNC_GEMM_3M ? Form::M3 : Form::M4);
   for (int s = 0; s < ns; ++s) {
     StepPlan& sp = cp->steps[s];
     auto prod = [&](const std::vector<int>& ls) {
@@ -538,8 +540,9 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
     // the arena before every batch; when this step runs one thread per
     // output (no transposed launch), it is read in place instead: its own
     // strides, row and K offset tables, and the chunk's base offset.
-    const bool small_step = choose_gemm_kernel(sp.h, sp.m, sp.n, sp.k) == GemmKernel::SMALL &&
-                            choose_gemm_kernel(sp.h, sp.n, sp.m, sp.k) != GemmKernel::MFMA;
+    const GemmKernel k0 = choose_gemm_kernel(sp.h, sp.m, sp.n, sp.k, share_k);
+    const GemmKernel k1 = choose_gemm_kernel(sp.h, sp.n, sp.m, sp.k, share_k);
+    const bool small_step = k0 == GemmKernel::SMALL && k1 != GemmKernel::MFMA;
     for (int x : {sp.A, sp.B})
       if (x < n && small_step && cp->leaf[x].base_slot >= 0 && !cp->leaf[x].inplace) {
         cp->leaf[x].inplace = true;
@@ -596,8 +599,6 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
     auto waste = [](int64_t r, int64_t c) {
       return static_cast<double>((r + 63) / 64 * 64) / r * static_cast<double>((c + 31) / 32 * 32) / c;
     };
-    const GemmKernel k0 = choose_gemm_kernel(sp.h, sp.m, sp.n, sp.k);
-    const GemmKernel k1 = choose_gemm_kernel(sp.h, sp.n, sp.m, sp.k);
     sp.swap = k1 == GemmKernel::MFMA && (k0 != GemmKernel::MFMA || waste(sp.n, sp.m) < waste(sp.m, sp.n));
     sp.kind = sp.swap ? k1 : k0;
     sp.la = sp.swap ? sp.B : sp.A;
@@ -682,9 +683,8 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
       // 256 x 256 as a pair 24.3, whole 14.8); in split precision, whose
       // stages are shorter, up to 2048 (4096 x 256 x 256 25.1, whole 18.4; in
       // complex64 that is 26 to 30 either way, with the store's order)
-      const bool shared = (plan.prec == TNC_PREC_C64 || plan.form == TNC_GEMM_4M) &&
-                          sp.h * ((sp.lm + 31) / 32) * ((sp.ln + 15) / 16) <=
-                              (plan.prec == TNC_PREC_C64 ? 1024 : 2048);
+      const bool shared = share_k && sp.h * ((sp.lm + 31) / 32) * ((sp.ln + 15) / 16) <=
+                                         (plan.prec == TNC_PREC_C64 ? 1024 : 2048);
       if (t0 < 512 && sp.k >= (shared ? 512 : 256))
         while (t0 * S * 2 <= 2048 && sp.k / (S * 2) >= 128 && sp.k % (16 * S * 2) == 0) S *= 2;
     } else if (sp.kind == GemmKernel::DOT) {

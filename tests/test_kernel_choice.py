@@ -36,3 +36,13 @@ def test_split_precision_keeps_two_sums_unless_it_had_one(ctx, h, m, n, k):
     full = rows * cols * s.h / (tiles * 256 * 128)
     if s.variant == 3:
         assert tiles >= 1024 and full >= 0.875
+
+
+@pytest.mark.parametrize("h, m, n, k", [(1, 16, 256, 256), (1, 60, 31, 512), (4, 16, 16, 1024), (1, 63, 31, 200)])
+@pytest.mark.parametrize("prec, form, kernel", [(tnc.PREC_C64, tnc.GEMM_4M, MFMA), (tnc.PREC_C64, tnc.GEMM_3M, MFMA),
+                                                (tnc.PREC_BF16X3, tnc.GEMM_4M, MFMA), (tnc.PREC_BF16X3, tnc.GEMM_3M, SMALL)],
+                         ids=["c64_4M", "c64_3M", "bf16x3_4M", "bf16x3_3M"])
+def test_few_outputs_and_a_long_k(ctx, h, m, n, k, prec, form, kernel):
+    """On MFMA only where its kernels share K out; split precision's 3M tiles
+    do not (and would round more than one thread per output does)."""
+    assert step(ctx, h, m, n, k, prec, form).kernel == kernel
