@@ -522,20 +522,47 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
   for (int t = 0; t < n; ++t)
     if (!cp->leaf[t].direct && !cp->leaf[t].cached && ns > 0) cp->steps[cp->leaf[t].step].preps.push_back(t);
 
-  // steps: sizes, batch strides, kernel, output offsets
-  const bool share_k = shares_k(plan.prec == TNC_PREC_BF16X3 ? Prec::BF16X3 : Prec::C64,
-                                plan.form == TNC_GEMM_3M ? Form::M3 : Form::M4);
+  // steps: sizes, and a level for each (one more than its operands': all steps
+  // of a level are independent)
+  auto prod = [&](const std::vector<int>& ls) {
+    int64_t p = 1;
+    for (int l : ls) p *= net.extents[l];
+    return p;
+  };
+  std::vector<int> lvl(n_ids, 0);
   for (int s = 0; s < ns; ++s) {
     StepPlan& sp = cp->steps[s];
-    auto prod = [&](const std::vector<int>& ls) {
-      int64_t p = 1;
-      for (int l : ls) p *= net.extents[l];
-      return p;
-    };
     sp.h = prod(sp.H);
     sp.m = prod(sp.M);
     sp.n = prod(sp.N);
     sp.k = prod(sp.K);
+    lvl[n + s] = 1 + std::max(lvl[plan.pairs[s][0]], lvl[plan.pairs[s][1]]);
+  }
+  // Steps that run on MFMA for their long K alone take a launch each there,
+  // about 7 us (10 with split K), while one thread per output runs all of a
+  // level's in one launch of about 0.075 us per k: they stay on MFMA up to k
+  // / 112 of them in a level (16 x 256 x 256: 3 in a level 45.1 us on MFMA,
+  // 46.0 grouped, 8 85 and 54, 32 270 and 86; 32 x 32 x 512: 4 44.6 and 47.3, 8 85
+  // and 53).  The rule holds whether or not the levels run grouped, so that
+  // results do not depend on that.
+  const bool has_share_k = shares_k(plan.prec == TNC_PREC_BF16X3 ? Prec::BF16X3 : Prec::C64,
+                                    plan.form == TNC_GEMM_3M ? Form::M3 : Form::M4);
+  std::vector<int64_t> long_steps(ns ? lvl[root] + 1 : 0, 0), long_k(long_steps);
+  auto on_mfma = [&](const StepPlan& sp, bool share_k) {
+    return choose_gemm_kernel(sp.h, sp.m, sp.n, sp.k, share_k) == GemmKernel::MFMA ||
+           choose_gemm_kernel(sp.h, sp.n, sp.m, sp.k, share_k) == GemmKernel::MFMA;
+  };
+  for (int s = 0; has_share_k && s < ns; ++s) {
+    const StepPlan& sp = cp->steps[s];
+    if (!on_mfma(sp, true) || on_mfma(sp, false)) continue;
+    ++long_steps[lvl[n + s]];
+    long_k[lvl[n + s]] = std::max(long_k[lvl[n + s]], sp.k);
+  }
+
+  // steps: batch strides, kernel, output offsets
+  for (int s = 0; s < ns; ++s) {
+    StepPlan& sp = cp->steps[s];
+    const bool share_k = has_share_k && 112 * long_steps[lvl[n + s]] <= long_k[lvl[n + s]];
     // A leaf whose sliced labels are fixed per chunk would be gathered into
     // the arena before every batch; when this step runs one thread per
     // output (no transposed launch), it is read in place instead: its own
@@ -683,8 +710,8 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
       // 256 x 256 as a pair 24.3, whole 14.8); in split precision, whose
       // stages are shorter, up to 2048 (4096 x 256 x 256 25.1, whole 18.4; in
       // complex64 that is 26 to 30 either way, with the store's order)
-      const bool shared = share_k && sp.h * ((sp.lm + 31) / 32) * ((sp.ln + 15) / 16) <=
-                                         (plan.prec == TNC_PREC_C64 ? 1024 : 2048);
+      const bool shared = has_share_k && sp.h * ((sp.lm + 31) / 32) * ((sp.ln + 15) / 16) <=
+                                             (plan.prec == TNC_PREC_C64 ? 1024 : 2048);
       if (t0 < 512 && sp.k >= (shared ? 512 : 256))
         while (t0 * S * 2 <= 2048 && sp.k / (S * 2) >= 128 && sp.k % (16 * S * 2) == 0) S *= 2;
     } else if (sp.kind == GemmKernel::DOT) {
@@ -758,11 +785,8 @@ std::unique_ptr<ChunkPlan> build_chunk(const Plan& plan, int j) {
                         static_cast<double>(sp.h) * sp.m * sp.n);
   }
 
-  // execution order: step by step, or level by level of the tree (a step's
-  // level is one more than its operands'; all steps of a level are
-  // independent and run together)
-  std::vector<int> lvl(n_ids, 0);
-  for (int s = 0; s < ns; ++s) lvl[n + s] = 1 + std::max(lvl[plan.pairs[s][0]], lvl[plan.pairs[s][1]]);
+  // execution order: step by step, or level by level of the tree (all steps of
+  // a level run together)
   cp->grouped = plan.grouping != 0 && ns > 0;
   auto when = [&](int s) { return cp->grouped ? lvl[n + s] : s; };
   const int t_end = ns == 0 ? 0 : (cp->grouped ? lvl[root] + 1 : ns);

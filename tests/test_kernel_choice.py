@@ -46,3 +46,33 @@ def test_few_outputs_and_a_long_k(ctx, h, m, n, k, prec, form, kernel):
     """On MFMA only where its kernels share K out; split precision's 3M tiles
     do not (and would round more than one thread per output does)."""
     assert step(ctx, h, m, n, k, prec, form).kernel == kernel
+
+
+def chain(ctx, n_pairs, d, e, k, prec=tnc.PREC_C64, grouping=True):
+    """Kernels of the first level of (A0 B0) (A1 B1) ...: n_pairs steps [d, k] x [k, e] or [e, k] x [k, d]."""
+    ext, lab = [d if i % 2 == 0 else e for i in range(n_pairs + 1)], []
+    for p in range(n_pairs):
+        lab += [(p, n_pairs + 1 + p), (p + 1, n_pairs + 1 + p)]
+        ext.append(k)
+    pairs, ids, nxt = [(2 * p, 2 * p + 1) for p in range(n_pairs)], [2 * n_pairs + p for p in range(n_pairs)], 3 * n_pairs
+    while len(ids) > 1:
+        pairs += [(ids[i], ids[i + 1]) for i in range(0, len(ids) - 1, 2)]
+        ids, nxt = list(range(nxt, nxt + len(ids) // 2)) + ids[len(ids) // 2 * 2:], nxt + len(ids) // 2
+    net = tnc.Network(ctx, lab, np.array(ext, dtype=np.int64), (0, n_pairs), None)
+    plan = tnc.Plan(net, pairs, (), prec, tnc.GEMM_4M)
+    tnc.tnc_plan_set_grouping(plan.handle, grouping)
+    kinds = [tnc.tnc_plan_get_step(plan.handle, s).kernel for s in range(n_pairs)]
+    plan.close()
+    net.close()
+    return kinds
+
+
+@pytest.mark.parametrize("d, e, k", [(16, 256, 256), (32, 32, 512), (16, 64, 256), (16, 1024, 128)])
+@pytest.mark.parametrize("prec", [tnc.PREC_C64, tnc.PREC_BF16X3], ids=["c64", "bf16x3"])
+def test_a_level_full_of_long_k_steps_shares_its_launch(ctx, d, e, k, prec):
+    """A launch each only while that is less than the level's one launch of
+    one thread per output, whatever the grouping."""
+    for n_pairs in (1, 2, 8, 32):
+        for grouping in (True, False):
+            want = MFMA if 112 * n_pairs <= k else SMALL
+            assert chain(ctx, n_pairs, d, e, k, prec, grouping) == [want] * n_pairs, (n_pairs, grouping)
