@@ -862,7 +862,7 @@ tnc_status tnc_batched_cgemm(tnc_ctx ctx, int64_t h, int64_t m, int64_t n, int64
   const GemmKernel kind = choose_gemm_kernel(h, m, n, k, shares_k(p, f));
   const int variant = c.gemm_variant >= 0
                           ? c.gemm_variant
-                          : default_variant(static_cast<tnc_prec>(prec), static_cast<tnc_cgemm>(form), h, m, n, false);
+                          : default_variant(static_cast<tnc_prec>(prec), static_cast<tnc_cgemm>(form), h, m, n, k, false);
   check_hip(launch_gemm(d, kind, variant, f, p, c.stream), "gemm launch");
   TNC_CATCH
 }

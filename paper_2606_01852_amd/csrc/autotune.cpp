@@ -13,6 +13,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <initializer_list>
 #include <sstream>
 
 #include "core.hpp"
@@ -57,23 +58,45 @@ std::vector<int> candidates(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m,
 
 }  // namespace
 
-// Split 3M: 128 x 128 where it has two tiles per CU, little padding and fills
-// its last round about as well as 128 x 64, which is 7 % slower per product
-// (16 x 1024 x 512 x 768 159 us on 128 x 64, 142 so; 200 x 90 x 100 x 300, which
-// has 200 tiles, 35.6, 38.4; 13 x 356 x 1918 x 2194, 585 tiles in three rounds,
-// 606, 637), else 128 x 64 unless it pads a quarter away that a small tile with
-// enough workgroups does not.  (64 x 64, the choice below 1024 tiles before:
-// 16 x 1024 x 256 x 1024 as a pair 212 us, now 143.)
-static int default_variant_3m(int64_t h, int64_t m, int64_t n) {
-  auto full = [&](int v) {  // the share of the rounds that is work
-    const int64_t t = tiles_for(v, h, m, n), q = (t + 255) / 256;
-    return (1.0 - padding_waste(v, m, n)) * static_cast<double>(t) / (256.0 * q);
-  };
-  if (tiles_for(2, h, m, n) >= 512 && padding_waste(2, m, n) <= 0.125 && full(2) > 0.935 * full(0)) return 2;
-  if (padding_waste(0, m, n) > 0.25)
-    for (int v : {4, 5, 6})
-      if (tiles_for(v, h, m, n) >= 1024 && padding_waste(v, m, n) <= 0.125) return v;
-  return 0;
+// What a tile takes: `alone` ns per complex k where its workgroup has a CU to
+// itself, `full` ns per k and workgroup where `at_once` of them share one.
+struct TileCost {
+  double alone, full;
+  int at_once;
+};
+
+// The variant whose launch takes least.  The CU with the most tiles, q of
+// them, runs them at_once by at_once, each batch for max(alone, batch x full)
+// per k and a prologue worth k0 of it; a tile's store takes a time of its own
+// where nothing else runs beside it (a shape of one workgroup per CU), less
+// where something does.  Fitted to forced variants over 104 random shapes
+// (h 1..8192, m, n 16..4000, k 16..2500, us): on average 0.2 % behind the best.
+static int least_time(const TileCost* cost, std::initializer_list<int> variants, double k0, double store_alone, double store,
+                      int64_t h, int64_t m, int64_t n, int64_t k) {
+  int best = *variants.begin();
+  double top = 0.0;
+  for (int v : variants) {
+    const TileCost& c = cost[v];
+    const int64_t q = (tiles_for(v, h, m, n) + 255) / 256;
+    auto batch = [&](int64_t b) { return b ? std::max(c.alone, static_cast<double>(b) * c.full) : 0.0; };
+    int bm = 0, bnc = 0;
+    gemm_variant_tile(v, &bm, &bnc);
+    const double t = (static_cast<double>(q / c.at_once) * batch(c.at_once) + batch(q % c.at_once)) * (static_cast<double>(k) + k0) * 1e-3 +
+                     (c.at_once == 1 ? store_alone : store) * static_cast<double>(q) * bm * bnc / 8192;
+    if (top == 0.0 || t < 0.99 * top) {
+      top = t;
+      best = v;
+    }
+  }
+  return best;
+}
+
+// Split 3M (before: 128 x 64 unless a small tile padded next to nothing and had
+// 1024 workgroups, so 579 x 33 x 51 x 460 ran 66 us on it, 64 x 64 takes 47; 134 x
+// 35 x 193 x 308 48 and, on 64 x 32, 34; 4096 x 32 x 32 x 128 110 and 81).
+static int default_variant_3m(int64_t h, int64_t m, int64_t n, int64_t k) {
+  static const TileCost cost[kGemmVariants] = {{55, 39, 2}, {99, 99, 1}, {69, 69, 1}, {0, 0, 1}, {82, 26.4, 3}, {89, 16.8, 2}, {88, 8.65, 4}};
+  return least_time(cost, {0, 2, 4, 5, 6}, 45, 0.74, 0.30, h, m, n, k);
 }
 
 // 4M kernels.  With few tiles the shapes that share K out (us per launch,
@@ -93,8 +116,8 @@ static int default_variant_3m(int64_t h, int64_t m, int64_t n) {
 // where the others keep the cross products apart (error against 64 bits at
 // k = 1024, 4096, 16384: 1.005, 1.02 and 1.08 times theirs), so nobody gets it
 // unasked except planned steps that give every CU four tiles of it.
-int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n, bool planned) {
-  if (!runs_4m(prec, form)) return default_variant_3m(h, m, n);
+int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n, int64_t k, bool planned) {
+  if (!runs_4m(prec, form)) return default_variant_3m(h, m, n, k);
   const int64_t few = tiles_for(kDirect32x16, h, m, n);
   if (few <= 256) return kDirect32x16;
   if (few <= 1024) {
@@ -263,7 +286,7 @@ void assign_variants(const Plan& plan, ChunkPlan& cp, bool tune) {
     if (tune && !c.host_only)
       sp.variant = tune_shape(c, key, d.k, perm);
     else
-      sp.variant = default_variant(plan.prec, plan.form, d.h, d.m, d.n, true);
+      sp.variant = default_variant(plan.prec, plan.form, d.h, d.m, d.n, d.k, true);
   }
   summarize_steps(cp);
 }

@@ -331,7 +331,7 @@ void plan_distribution(const Plan& plan, int P, double large_bytes, const tnc_di
                        std::vector<tnc_dist_step>& out, double& total, double& moved);
 
 // autotune.cpp
-int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n, bool planned);
+int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n, int64_t k, bool planned);
 void load_tune_cache(Ctx& c);
 void assign_variants(const Plan& plan, ChunkPlan& cp, bool tune);
 

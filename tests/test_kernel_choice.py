@@ -76,3 +76,18 @@ def test_a_level_full_of_long_k_steps_shares_its_launch(ctx, d, e, k, prec):
         for grouping in (True, False):
             want = MFMA if 112 * n_pairs <= k else SMALL
             assert chain(ctx, n_pairs, d, e, k, prec, grouping) == [want] * n_pairs, (n_pairs, grouping)
+
+
+TILES = [(128, 64), (256, 64), (128, 128), (256, 128), (64, 64), (128, 32), (64, 32)]
+
+
+@pytest.mark.parametrize("h, m, n, k", [(4096, 32, 32, 128), (1738, 39, 31, 134), (579, 33, 51, 460), (134, 35, 193, 308),
+                                        (7301, 18, 97, 46), (145, 34, 538, 916), (3777, 44, 63, 290), (2000, 64, 64, 64)])
+def test_split_3m_does_not_pad_small_steps_to_large_tiles(ctx, h, m, n, k):
+    """Batches of small steps on a tile that pads them no more than 64 x 64
+    does (all of these ran longer on 128 x 64)."""
+    s = step(ctx, h, m, n, k, tnc.PREC_BF16X3, tnc.GEMM_3M)
+    assert s.kernel == MFMA
+    rows, cols = (s.n, s.m) if s.swapped else (s.m, s.n)
+    padded = [-(-rows // bm) * bm * -(-cols // bn) * bn for bm, bn in TILES]
+    assert padded[s.variant] <= padded[4], (s.variant, s.swapped)
