@@ -69,8 +69,9 @@ struct TileCost {
 // them, runs them at_once by at_once, each batch for max(alone, batch x full)
 // per k and a prologue worth k0 of it; a tile's store takes a time of its own
 // where nothing else runs beside it (a shape of one workgroup per CU), less
-// where something does.  Fitted to forced variants over 104 random shapes
-// (h 1..8192, m, n 16..4000, k 16..2500, us): on average 0.2 % behind the best.
+// where something does.  Fitted to forced variants over some 105 random
+// shapes in each form (h 1..8192, m, n 16..4000, k 16..2500): on average 0.2 %
+// behind the best in 3M, 0.4 % in 4M.
 static int least_time(const TileCost* cost, std::initializer_list<int> variants, double k0, double store_alone, double store,
                       int64_t h, int64_t m, int64_t n, int64_t k) {
   int best = *variants.begin();
@@ -106,16 +107,19 @@ static int default_variant_3m(int64_t h, int64_t m, int64_t n, int64_t k) {
 // the least rounds, weighed by what a round takes (1 x 1000 x 500 x 200: 1024
 // tiles of 32 x 16, two to a CU, 15.9; 512 of 32 x 32 15.7; 256 of 64 x 32
 // 12.4; where 64 x 32 pads into a second round, 3 x 138 x 1067 x 79: 12.1, 11.9,
-// 15.2).  Else the
+// 15.2).  Else in complex64 the
 // tile with the largest product of what it reaches on large shapes (relative
 // to 256 x 128), the share of it that is not padding, how evenly its
 // workgroups fill 256 CUs, and how well one CU's waves hide each other's
 // latency (fewer than two per SIMD do not: 2 x 4096 x 256 x 128 runs 20.5 us
 // on 256 workgroups of four waves, 28.0 on 512 of two, 24.8 on 128 of eight).
-// Split precision's 256 x 128 tile (3) has one sum for all three products
-// where the others keep the cross products apart (error against 64 bits at
-// k = 1024, 4096, 16384: 1.005, 1.02 and 1.08 times theirs), so nobody gets it
-// unasked except planned steps that give every CU four tiles of it.
+// In split precision the tile of the least predicted time (by rates as in
+// complex64 5 x 1699 x 917 x 2208 ran on 64 x 64, 525 us, 472 on 128 x 64; 246 x
+// 130 x 42 x 1239 174, now 126).  Its 256 x 128 tile (3) has one sum for all
+// three products where the others keep the cross products apart (error
+// against 64 bits at k = 1024, 4096, 16384: 1.005, 1.02 and 1.08 times
+// theirs), so nobody gets it unasked except planned steps that give every CU
+// four tiles of it.
 int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t n, int64_t k, bool planned) {
   if (!runs_4m(prec, form)) return default_variant_3m(h, m, n, k);
   const int64_t few = tiles_for(kDirect32x16, h, m, n);
@@ -125,16 +129,18 @@ int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t
     const double t7 = 1.2 * rounds(kDirect32x16, 512), t8 = rounds(kDirect32x32, 256), t9 = 1.4 * rounds(kDirect64x32, 256);
     return t9 <= t8 && t9 <= t7 ? kDirect64x32 : t8 <= t7 ? kDirect32x32 : kDirect32x16;
   }
-  // (8192 x 8192 x 4096 in complex64, 64 x 1024 x 256 x 1024 in split precision)
-  static const double c64[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};
-  static const double split[kGemmVariants] = {0.83, 0.86, 0.875, 1.0, 0.70, 0.52, 0.495};
-  const double* rate = prec == TNC_PREC_BF16X3 ? split : c64;
+  if (prec == TNC_PREC_BF16X3) {
+    static const TileCost cost[kGemmVariants] = {{42, 44, 2}, {86, 86, 1}, {71.5, 71.5, 1}, {155, 155, 1}, {85, 27.7, 4}, {47, 30.5, 4}, {74.5, 18.3, 8}};
+    if (planned && tiles_for(3, h, m, n) >= 1024 && padding_waste(3, m, n) <= 0.125)
+      return least_time(cost, {3, 0, 1, 2, 4, 5, 6}, 37, 0.82, 0.24, h, m, n, k);
+    return least_time(cost, {0, 1, 2, 4, 5, 6}, 37, 0.82, 0.24, h, m, n, k);
+  }
+  static const double rate[kGemmVariants] = {0.86, 0.83, 0.97, 1.0, 0.74, 0.70, 0.575};  // 8192 x 8192 x 4096
   static const int waves[kGemmVariants] = {4, 4, 8, 8, 2, 2, 1};
   int best = 4;
   double top = 0.0;
   for (int v : {3, 2, 0, 1, 4, 5, 6}) {
     const int64_t t = tiles_for(v, h, m, n), q = (t + 255) / 256;
-    if (v == 3 && prec == TNC_PREC_BF16X3 && !(planned && t >= 1024 && padding_waste(v, m, n) <= 0.125)) continue;
     const int64_t w = q * waves[v];
     const double hide = w >= 8 ? 1.0 : w >= 4 ? 0.58 : w >= 2 ? 0.32 : 0.2;
     const double e = rate[v] * (1.0 - padding_waste(v, m, n)) * (static_cast<double>(t) / (256.0 * q)) * hide;

@@ -157,8 +157,10 @@ struct XTile {
   static constexpr int PA = BM * 32, PB = 2 * BNC * 32;  // bytes of one part's plane: 16 bf16 per row
   static constexpr int STAGE = PARTS * (PA + PB);
   // LDS holds BUFS stages and is staged AHEAD of the products, with a barrier
-  // every AHEAD stages: two parts make half the MFMAs of three, so their
-  // stages go in pairs.
+  // every AHEAD stages, and the AHEAD stages behind those are on their way to
+  // registers: two parts make half the MFMAs of three, so their stages go in
+  // pairs (one stage on its way: 20 x 130 x 260 x 900 48.3 us, two 46.2; 40 x 700 x
+  // 190 x 300 with its operands in HBM 73.9, 70.7; 1 x 2437 x 2113 x 1999 334, 287).
   static constexpr int BUFS = EXACT ? 2 : 4, AHEAD = BUFS / 2;
   static constexpr size_t kLds = BUFS * STAGE;
   static constexpr int PRODUCTS = EXACT ? 6 : 3;
@@ -173,7 +175,7 @@ struct XTile {
   static constexpr bool CROSS = !EXACT && !(PW == 2 && WM * WN > 4);
   static constexpr int WAVES = CROSS && PW == 2 ? 1 : 2;  // per SIMD, at least
   f16v t[2][CROSS ? NJ : 1];
-  f4 ra[AL], rb[BL];
+  f4 ra[AHEAD][AL], rb[AHEAD][BL];  // the next AHEAD stages, on their way
   const float2 *pa[AL], *pb[BL];
   uint32_t tiny;
 
@@ -236,17 +238,17 @@ struct XTile {
   static constexpr int U = AL + BL, PIECES = 2 * PARTS + 2;
   uint32_t w[2][PARTS];  // the unit's parts: of its first and second complex value
 
-  template <int u>
+  template <int set, int u>
   __device__ __forceinline__ f4& staged() {
     if constexpr (u < AL)
-      return ra[u];
+      return ra[set][u];
     else
-      return rb[u - AL];
+      return rb[set][u - AL];
   }
-  template <int u, int q>
+  template <int set, int u, int q>
   __device__ __forceinline__ void piece(char* lds, int tid) {
     const int r = tid >> 2, c = tid & 3;
-    f4& v = staged<u>();
+    f4& v = staged<set, u>();
     if constexpr (q < 2 * PARTS) {
       constexpr int e = q / PARTS, part = q % PARTS;
       float x = v[2 * e], y = v[2 * e + 1];
@@ -277,29 +279,31 @@ struct XTile {
       }
     }
   }
-  template <bool CHECK, int u>
+  template <bool CHECK, int set, int u>
   __device__ __forceinline__ void load_unit(int left, int tid) {
     if constexpr (u < AL)
-      ra[u] = fetch<CHECK>(pa[u], left, tid);
+      ra[set][u] = fetch<CHECK>(pa[u], left, tid);
     else
-      rb[u - AL] = fetch<CHECK>(pb[u - AL], left, tid);
+      rb[set][u - AL] = fetch<CHECK>(pb[u - AL], left, tid);
   }
   // `left` complex k are left of the rows
+  template <int set>
   __device__ __forceinline__ void load(int64_t left, int tid) {
     if (left >= XK)
-      each<U>([&](auto u) { load_unit<false, u>(0, tid); });
+      each<U>([&](auto u) { load_unit<false, set, u>(0, tid); });
     else
-      each<U>([&](auto u) { load_unit<true, u>(static_cast<int>(left), tid); });
+      each<U>([&](auto u) { load_unit<true, set, u>(static_cast<int>(left), tid); });
   }
+  template <int set>
   __device__ __forceinline__ void stage(char* lds, int tid) {
-    each<U * PIECES>([&](auto q) { piece<q / PIECES, q % PIECES>(lds, tid); });
+    each<U * PIECES>([&](auto q) { piece<set, q / PIECES, q % PIECES>(lds, tid); });
   }
 
   // One stage: the products of `cur`; with NEXT the staged registers are
   // split into `nxt` and loaded again (whole stages).  Three parts: each 32 x
   // 32 block's six products of the stage are summed from zero and then added
   // to its accumulator by the VALU.
-  template <bool NEXT>
+  template <bool NEXT, int set>
   __device__ __forceinline__ void step(const char* cur, char* nxt, int tid, int wm, int wn, int lane) {
     const int h = lane >> 5, r = lane & 31;
     const char* a = cur + (wm * 64 + r) * 32 + ((h ^ ((r >> 3) & 1)) << 4);
@@ -337,8 +341,8 @@ struct XTile {
       if constexpr (NEXT)
         each<(s + 1) * Q / SLOTS - s * Q / SLOTS>([&](auto n) {
           constexpr int q = s * Q / SLOTS + n;
-          piece<q / PIECES, q % PIECES>(nxt, tid);
-          if constexpr (q % PIECES == PIECES - 1) load_unit<false, q / PIECES>(0, tid);
+          piece<set, q / PIECES, q % PIECES>(nxt, tid);
+          if constexpr (q % PIECES == PIECES - 1) load_unit<false, set, q / PIECES>(0, tid);
         });
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -359,26 +363,30 @@ struct XTile {
     const float2* B = d.B + uniform(ob);
     init(A, B, d, tc, tid);
     const int64_t k = d.k, nk = (k + XK - 1) / XK, full = k / XK;
-#pragma unroll
-    for (int q = 0; q < AHEAD; ++q)
-      if (q < nk) {
-        load(k - q * XK, tid);
-        stage(lds + q * STAGE, tid);
-      }
-    if (AHEAD < nk) load(k - AHEAD * XK, tid);
+    // stage st goes through register set st % AHEAD
+    each<AHEAD>([&](auto q) {
+      if (!q || q < nk) load<q>(k - q * XK, tid);
+    });
+    each<AHEAD>([&](auto q) {
+      if (!q || q < nk) stage<q>(lds + q * STAGE, tid);
+      if (q + AHEAD < nk) load<q>(k - (q + AHEAD) * XK, tid);
+    });
     __syncthreads();
     auto buf = [&](int64_t st) { return lds + (st & (BUFS - 1)) * STAGE; };
     int64_t kt = 0;
-    for (; kt + 2 * AHEAD < full; kt += AHEAD) {
-      each<AHEAD>([&](auto q) { step<true>(buf(kt + q), buf(kt + q + AHEAD), tid, wm, wn, lane); });
+    for (; kt + 3 * AHEAD - 1 < full; kt += AHEAD) {
+      each<AHEAD>([&](auto q) { step<true, q>(buf(kt + q), buf(kt + q + AHEAD), tid, wm, wn, lane); });
       __syncthreads();
     }
-    for (; kt < nk; ++kt) {
-      if (kt + AHEAD < nk) stage(buf(kt + AHEAD), tid);
-      if (kt + AHEAD + 1 < nk) load(k - (kt + AHEAD + 1) * XK, tid);
-      step<false>(buf(kt), nullptr, tid, wm, wn, lane);
-      __syncthreads();
-    }
+    for (; kt < nk; kt += AHEAD)
+      each<AHEAD>([&](auto q) {
+        const int64_t st = kt + q;
+        if (q && st >= nk) return;
+        if (st + AHEAD < nk) stage<q>(buf(st + AHEAD), tid);
+        if (st + 2 * AHEAD < nk) load<q>(k - (st + 2 * AHEAD) * XK, tid);
+        step<false, q>(buf(st), nullptr, tid, wm, wn, lane);
+        __syncthreads();
+      });
     if constexpr (!EXACT) return true;
     acc[1][NJ - 1] += t[1][0];
     float s = 0.f;  // NaN if any sum is not finite

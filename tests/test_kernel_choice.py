@@ -91,3 +91,11 @@ def test_split_3m_does_not_pad_small_steps_to_large_tiles(ctx, h, m, n, k):
     rows, cols = (s.n, s.m) if s.swapped else (s.m, s.n)
     padded = [-(-rows // bm) * bm * -(-cols // bn) * bn for bm, bn in TILES]
     assert padded[s.variant] <= padded[4], (s.variant, s.swapped)
+
+
+@pytest.mark.parametrize("h, m, n, k, near_best", [(639, 64, 18, 203, (6,)), (579, 33, 51, 460, (4,)), (78, 403, 157, 740, (0, 1)),
+                                                   (13, 356, 1918, 1094, (0, 2))])
+def test_split_4m_tile_is_near_the_best(ctx, h, m, n, k, near_best):
+    """Ragged extents: the tiles that were measured within 7 % of the best."""
+    s = step(ctx, h, m, n, k, tnc.PREC_BF16X3, tnc.GEMM_4M)
+    assert not s.swapped and s.variant in near_best
