@@ -29,12 +29,21 @@
 // VALU operations of the next stage's split or of the last block's sum, so
 // that one wave alone keeps the pipe busy (without: 206 instead of 218).
 //
-// Where the split is not exact the tile is computed again on the FP32 pipe
-// (fp32_tile below), so every input that a float32 can hold means what it
-// meant there: a remainder that is a subnormal float32 (|x| below about
-// 2^-102: bf16 has no bits there) is noticed while the operands are staged,
-// infinities, NaNs and values that round to a bf16 infinity make the tile's
-// own sums non-finite, which is looked at once at the end.
+// Every input that a float32 can hold means what it means to float32
+// arithmetic.  Both operands are scaled by 2^24 on their way in, so the split
+// is exact for all of them, subnormals included; an operand with values of
+// 2^30 or more is left as it is, and there a remainder that is a subnormal
+// float32 (|x| below about 2^-102: bf16 has no bits there) is noticed while it
+// is staged.  Such tiles, and those whose sums are not finite (infinities,
+// NaNs, and sums past 2^80 where both operands were scaled), are computed
+// again on the FP32 pipe.  2048^3, ms: 0.330 whatever small values there are
+// (1.67 when one value below 2^-102 sent its tile to the FP32 pass, which
+// then waited for every read), 0.343 with operands of 2^43, 0.914 with an
+// infinity in every tile (1.67; all on the FP32 pipe: 0.544).  The scaling
+// takes two operations for two values and the test for subnormal remainders,
+// which the scaled copy of the loop does without, three: 6 x 1000 x 500 x 777
+// 113.3 -> 112.7 us, 8192 x 4096 x 4096 4.83 -> 4.84 ms, 30 x 300 x 300 x 64 18.5
+// -> 18.8 us.
 //
 // complex64 in the 3M form runs here as well: 16 x 1024 x 512 x 768 312 us
 // on the FP32 pipe with three products, 243 here, at 0.3 of the error.
@@ -65,6 +74,7 @@ constexpr int XK = 8;  // complex k per LDS stage: 16 real, one bf16 MFMA step
 
 // The next part of x and y, packed [x | y << 16], which it is taken off.
 __device__ __forceinline__ uint32_t take_part(float& x, float& y) {
+#pragma clang fp contract(off)
   typedef float fv2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bv2 __attribute__((ext_vector_type(2)));
   const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((fv2){x, y}, bv2));
@@ -83,6 +93,20 @@ __device__ __forceinline__ uint32_t last_part(float x, float y, uint32_t& tiny) 
   const uint32_t t = tx < ty ? tx : ty;
   tiny = tiny < t ? tiny : t;
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((fv2){x, y}, bv2));
+}
+
+// Scaled by 2^24 every float32's last bit is 2^-125 or more, so the three parts
+// of every value are normal; operands that are scaled hold values below 2^30,
+// as far as they were looked at.
+constexpr int kScale = 24;
+constexpr float kScaleBelow = 1073741824.f;
+__device__ __forceinline__ float pow2(int e) { return __int_as_float((127 + e) << 23); }
+// Whether a wave's lanes all have values that may be scaled (uniform).
+__device__ __forceinline__ bool scalable(float largest) {
+  return __builtin_amdgcn_ballot_w64(!(largest < kScaleBelow)) == 0;
+}
+__device__ __forceinline__ float largest_of(const f4& v) {
+  return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
 }
 
 // f(integral_constant 0), ..., f(N - 1): loops whose counters index registers
@@ -106,35 +130,89 @@ __device__ __forceinline__ TileCoord uniform(const TileCoord& t) {
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));  // rows of odd length start on 8 bytes
 
-// A 32 x 16 complex block of C again, on the FP32 pipe, straight from global
-// memory and back: right for every float32, and only as fast as such tiles
-// are rare.
-__device__ __forceinline__ void fp32_block(const GemmDesc& d, int64_t b, int64_t row0, int64_t col0, int lane) {
+// BI x BJ blocks of 32 x 16 complex of C again, by one wave on the FP32 pipe,
+// straight from global memory and back: right for every float32.  Stages of
+// four complex k, the next one's values on their way: with 2 x 2 blocks 16
+// MFMAs of 64 cycles, and the same of the other wave on the SIMD, cover a read.
+template <int BI, int BJ>
+__device__ __forceinline__ void fp32_blocks(const GemmDesc& d, int64_t b, int64_t row0, int64_t col0, int lane) {
+  if (row0 >= d.m || col0 >= d.n) return;
   int64_t oa, ob;
   batch_offsets(d, b, oa, ob);
-  const int64_t ld = row_stride(d);
+  const int64_t ld = row_stride(d), k = d.k, n = (k + 3) / 4;
   const int h = lane >> 5, l32 = lane & 31;
-  const int64_t col = col0 + (l32 >> 1);
-  const float2* x = d.A + oa + (row0 + l32 < d.m ? row0 + l32 : d.m - 1) * ld + h;
-  const float2* y = d.B + ob + (col < d.n ? col : d.n - 1) * ld + h;
-  f16v c = {};
-#pragma unroll 1
-  for (int64_t l = 0; l < d.k; l += 2) {
-    float2 u = make_float2(0.f, 0.f), w = u;
-    if (l + h < d.k) {
-      u = x[l];
-      w = y[l];
-    }
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.x, lane & 1 ? w.y : w.x, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(u.y, lane & 1 ? w.x : -w.y, c, 0, 0, 0);
-  }
-  if (col >= d.n) return;
-  float* C = reinterpret_cast<float*>(d.C + b * d.m * d.n) + (l32 & 1);
-  const int64_t co = d.offM ? d.offN[col] : col;
+  const bool odd = lane & 1;
+  const float2 *pa[BI], *pb[BJ];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int64_t row = row0 + 8 * (v >> 2) + 4 * h + (v & 3);
-    if (row < d.m) C[2 * ((d.offM ? d.offM[row] : row * d.n) + co)] = c[v];
+  for (int i = 0; i < BI; ++i) {
+    const int64_t r = row0 + 32 * i + l32;
+    pa[i] = d.A + uniform(oa) + (r < d.m ? r : d.m - 1) * ld;
+  }
+#pragma unroll
+  for (int j = 0; j < BJ; ++j) {
+    const int64_t r = col0 + 16 * j + (l32 >> 1);
+    pb[j] = d.B + uniform(ob) + (r < d.n ? r : d.n - 1) * ld;
+  }
+  f4 x[2][BI], y[2][BJ];  // two complex values of each row: k 4 st + 2 h and the next
+  auto fetch = [&](const float2* row, int64_t l) {
+    if (l + 2 <= k) return static_cast<f4>(*reinterpret_cast<const f4u*>(row + l));
+    f4 v = {0.f, 0.f, 0.f, 0.f};
+    if (l < k) {
+      v.x = row[l].x;
+      v.y = row[l].y;
+    }
+    return v;
+  };
+  auto load = [&](auto set, int64_t st) {
+    const int64_t l = 4 * st + 2 * h;
+#pragma unroll
+    for (int i = 0; i < BI; ++i) x[set][i] = fetch(pa[i], l);
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) y[set][j] = fetch(pb[j], l);
+  };
+  f16v c[BI][BJ] = {};
+  auto multiply = [&](auto set) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int j = 0; j < BJ; ++j) {
+        const float br = y[set][j][2 * e], bi = y[set][j][2 * e + 1];
+        const float first = odd ? bi : br, second = odd ? br : -bi;
+#pragma unroll
+        for (int i = 0; i < BI; ++i) {
+          c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[set][i][2 * e], first, c[i][j], 0, 0, 0);
+          c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[set][i][2 * e + 1], second, c[i][j], 0, 0, 0);
+        }
+      }
+  };
+  constexpr std::integral_constant<int, 0> s0{};
+  constexpr std::integral_constant<int, 1> s1{};
+  load(s0, 0);
+  int64_t st = 0;
+#pragma unroll 1
+  for (; st + 1 < n; st += 2) {
+    load(s1, st + 1);
+    multiply(s0);
+    if (st + 2 < n) load(s0, st + 2);
+    multiply(s1);
+  }
+  if (st < n) multiply(s0);
+  // opaque, so that the stores' addresses are not made before the loop
+  int at = lane;
+  asm volatile("" : "+v"(at));
+#pragma unroll
+  for (int j = 0; j < BJ; ++j) {
+    const int64_t col = col0 + 16 * j + (at >> 1 & 15);
+    if (col >= d.n) continue;
+    float* C = reinterpret_cast<float*>(d.C + b * d.m * d.n) + (at & 1);
+    const int64_t co = d.offM ? d.offN[col] : col;
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int64_t row = row0 + 32 * i + 8 * (v >> 2) + 4 * (at >> 5) + (v & 3);
+        if (row < d.m) C[2 * ((d.offM ? d.offM[row] : row * d.n) + co)] = c[i][j][v];
+      }
   }
 }
 
@@ -148,7 +226,18 @@ constexpr int kPartA[6] = {0, 0, 1, 1, 2, 0}, kPartB[6] = {2, 1, 1, 0, 0, 0};
 // Split precision's three: a_hi b_lo, a_lo b_hi, a_hi b_hi.
 constexpr int kSplitA[3] = {0, 1, 0}, kSplitB[3] = {1, 0, 0};
 
-// PARTS = 3: complex64, 2: split precision.
+// What the scale of an operand is chosen by, the same in every wave: the first
+// two values of 64 of its rows, which the first stage reads as well.
+__device__ __forceinline__ f4 sample(const float2* X, int64_t row0, int64_t rows, int64_t ld, int64_t k, int lane) {
+  const float2* p = X + (row0 + lane < rows ? row0 + lane : rows - 1) * ld;
+  if (k > 1) return *reinterpret_cast<const f4u*>(p);
+  return (f4){p->x, p->y, 0.f, 0.f};
+}
+
+// PARTS = 3: complex64, 2: split precision.  In complex64 the code from the
+// first stage on is there twice, SCALED: both operands are scaled, otherwise
+// each as its sample says, with an eye on remainders that bf16 loses (which
+// costs three operations for every two values).
 template <int PARTS, int WM, int WN, int PW>
 struct XTile {
   static constexpr bool EXACT = PARTS == 3;
@@ -178,6 +267,7 @@ struct XTile {
   f4 ra[AHEAD][AL], rb[AHEAD][BL];  // the next AHEAD stages, on their way
   const float2 *pa[AL], *pb[BL];
   uint32_t tiny;
+  float sa, sb, un;  // complex64: the operands' scales and what takes them off again
 
   // rows past the edge repeat the last one: their products are not stored
   __device__ __forceinline__ void init(const float2* A, const float2* B, const GemmDesc& d, const TileCoord& tc,
@@ -245,19 +335,24 @@ struct XTile {
     else
       return rb[set][u - AL];
   }
-  template <int set, int u, int q>
+  template <bool SCALED, int set, int u, int q>
   __device__ __forceinline__ void piece(char* lds, int tid) {
     const int r = tid >> 2, c = tid & 3;
     f4& v = staged<set, u>();
     if constexpr (q < 2 * PARTS) {
+#pragma clang fp contract(off)
       constexpr int e = q / PARTS, part = q % PARTS;
       float x = v[2 * e], y = v[2 * e + 1];
+      if constexpr (EXACT && part == 0) {
+        x *= u < AL ? sa : sb;
+        y *= u < AL ? sa : sb;
+      }
       if constexpr (part < 2) {  // (what the second of two parts leaves is not read)
         w[e][part] = take_part(x, y);
         v[2 * e] = x;
         v[2 * e + 1] = y;
       } else {
-        w[e][part] = last_part(x, y, tiny);
+        w[e][part] = SCALED ? take_part(x, y) : last_part(x, y, tiny);
       }
     } else if constexpr (u < AL) {
       if (q % 2 == 1) return;
@@ -294,16 +389,16 @@ struct XTile {
     else
       each<U>([&](auto u) { load_unit<true, set, u>(static_cast<int>(left), tid); });
   }
-  template <int set>
+  template <bool SCALED, int set>
   __device__ __forceinline__ void stage(char* lds, int tid) {
-    each<U * PIECES>([&](auto q) { piece<set, q / PIECES, q % PIECES>(lds, tid); });
+    each<U * PIECES>([&](auto q) { piece<SCALED, set, q / PIECES, q % PIECES>(lds, tid); });
   }
 
   // One stage: the products of `cur`; with NEXT the staged registers are
   // split into `nxt` and loaded again (whole stages).  Three parts: each 32 x
   // 32 block's six products of the stage are summed from zero and then added
   // to its accumulator by the VALU.
-  template <bool NEXT, int set>
+  template <bool SCALED, bool NEXT, int set>
   __device__ __forceinline__ void step(const char* cur, char* nxt, int tid, int wm, int wn, int lane) {
     const int h = lane >> 5, r = lane & 31;
     const char* a = cur + (wm * 64 + r) * 32 + ((h ^ ((r >> 3) & 1)) << 4);
@@ -341,50 +436,61 @@ struct XTile {
       if constexpr (NEXT)
         each<(s + 1) * Q / SLOTS - s * Q / SLOTS>([&](auto n) {
           constexpr int q = s * Q / SLOTS + n;
-          piece<set, q / PIECES, q % PIECES>(nxt, tid);
+          piece<SCALED, set, q / PIECES, q % PIECES>(nxt, tid);
           if constexpr (q % PIECES == PIECES - 1) load_unit<false, set, q / PIECES>(0, tid);
         });
       __builtin_amdgcn_sched_barrier(0);
     });
   }
 
-  __device__ __forceinline__ static void fp32_tile(const GemmDesc& d, const TileCoord& tc, int wm, int wn, int lane) {
-#pragma unroll 1
-    for (int ij = 0; ij < 2 * NJ; ++ij)
-      fp32_block(d, tc.b, tc.row0 + wm * 64 + (ij & 1) * 32, tc.col0 + wn * 32 * PW + (ij >> 1) * 16, lane);
-  }
-
-  // The tile's sums; false if they have to come from the FP32 pipe.
+  // The tile's sums; false if they have to come from the FP32 pipe (never with
+  // two parts).
   __device__ __forceinline__ bool run(const GemmDesc& d, const TileCoord& tc, char* lds, int tid, int wm, int wn,
                                       int lane) {
     int64_t oa, ob;
     batch_offsets(d, tc.b, oa, ob);
     const float2* A = d.A + uniform(oa);
     const float2* B = d.B + uniform(ob);
+    f4 xa, xb;
+    if constexpr (EXACT) {
+      xa = sample(A, tc.row0, d.m, row_stride(d), d.k, lane);
+      xb = sample(B, tc.col0, d.n, row_stride(d), d.k, lane);
+    }
     init(A, B, d, tc, tid);
-    const int64_t k = d.k, nk = (k + XK - 1) / XK, full = k / XK;
+    each<AHEAD>([&](auto q) {
+      if (!q || q < (d.k + XK - 1) / XK) load<q>(d.k - q * XK, tid);
+    });
+    if constexpr (EXACT) {
+      const int ea = scalable(largest_of(xa)) ? kScale : 0, eb = scalable(largest_of(xb)) ? kScale : 0;
+      sa = pow2(ea);
+      sb = pow2(eb);
+      un = pow2(-ea - eb);
+      if (ea & eb) return add_up<true>(d.k, lds, tid, wm, wn, lane);
+    }
+    return add_up<false>(d.k, lds, tid, wm, wn, lane);
+  }
+  template <bool SCALED>
+  __device__ __forceinline__ bool add_up(int64_t k, char* lds, int tid, int wm, int wn, int lane) {
+    const int64_t nk = (k + XK - 1) / XK, full = k / XK;
     // stage st goes through register set st % AHEAD
     each<AHEAD>([&](auto q) {
-      if (!q || q < nk) load<q>(k - q * XK, tid);
-    });
-    each<AHEAD>([&](auto q) {
-      if (!q || q < nk) stage<q>(lds + q * STAGE, tid);
+      if (!q || q < nk) stage<SCALED, q>(lds + q * STAGE, tid);
       if (q + AHEAD < nk) load<q>(k - (q + AHEAD) * XK, tid);
     });
     __syncthreads();
     auto buf = [&](int64_t st) { return lds + (st & (BUFS - 1)) * STAGE; };
     int64_t kt = 0;
     for (; kt + 3 * AHEAD - 1 < full; kt += AHEAD) {
-      each<AHEAD>([&](auto q) { step<true, q>(buf(kt + q), buf(kt + q + AHEAD), tid, wm, wn, lane); });
+      each<AHEAD>([&](auto q) { step<SCALED, true, q>(buf(kt + q), buf(kt + q + AHEAD), tid, wm, wn, lane); });
       __syncthreads();
     }
     for (; kt < nk; kt += AHEAD)
       each<AHEAD>([&](auto q) {
         const int64_t st = kt + q;
         if (q && st >= nk) return;
-        if (st + AHEAD < nk) stage<q>(buf(st + AHEAD), tid);
+        if (st + AHEAD < nk) stage<SCALED, q>(buf(st + AHEAD), tid);
         if (st + 2 * AHEAD < nk) load<q>(k - (st + 2 * AHEAD) * XK, tid);
-        step<false, q>(buf(st), nullptr, tid, wm, wn, lane);
+        step<SCALED, false, q>(buf(st), nullptr, tid, wm, wn, lane);
         __syncthreads();
       });
     if constexpr (!EXACT) return true;
@@ -396,12 +502,14 @@ struct XTile {
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) s = fmaf(acc[i][j][v], 0.f, s);
-    return !__syncthreads_or(tiny < 0x00FFFFFFu || !(s == 0.f));
+    return !__syncthreads_or((!SCALED && tiny < 0x00FFFFFFu) || !(s == 0.f));
   }
 
   __device__ __forceinline__ float value(int i, int j, int v) const {
     if constexpr (CROSS)
       return acc[i][j][v] + t[i][j][v];
+    else if constexpr (EXACT)
+      return acc[i][j][v] * un;
     else
       return acc[i][j][v];
   }
@@ -412,20 +520,29 @@ struct XTile {
   }
 };
 
+// A tile of C.
+template <int PARTS, int WM, int WN, int PW>
+__device__ __forceinline__ void tile(const GemmDesc& d, bool perm, const TileCoord& tc, char* lds, int tid, int wm,
+                                     int wn, int lane) {
+  XTile<PARTS, WM, WN, PW> t;
+  if (t.run(d, tc, lds, tid, wm, wn, lane)) {
+    t.store(d, perm, tc, wm, wn, lane);
+    return;
+  }
+#pragma unroll 1
+  for (int p = 0; p < PW; ++p)
+    fp32_blocks<2, 2>(d, tc.b, tc.row0 + wm * 64, tc.col0 + wn * 32 * PW + 32 * p, lane);
+}
+
 template <int PARTS, int WM, int WN, int PW, bool PERM>
 __global__ __launch_bounds__(64 * WM * WN, (XTile<PARTS, WM, WN, PW>::WAVES)) void cgemm_4m(GemmDesc d, int64_t tiles_m,
-                                                                                   int64_t tiles_n, int64_t total) {
+                                                                                  int64_t tiles_n, int64_t total) {
   using T = XTile<PARTS, WM, WN, PW>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
   const TileCoord tc = uniform(map_tile_shared<T::BM, T::BNC>(tiles_m, tiles_n, total));
-  T t;
-  if (t.run(d, tc, lds, tid, wm, wn, lane))  // (always, with two parts)
-    t.store(d, PERM, tc, wm, wn, lane);
-  else
-    T::fp32_tile(d, tc, wm, wn, lane);
+  tile<PARTS, WM, WN, PW>(d, PERM, tc, lds, tid, wave / WN, wave % WN, lane);
 }
 
 // Persistent grouped form: see GroupedEntry.  Tiles are dealt to the 8 XCDs
@@ -450,12 +567,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4 ? XTile<PARTS, WM, WN, 
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-    T t;
-    if (t.run(d, tc, lds, tid, wm, wn, lane))
-      t.store(d, d.offM != nullptr, tc, wm, wn, lane);
-    else
-      T::fp32_tile(d, tc, wm, wn, lane);
+    tile<PARTS, WM, WN, PW>(d, d.offM != nullptr, tc, lds, tid, wave / WN, wave % WN, lane);
   }
 }
 
@@ -467,7 +579,9 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN == 4 ? XTile<PARTS, WM, WN, 
 // ..., reads its fragments straight from global memory (lane (h, r) needs
 // four consecutive complex values of row r), splits them in registers, and
 // meets the others only to add the W sums up, in LDS, in order.  No staging,
-// no barrier in the loop.  It splits every value once per wave that reads it,
+// no barrier in the loop.  complex64 is scaled first and goes again, unscaled,
+// where sums come out too large for that (256 x 256 x 256 with operands of 2^43
+// 10.7 us).  It splits every value once per wave that reads it,
 // so it loses where tiles are many.  256 x 256 x 256 26.6 -> 7.0 us, 1024 x
 // 128 x 128 16.5 -> 5.5, 16 x 256 x 256 25.8 -> 6.7 (launches back to back, 4.6
 // of it the launch).
@@ -498,14 +612,19 @@ struct XDirect {
     }
   }
 
+  template <bool SCALED>
   __device__ __forceinline__ static void split(const f4 (&v)[2], s8v (&part)[PARTS], uint32_t& tiny) {
     uint32_t w[3][4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float a = v[e >> 1][2 * (e & 1)], b = v[e >> 1][2 * (e & 1) + 1];
+      if constexpr (SCALED) {
+        a *= pow2(kScale);
+        b *= pow2(kScale);
+      }
       w[0][e] = take_part(a, b);
       w[1][e] = take_part(a, b);
-      if constexpr (PARTS == 3) w[2][e] = last_part(a, b, tiny);
+      if constexpr (PARTS == 3) w[2][e] = SCALED ? take_part(a, b) : last_part(a, b, tiny);
     }
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -538,7 +657,6 @@ struct XDirect {
       const int64_t col = tc.col0 + 16 * j + (r >> 1);
       pb[j] = d.B + uniform(ob) + (col < d.n ? col : d.n - 1) * ld;
     }
-    uint32_t tiny = 0xFFFFFFFFu;
     f16v acc[BI][BJ];
     auto load_stage = [&](int64_t st) {
       const int64_t l = st * XK + 4 * h;
@@ -548,8 +666,10 @@ struct XDirect {
         load<true>(pa, pb, l, k);
     };
     const int64_t nk = (k + XK - 1) / XK;
+    uint32_t tiny = 0xFFFFFFFFu;
     // the sum of the stages first, first + stride, ...
-    auto add_up = [&](int64_t first, auto stride) {
+    auto add_up = [&](auto scaled, int64_t first, auto stride) {
+      constexpr bool SCALED = decltype(scaled)::value;
 #pragma unroll
       for (int i = 0; i < BI; ++i)
 #pragma unroll
@@ -558,7 +678,7 @@ struct XDirect {
       for (int64_t st = first; st < nk; st += stride) {
         s8v fa[BI][PARTS], fb[BJ][PARTS];
 #pragma unroll
-        for (int i = 0; i < BI; ++i) split(x[i], fa[i], tiny);
+        for (int i = 0; i < BI; ++i) split<SCALED>(x[i], fa[i], tiny);
 #pragma unroll
         for (int j = 0; j < BJ; ++j) {
           f4 z[2];  // B': (br, -bi) for even real columns, (bi, br) for odd ones
@@ -569,7 +689,7 @@ struct XDirect {
             z[e].z = odd ? y[j][e].w : y[j][e].z;
             z[e].w = odd ? y[j][e].z : -y[j][e].w;
           }
-          split(z, fb[j], tiny);
+          split<SCALED>(z, fb[j], tiny);
         }
         if (st + stride < nk) load_stage(st + stride);
         f16v c[BI][BJ] = {};
@@ -607,17 +727,22 @@ struct XDirect {
       for (int q = 1; q < 4; ++q) top[0] = top[0] < top[q] ? top[q] : top[0];
       return top[0] >= (uint32_t{127 + 124} << 24);
     };
-    add_up(wave, std::integral_constant<int, W>{});
+    float un = PARTS == 3 ? pow2(-2 * kScale) : 1.f;
+    add_up(std::bool_constant<PARTS == 3>{}, wave, std::integral_constant<int, W>{});
     // (the vote is a barrier: every wave's sums are in LDS behind it)
-    const bool large = put();
-    if (__syncthreads_or(large || (PARTS == 3 && tiny < 0x00FFFFFFu))) {
+    if (__syncthreads_or(put())) {
       if constexpr (PARTS == 3) {
-        if (wave < BI * BJ) fp32_block(d, tc.b, tc.row0 + 32 * (wave / BJ), tc.col0 + 16 * (wave % BJ), lane);
-        return;
+        un = 1.f;
+        add_up(std::false_type{}, wave, std::integral_constant<int, W>{});
+        if (__syncthreads_or(put() || tiny < 0x00FFFFFFu)) {
+          if (wave < BI * BJ) fp32_blocks<1, 1>(d, tc.b, tc.row0 + 32 * (wave / BJ), tc.col0 + 16 * (wave % BJ), lane);
+          return;
+        }
+      } else {
+        add_up(std::false_type{}, wave ? nk : 0, std::integral_constant<int, 1>{});  // all of K in order, in one wave
+        (void)put();
+        __syncthreads();
       }
-      add_up(wave ? nk : 0, std::integral_constant<int, 1>{});  // all of K in order, in one wave
-      (void)put();
-      __syncthreads();
     }
     const float* part = reinterpret_cast<const float*>(lds) + wave * N * 64 + lane;
     const int ij = wave * N / 16, v0 = wave * N & 15;
@@ -638,7 +763,7 @@ struct XDirect {
     if (co >= 0)
 #pragma unroll
       for (int u = 0; u < N; ++u)
-        if (ro[u] >= 0) C[2 * (ro[u] + co)] = sum[u];
+        if (ro[u] >= 0) C[2 * (ro[u] + co)] = PARTS == 3 ? sum[u] * un : sum[u];
   }
 };
 

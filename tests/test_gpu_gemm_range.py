@@ -2,7 +2,9 @@
 few tiles.
 
 A sum whose partial sums in order stay finite is finite, however the kernel
-shares K out.
+shares K out.  In complex64, scaling an operand by a power of two scales the
+result, bit for bit, as long as nothing leaves float32's range, and one value
+far below the others changes no other row's bits.
 """
 import numpy as np
 import pytest
@@ -26,6 +28,16 @@ def ctx():
     c = tnc.Context(0, arena_bytes=64 << 20)
     yield c
     c.close()
+
+
+def cn(rng, shape):
+    return (rng.standard_normal(shape + (2,), dtype=np.float32) * np.float32(np.sqrt(0.5))).view(np.complex64).reshape(shape)
+
+
+def operands(shape):
+    h, m, n, k = shape
+    rng = np.random.Generator(np.random.PCG64(m * 17 + k))
+    return cn(rng, (h, m, k)), cn(rng, (h, n, k))
 
 
 def gemm(ctx, A, B, variant, prec=tnc.PREC_C64):
@@ -57,3 +69,37 @@ def test_partial_sums_stay_finite(ctx, variant, shape, prec):
     print(variant, shape, flush=True)
     got = gemm(ctx, A, B, variant, prec)
     assert np.all(got[..., 0] == np.float32(2.0 ** 126)) and not np.any(got[..., 1])
+
+
+@pytest.mark.parametrize("variant, shape", CALLS, ids=str)
+@pytest.mark.parametrize("ea, eb", [(-100, 60), (60, -100), (45, 45), (-60, -20)])
+def test_a_power_of_two_scales_the_bits(ctx, variant, shape, ea, eb):
+    """Every operand value keeps its 24 bits above 2^-149 (values of CN(0, 1)
+    below 2^-20 are set to zero), and so does every result."""
+    A, B = operands(shape)
+    for X in (A, B):
+        f = X.view(np.float32)
+        f[np.abs(f) < 2.0 ** -20] = 0
+    print(variant, shape, ea, eb, flush=True)
+    ref = gemm(ctx, A, B, variant)
+    ref[np.abs(ref) < 2.0 ** -20] = 0   # below it a scaled result may round to a subnormal
+    got = gemm(ctx, A * np.float32(2.0 ** ea), B * np.float32(2.0 ** eb), variant)
+    got = got * np.float32(2.0 ** -(ea + eb))
+    got[np.abs(got) < 2.0 ** -20] = 0
+    np.testing.assert_array_equal(got, ref)
+
+
+@pytest.mark.parametrize("variant, shape", CALLS, ids=str)
+def test_a_tiny_value_leaves_other_rows_alone(ctx, variant, shape):
+    """One value of the size of a product of two entries that should have been
+    zero (6.1e-17 each), and one of full length near the smallest normal: the
+    other rows' bits are those without them."""
+    A, B = operands(shape)
+    print(variant, shape, flush=True)
+    ref = gemm(ctx, A, B, variant)
+    A2 = A.copy()
+    A2[0, 5, 3] = complex(np.float32(6.123234e-17) * np.float32(6.123234e-17), 1.3e-37)
+    got = gemm(ctx, A2, B, variant)
+    rows = np.ones(A.shape[:2], dtype=bool)
+    rows[0, 5] = False
+    np.testing.assert_array_equal(got[rows], ref[rows])
