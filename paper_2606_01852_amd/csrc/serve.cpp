@@ -323,13 +323,19 @@ struct Server {
     r0.table_bytes = static_cast<int64_t>(lockstep_table_bytes(r0.tables, static_cast<int>(job.size())));
     // small results side by side behind the table, so that one copy fetches
     // them all (a copy of its own costs a request as much as a launch)
-    const int64_t results = static_cast<int64_t>(job.size()) * r0.plan->chunks[0]->R * 16;
+    const int64_t results = static_cast<int64_t>(job.size()) * r0.plan->chunks[0]->R * 16, table = r0.table_bytes;
     r0.result_off = -1;
+    r0.table_off = -1;
     if (results <= kPackedResults) {
-      r0.result_off = align_up(r0.table_bytes);
+      r0.result_off = align_up(table);
       r0.table_bytes = r0.result_off + results;
+      r0.table_off = arena.alloc(r0.table_bytes);
     }
-    r0.table_off = arena.alloc(r0.table_bytes);
+    if (r0.table_off < 0) {  // without the results, each in its own run's memory
+      r0.result_off = -1;
+      r0.table_bytes = table;
+      r0.table_off = arena.alloc(table);
+    }
     if (r0.table_off >= 0) return;
     // no room for the table: the others go back to the front of the queue
     for (size_t q = job.size() - 1; q >= 1; --q) {
