@@ -4,7 +4,8 @@ few tiles.
 A sum whose partial sums in order stay finite is finite, however the kernel
 shares K out.  In complex64, scaling an operand by a power of two scales the
 result, bit for bit, as long as nothing leaves float32's range, and one value
-far below the others changes no other row's bits.
+far below the others changes no other row's bits; values down to float32's
+smallest keep every bit against a large partner.
 """
 import numpy as np
 import pytest
@@ -103,3 +104,56 @@ def test_a_tiny_value_leaves_other_rows_alone(ctx, variant, shape):
     rows = np.ones(A.shape[:2], dtype=bool)
     rows[0, 5] = False
     np.testing.assert_array_equal(got[rows], ref[rows])
+
+
+@pytest.mark.parametrize("variant, shape", CALLS, ids=str)
+def test_small_values_keep_every_bit(ctx, variant, shape):
+    """Values whose parts bf16 holds as subnormals or not at all, alone in
+    their rows, against 2^100."""
+    A, B = operands(shape)
+    small = [2.0 ** -140, 2.0 ** -130, 2.0 ** -115 + 2.0 ** -130, 2.0 ** -149, float(np.float32(1.3e-37)),
+             2.0 ** -126 - 2.0 ** -149, float(np.float32(3.7e-33))]
+    l = A.shape[2] - 1
+    for i, x in enumerate(small):
+        A[0, 7 + i] = 0
+        A[0, 7 + i, l] = np.float32(x)
+    B[0, 9, l] = np.float32(2.0 ** 100)
+    print(variant, shape, flush=True)
+    got = gemm(ctx, A, B, variant)
+    for i, x in enumerate(small):
+        assert got[0, 7 + i, 9, 0] == np.float32(x * 2.0 ** 100) and got[0, 7 + i, 9, 1] == 0, x
+
+
+@pytest.mark.parametrize("m", [128, 1024])
+def test_small_values_in_a_fused_job(m):
+    """The same through the server, where the steps of several requests share
+    a launch: every request's result is bitwise its result alone."""
+    ctx = tnc.Context(0, arena_bytes=1 << 30)
+    rng = np.random.Generator(np.random.PCG64(m))
+    nets, plans, k = [], [], 64
+    for r in range(6):
+        A, B = cn(rng, (m, k)), cn(rng, (m, k))
+        A[7] = 0
+        A[7, k - 1] = np.float32(2.0 ** -115 + 2.0 ** -130)
+        A[8, 3] = np.inf if r == 2 else 1.3e-37
+        B[9, k - 1] = np.float32(2.0 ** 100)
+        nets.append(tnc.Network(ctx, [(0, 2), (1, 2)], np.array([m, m, k], dtype=np.int64), (0, 1), [A, B]))
+        plans.append(tnc.Plan(nets[-1], [(0, 1)]))
+    print(f"m {m}: variant {tnc.tnc_plan_get_step(plans[0].handle, 0).variant}", flush=True)
+    alone = [p.contract() for p in plans]
+    tnc.tnc_serve_start(ctx.handle, 1, 64)
+    tnc.tnc_serve_set_fusion(ctx.handle, 8, tnc.FUSE_ALL)
+    outs = [np.zeros(m * m, dtype=np.complex128) for _ in plans]
+    ids = [tnc.tnc_submit(ctx.handle, p.handle, 0, 1, o) for p, o in zip(plans, outs)]
+    for i in ids:
+        tnc.tnc_wait(ctx.handle, i)
+    fused = tnc.tnc_serve_get_stats(ctx.handle)[1]
+    tnc.tnc_serve_stop(ctx.handle)
+    assert fused >= 1
+    for r, (o, a) in enumerate(zip(outs, alone)):
+        np.testing.assert_array_equal(o.view(np.float64), np.asarray(a).reshape(-1).view(np.float64), err_msg=str(r))
+        assert o.reshape(m, m)[7, 9] == 2.0 ** -15 + 2.0 ** -30
+    for p, t in zip(plans, nets):
+        p.close()
+        t.close()
+    ctx.close()
