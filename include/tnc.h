@@ -391,9 +391,9 @@ tnc_status tnc_serve_set_heavy(tnc_ctx ctx, double heavy_flops, int32_t heavy_sl
  * all the requests are one launch each.  Only requests that wait on their
  * launches more than on their arithmetic are fused: planned FLOP below
  * flops_per_launch times the launches of the request's own run
- * (tnc_plan_info.n_launches for a whole-range request; default 2^30, set
- * between a measured 1.05x gain at 4.5e8 FLOP per launch and a 0.96x loss
- * at 4.1e9); heavier requests would lose the overlap of separate streams.  A huge flops_per_launch (e.g. 1e300) fuses every
+ * (tnc_plan_info.n_launches for a whole-range request; default 2^26, set
+ * between a measured 1.25x gain at 4e7 FLOP per launch and a 0.96x loss
+ * at 1.4e8); heavier requests would lose the overlap of separate streams.  A huge flops_per_launch (e.g. 1e300) fuses every
  * light request.  Each request's result is bitwise the one it gets alone:
  * its every output element is computed by the same tile code in the same
  * order.  Applies to admissions from now on; TNC_E_ARG if the context is

@@ -146,11 +146,12 @@ struct Server {
   // A light request is fused only below this many planned FLOP per launch
   // of its own run.  Fusing shares launches; it pays while a run waits on
   // them, and costs the overlap of separate streams once a run's own
-  // arithmetic fills the GPU.  Measured on 8 slots (random grid circuits,
-  // 512 requests): 2.3x the unfused rate at 1.4e7 FLOP per launch (4x5,
-  // depth 10), 1.05x at 4.5e8 (5x5, depth 10), 0.96x at 4.1e9 (5x6, depth
-  // 10); the default, 2^30, lies between the last two.
-  double fuse_flops_per_launch = 1073741824.0;
+  // arithmetic fills the GPU.  Measured on 8 slots (random grid circuits, 512
+  // requests, fused over unfused rate by log2 of FLOP per launch): 24.4 (4x5,
+  // depth 10) 1.13, 24.8 (5x5, 9) 1.14, 25.3 (5x5, 8) 1.25, 27.1 (4x5, 12) 0.96,
+  // 27.4 (4x6, 10) 1.00, 29.2 (5x5, 10) 0.96, 30.4 (5x6, 9) 0.96, 32.0 (4x6, 12)
+  // 0.93; the default, 2^26, lies between the last gain and the first loss.
+  double fuse_flops_per_launch = 67108864.0;
   int64_t n_jobs = 0, n_fused_jobs = 0, n_fused_requests = 0;
   ArenaAllocator arena;
   bool stop = false;
