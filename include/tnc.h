@@ -224,7 +224,8 @@ tnc_status tnc_plan_get_order(tnc_plan plan, int32_t id, int32_t* labels, int32_
 tnc_status tnc_plan_set_max_chunk(tnc_plan plan, int64_t max_chunk);
 /* Time the candidate MFMA workgroup shapes of every GEMM step shape of the
  * plan on the device and keep the fastest (cached per context, and in the
- * file named by the environment variable TNC_AUTOTUNE_CACHE if set).
+ * file named by the environment variable TNC_AUTOTUNE_CACHE if set; lines
+ * of that file that were measured on other kernels are passed over).
  * Untuned steps use a shape-based default.  Synchronous. */
 tnc_status tnc_plan_autotune(tnc_plan plan);
 /* 1 = capture each chunk's launches in a hipGraph and replay it.  A graph is

@@ -152,9 +152,16 @@ int default_variant(tnc_prec prec, tnc_cgemm form, int64_t h, int64_t m, int64_t
   return best;
 }
 
+// Entries of the file count only for the kernels they were measured on: the
+// first field is "generation:precision", and a line of another generation
+// (or of none) is passed over.  The generation goes up whenever kernels behind
+// the variants' numbers change (2: complex64 and split 4M on the bf16 pipe,
+// the shapes for few tiles; 3: split 4M with two stages on their way).
+static constexpr int kTuneGeneration = 3;
+
 std::string TuneKey::str() const {
   std::ostringstream o;
-  o << prec << ' ' << form << ' ' << perm << ' ' << h << ' ' << m << ' ' << n << ' ' << k;
+  o << kTuneGeneration << ':' << prec << ' ' << form << ' ' << perm << ' ' << h << ' ' << m << ' ' << n << ' ' << k;
   return o.str();
 }
 
@@ -162,11 +169,16 @@ void load_tune_cache(Ctx& c) {
   const char* path = std::getenv("TNC_AUTOTUNE_CACHE");
   if (!path) return;
   std::ifstream f(path);
-  TuneKey key;
-  int v = 0;
-  while (f >> key.prec >> key.form >> key.perm >> key.h >> key.m >> key.n >> key.k >> v)
-    if (v >= 0 && v < (runs_4m(key.prec, key.form) ? kAllVariants : kGemmVariants))
-      c.tune_cache[key] = v;
+  std::string line;
+  while (std::getline(f, line)) {
+    std::istringstream in(line);
+    TuneKey key;
+    int generation = 0, v = 0;
+    char colon = 0;
+    if (!(in >> generation >> colon >> key.prec >> key.form >> key.perm >> key.h >> key.m >> key.n >> key.k >> v)) continue;
+    if (generation != kTuneGeneration || colon != ':') continue;
+    if (v >= 0 && v < (runs_4m(key.prec, key.form) ? kAllVariants : kGemmVariants)) c.tune_cache[key] = v;
+  }
 }
 
 static void save_tune_entry(const TuneKey& key, int v) {
