@@ -465,12 +465,21 @@ struct XTile {
       sa = pow2(ea);
       sb = pow2(eb);
       un = pow2(-ea - eb);
-      if (ea & eb) return add_up<true>(d.k, lds, tid, wm, wn, lane);
+      if (ea & eb) return add_up<true>(d.k, true, lds, tid, wm, wn, lane);
     }
-    return add_up<false>(d.k, lds, tid, wm, wn, lane);
+    const bool busy = tc.row0 + wm * 64 < d.m && tc.col0 + wn * 32 * PW < d.n;
+    return add_up<false>(d.k, busy, lds, tid, wm, wn, lane);
+  }
+  // A stage's staging alone.
+  template <bool SCALED, int set>
+  __device__ __forceinline__ void pass(char* nxt, int tid) {
+    each<U>([&](auto u) {
+      each<PIECES>([&](auto q) { piece<SCALED, set, u, q>(nxt, tid); });
+      load_unit<false, set, u>(0, tid);
+    });
   }
   template <bool SCALED>
-  __device__ __forceinline__ bool add_up(int64_t k, char* lds, int tid, int wm, int wn, int lane) {
+  __device__ __forceinline__ bool add_up(int64_t k, bool busy, char* lds, int tid, int wm, int wn, int lane) {
     const int64_t nk = (k + XK - 1) / XK, full = k / XK;
     // stage st goes through register set st % AHEAD
     each<AHEAD>([&](auto q) {
@@ -479,20 +488,33 @@ struct XTile {
     });
     __syncthreads();
     auto buf = [&](int64_t st) { return lds + (st & (BUFS - 1)) * STAGE; };
-    int64_t kt = 0;
-    for (; kt + 3 * AHEAD - 1 < full; kt += AHEAD) {
-      each<AHEAD>([&](auto q) { step<SCALED, true, q>(buf(kt + q), buf(kt + q + AHEAD), tid, wm, wn, lane); });
-      __syncthreads();
-    }
-    for (; kt < nk; kt += AHEAD)
-      each<AHEAD>([&](auto q) {
-        const int64_t st = kt + q;
-        if (q && st >= nk) return;
-        if (st + AHEAD < nk) stage<SCALED, q>(buf(st + AHEAD), tid);
-        if (st + 2 * AHEAD < nk) load<q>(k - (st + 2 * AHEAD) * XK, tid);
-        step<SCALED, false, q>(buf(st), nullptr, tid, wm, wn, lane);
+    // products: a wave with nothing of C only stages (its barriers are the
+    // others', one for one)
+    auto loop = [&](auto products) {
+      int64_t kt = 0;
+      for (; kt + 3 * AHEAD - 1 < full; kt += AHEAD) {
+        each<AHEAD>([&](auto q) {
+          if constexpr (decltype(products)::value)
+            step<SCALED, true, q>(buf(kt + q), buf(kt + q + AHEAD), tid, wm, wn, lane);
+          else
+            pass<SCALED, q>(buf(kt + q + AHEAD), tid);
+        });
         __syncthreads();
-      });
+      }
+      for (; kt < nk; kt += AHEAD)
+        each<AHEAD>([&](auto q) {
+          const int64_t st = kt + q;
+          if (q && st >= nk) return;
+          if (st + AHEAD < nk) stage<SCALED, q>(buf(st + AHEAD), tid);
+          if (st + 2 * AHEAD < nk) load<q>(k - (st + 2 * AHEAD) * XK, tid);
+          if constexpr (decltype(products)::value) step<SCALED, false, q>(buf(st), nullptr, tid, wm, wn, lane);
+          __syncthreads();
+        });
+    };
+    if (EXACT || busy)
+      loop(std::true_type{});
+    else
+      loop(std::false_type{});
     if constexpr (!EXACT) return true;
     acc[1][NJ - 1] += t[1][0];
     float s = 0.f;  // NaN if any sum is not finite
