@@ -323,10 +323,9 @@ def fusion_leg(ctx, tnc, n: int = 512):
     and without; the results are compared bitwise.  Three mixes of 64 random
     circuits each (different gates and bitstrings, one network shape, so one
     path and slicing), by planned FLOP per launch of a request's own run:
-    4x5-grid circuits of depth 10 (1 sliced label, 2.4e8 FLOP over 18
-    launches per amplitude: launch-bound), 5x5 of depth 10 (2 sliced labels,
-    8.9e9 over 20) and 5x6 of depth 10 (2 sliced labels, 9.8e10 over 24:
-    bound by the GPU's arithmetic).  Where the server's default criterion
+    4x5-grid circuits of depth 10 (1 sliced label, 2.4e8 FLOP per amplitude:
+    launch-bound), 5x5 of depth 10 (2 sliced labels, 8.9e9) and 5x6 of depth
+    10 (2 sliced labels, 9.8e10: bound by the GPU's arithmetic).  Where the server's default criterion
     does not fuse a mix, forced fusion is timed for comparison."""
     from workloads.circuits import circuit_network, random_circuit
     from workloads.paths import greedy_path, greedy_slice

@@ -61,10 +61,14 @@ typedef enum {
 
 /* Arithmetic of the GEMMs.  C64: complex64 operands, float32 products and
  * accumulation (the paper's setting, Sec. V).  MFMA steps run on the bf16
- * matrix pipe with every operand split exactly into three bf16 parts; the
- * error against exact arithmetic is below that of a chain of float32 FMAs,
- * and values that such a split cannot hold (infinities, NaNs, the far ends
- * of the exponent range) are computed on the FP32 pipe.  BF16X3: each
+ * matrix pipe with every operand, of whatever size, split exactly into three
+ * bf16 parts, and six of the nine products of the parts (the others are
+ * below 2^-24 of the whole).  The error against exact arithmetic is below that
+ * of a chain of float32 FMAs where six or more real terms that are not zero
+ * add up (rms 0.9 of it at six, 0.5 at 64, 0.3 for long dense sums); with fewer
+ * it is up to 1.5 times that, and one term alone comes out within 2.7 * 2^-24
+ * of itself (an FMA: 2^-24).  Infinities, NaNs and sums past 2^80 are computed on the
+ * FP32 pipe.  BF16X3: each
  * float32 operand plane is split into bf16 hi + lo (round to nearest even)
  * and every real product is a_hi*b_hi + a_hi*b_lo + a_lo*b_hi on bf16 MFMA
  * with FP32 accumulate (an extension, not in the paper). */
@@ -192,7 +196,9 @@ typedef struct {
   int32_t natural;
   int32_t kernel;                /* 0 = MFMA tiles, 1 = small-shape VALU kernel,
                                     2 = long-K dot kernel (k large, m*n tiny)  */
-  int32_t variant;               /* MFMA workgroup shape (autotuned)           */
+  int32_t variant;               /* MFMA workgroup shape (autotuned): 0 ..
+                                    tnc_gemm_variant_count() - 1, or 7 to 9, the
+                                    shapes for few tiles, which nobody can force */
   int32_t swapped;               /* 1 = the GEMM runs transposed (B supplies
                                     the rows) because that fills MFMA tiles   */
   int32_t split;                 /* K cut into this many parts (split-K)       */
@@ -321,25 +327,29 @@ tnc_status tnc_plan_result_norm2(tnc_plan plan, double* out);
  * Operand permutation (a bit copy): out[pi(idx)] = in[idx] for a complex64
  * tensor of `rank` modes with extents in[rank] (input order); perm[j] = the
  * input mode that becomes output mode j.  in/out: device pointers, must not
- * overlap.  Asynchronous on the context's stream.  TNC_E_ARG for an extent
+ * overlap.  Asynchronous on the context's stream, except that a call whose
+ * index tables (permutations of more than 65536 tiles have them) outgrow the
+ * context's area waits for the stream and allocates: the first such call, which
+ * takes 1 MiB, and any that needs more.  TNC_E_ARG for an extent
  * below 1, a size past 2^60 elements or a perm that is not a permutation
  * (checked before any device work); TNC_E_UNSUPPORTED on a host-only
  * context or above 64 modes. */
 tnc_status tnc_permute(tnc_ctx ctx, const void* in, void* out, int32_t rank,
                        const int64_t* extents, const int32_t* perm);
 /* The same permutation for callers that cannot allocate device memory
- * (code under stream capture, tight serving loops, harnesses that forbid
- * allocation): same arguments, checks and result as tnc_permute, but the
- * permutation's index tables go to a fixed device-resident table area of
- * 1 MiB per GPU that the library holds from its first context on that GPU
- * until the process ends, instead of memory the library allocates.
+ * (tight serving loops, harnesses that forbid allocation): same arguments,
+ * checks and result as tnc_permute, but index tables, where there are any, go
+ * to a fixed device-resident table area of 1 MiB per GPU that the library
+ * holds from its first context on that GPU until the process ends, instead of
+ * memory the library allocates, and no call waits on the host.
  * TNC_E_NOMEM if the tables need more than 1 MiB (decided on the host
  * before any device work; the tables of a 2^30-element permutation take
- * about 130 KiB).  Every call on one GPU shares that area: its launches are
- * ordered behind those of the call before it, whatever their streams and
- * threads.  Neither form waits on the host, and neither can be captured in a
- * graph (TNC_E_DEVICE), except small permutations that run as a plain
- * gather: they use no tables. */
+ * about 130 KiB).  Every call with tables on one GPU shares that area: its
+ * launches are ordered behind those of the call before it, whatever their
+ * streams and threads.  Under stream capture either form runs permutations
+ * that can do without tiles (small ones, and those from 2^18 elements whose
+ * tiles are only the faster way) as a plain gather, and refuses the others
+ * (TNC_E_DEVICE). */
 tnc_status tnc_permute_noalloc(tnc_ctx ctx, const void* in, void* out, int32_t rank,
                                const int64_t* extents, const int32_t* perm);
 /* Batched complex GEMM with both operands K-contiguous:
@@ -388,7 +398,7 @@ tnc_status tnc_serve_set_heavy(tnc_ctx ctx, double heavy_flops, int32_t heavy_sl
  * one run: every MFMA step is one grouped launch over the requests' GEMMs
  * of that step (one persistent kernel whose workgroups loop over the tiles
  * of all of them; every tile variant but split precision's 3 in 3M, whose
- * steps are one launch per request), and every tree level's small GEMMs and leaf gathers of
+ * steps are one launch per request, and even k only), and every tree level's small GEMMs and leaf gathers of
  * all the requests are one launch each.  Only requests that wait on their
  * launches more than on their arithmetic are fused: planned FLOP below
  * flops_per_launch times the launches of the request's own run

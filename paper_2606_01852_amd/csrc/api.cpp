@@ -685,7 +685,9 @@ PermuteJob plan_permute(int32_t rank, const int64_t* extents, const int32_t* per
 // Whether a stand-alone permute runs as a plain gather.  The table areas are
 // shared by calls, in stream order: a graph that had captured one would share
 // it with calls made outside its stream's order, so a tiled permutation is
-// refused under capture (and one that need not be tiled is not tiled there).
+// refused under capture, with tables or (permute_direct) without, so that the
+// number of its tiles does not decide; one that need not be tiled is not tiled
+// there.
 bool runs_plain(const PermuteJob& j, hipStream_t s) {
   if (!j.shape.tiled) return true;
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;

@@ -13,6 +13,10 @@
 // one rounding at the accumulator's size per 16 terms instead of 16.  Error
 // against the FP32 MFMA's, k = 16 .. 16384: 0.42 .. 0.26 of it for CN(0,1)
 // operands, 0.55 .. 0.36 for real ones, 0.79 .. 0.44 for magnitudes over 2^30.
+// Sums of few terms pay for the products left out and for the MFMA's cutting
+// bits off where an FMA rounds: rms, in units of 2^-24 of the terms' size, FP32
+// MFMA and here, one real term that is not zero 0.42 and 0.58 (largest 1.0 and
+// 2.7), two 0.44 and 0.63, four 0.45 and 0.49, six 0.46 and 0.42, 64 0.47 and 0.23.
 // (With the six products accumulated in place: 0.64 .. 1.05, 0.9 .. 1.3 and
 // 1.0 .. 1.6, at 3 % less time: not kept.)
 //

@@ -216,7 +216,8 @@ hipError_t launch_gemm(const GemmDesc& d, GemmKernel kind, int variant, Form for
 // one persistent launch whose workgroups loop over the tiles of all of them.
 // Every tile is computed exactly as the single-GEMM kernel of that variant
 // computes it, so each result is bitwise the same as a launch of its own.
-// Entries need even k and row stride.  Every shape of the 4M kernels has a
+// grouped_layout takes entries of even k and row stride (the 3M kernels read
+// pairs; the 4M kernels could do without).  Every shape of the 4M kernels has a
 // grouped form, of split precision's 3M form every one but 3
 // (grouped_variant_ok); other launches fail with hipErrorInvalidValue.
 struct GroupedEntry {
